@@ -7,34 +7,9 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "panel_exchange.h"
 
 namespace {
-
-// Barrier that orders LDS only, so that global loads issued before it stay in
-// flight across it.
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
-// (value, index) argmax: larger value wins, equal values go to the smaller
-// index (the first maximum, as in BLAS idamax).  NaN never wins.
-__device__ __forceinline__ void argmax_merge(double &v, int &idx, double ov, int oidx) {
-    if (ov > v || (ov == v && oidx < idx)) {
-        v = ov;
-        idx = oidx;
-    }
-}
-
-__device__ __forceinline__ void wave_argmax(double &v, int &idx) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        const double ov = __shfl_xor(v, off);
-        const int oi = __shfl_xor(idx, off);
-        argmax_merge(v, idx, ov, oi);
-    }
-}
 
 // ---------------------------------------------------------------------------
 // PFACT leaf: columns [r0, r0 + w) of rows [r0, r0 + m), w <= kLeafW.
@@ -71,8 +46,6 @@ __device__ __forceinline__ void wave_argmax(double &v, int &idx) {
 // high), the row index, one unused word and the candidate's leaf row (two
 // words per value); `rowj` is [2][kRowWords].
 // ---------------------------------------------------------------------------
-constexpr int kRowWords = 2 * mxlu::kLeafW;      // a leaf row, two words per value
-constexpr int kSlotWords = 4 + kRowWords;
 constexpr int kOnePhaseGroups = 8;               // one-batch gather up to this many groups
 // the gathers are done by wave 0 alone: fewer pollers on the same lines
 constexpr int kOneBatch = (kOnePhaseGroups * kSlotWords + 63) / 64;
@@ -80,65 +53,6 @@ constexpr int kCandPerLane = (mxlu::kMaxGroups * 3 + 63) / 64;
 constexpr int kWordsLds = (kOnePhaseGroups * kSlotWords > mxlu::kMaxGroups * 3)
                               ? kOnePhaseGroups * kSlotWords
                               : mxlu::kMaxGroups * 3;
-
-__device__ __forceinline__ void ll_store(uint64_t *p, uint32_t seq, uint32_t payload) {
-    __hip_atomic_store(p, ((uint64_t)seq << 32) | payload, __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
-}
-
-__device__ __forceinline__ uint64_t ll_load(const uint64_t *p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Payload of *p once it carries `seq`; x is a load of *p already issued.
-__device__ __forceinline__ uint32_t ll_wait(const uint64_t *p, uint64_t x, uint32_t seq,
-                                           int *flags) {
-    long spins = 0;
-    while ((uint32_t)(x >> 32) != seq) {
-        if ((spins & 1023) == 0) {
-            // once any wait has expired the results are invalid: later waits
-            // give up at their first check instead of spinning
-            if (__hip_atomic_load(&flags[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
-            if (spins > (1L << 22)) {
-                atomicExch(&flags[1], 1);
-                break;
-            }
-        }
-        ++spins;
-        __builtin_amdgcn_s_sleep(1);
-        x = ll_load(p);
-    }
-    return (uint32_t)x;
-}
-
-// Wait until each word x[k] with bit k of `valid` carries `seq` (x holds
-// loads already issued; addr(k) is the word's address).  Every round re-issues
-// the loads of all words still stale at once, so a round costs one load
-// latency however many words are late; the loop is wave-uniform.
-template <int K, class Addr>
-__device__ __forceinline__ void ll_gather(uint64_t (&x)[K], uint32_t valid, Addr addr, uint32_t seq,
-                                          int *flags) {
-    long rounds = 0;
-    while (true) {
-        uint32_t stale = 0;
-#pragma unroll
-        for (int k = 0; k < K; ++k)
-            if (((valid >> k) & 1u) && (uint32_t)(x[k] >> 32) != seq) stale |= 1u << k;
-        if (__builtin_amdgcn_ballot_w64(stale != 0) == 0) break;
-        if ((rounds & 63) == 0) {
-            if (__hip_atomic_load(&flags[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
-            if (rounds > (1L << 22)) {
-                atomicExch(&flags[1], 1);
-                break;
-            }
-        }
-        ++rounds;
-        __builtin_amdgcn_s_sleep(1);
-#pragma unroll
-        for (int k = 0; k < K; ++k)
-            if ((stale >> k) & 1u) x[k] = ll_load(addr(k));
-    }
-}
 
 template <typename T>
 __global__ __launch_bounds__(256) void panel_leaf_kernel(
@@ -352,36 +266,6 @@ __global__ __launch_bounds__(256) void panel_leaf_kernel(
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ double words_double(const uint32_t *q) {
     return __longlong_as_double((long long)(((uint64_t)q[1] << 32) | q[0]));
-}
-
-template <int CTRL>
-__device__ __forceinline__ void argmax_dpp(double &v, int &idx) {
-    const uint64_t b = (uint64_t)__double_as_longlong(v);
-    const int lo = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)b, CTRL, 0xF, 0xF, false);
-    const int hi = __builtin_amdgcn_update_dpp(0, (int)(uint32_t)(b >> 32), CTRL, 0xF, 0xF, false);
-    const int oi = __builtin_amdgcn_update_dpp(0, idx, CTRL, 0xF, 0xF, false);
-    argmax_merge(v, idx,
-                 __longlong_as_double((long long)(((uint64_t)(uint32_t)hi << 32) | (uint32_t)lo)), oi);
-}
-
-// every lane ends with the wave's (max, first index); all lanes active
-__device__ __forceinline__ void wave_argmax_dpp(double &v, int &idx) {
-    argmax_dpp<0xB1>(v, idx);    // quad_perm [1,0,3,2]
-    argmax_dpp<0x4E>(v, idx);    // quad_perm [2,3,0,1]
-    argmax_dpp<0x124>(v, idx);   // row_ror:4
-    argmax_dpp<0x128>(v, idx);   // row_ror:8 (each row of 16 lanes now agrees)
-    const uint64_t b = (uint64_t)__double_as_longlong(v);
-    double rv = -1.0;
-    int ri = INT_MAX;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-        const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, 16 * r);
-        const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), 16 * r);
-        argmax_merge(rv, ri, __longlong_as_double((long long)(((uint64_t)hi << 32) | lo)),
-                     __builtin_amdgcn_readlane(idx, 16 * r));
-    }
-    v = rv;
-    idx = ri;
 }
 
 struct RegLeafShared {
@@ -737,19 +621,26 @@ static int leaf_lds_budget(int64_t *budget) {
 }
 
 // Workgroups of the register form of the FP64 leaf that one CU can hold.
-static int reg_leaf_occupancy(int rpt) {
-    static int occ[3] = {-1, -1, -1};
-    if (occ[rpt] < 0) {
+static int reg_leaf_occupancy() {
+    static int occ = -1;
+    if (occ < 0) {
         int v = 0;
-        const void *k = rpt == 1 ? (const void *)panel_leaf_reg_kernel<1>
-                                 : (const void *)panel_leaf_reg_kernel<2>;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&v, k, 256, 0) != hipSuccess) {
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
+                &v, (const void *)panel_leaf_reg_kernel<2>, 256, 0) != hipSuccess) {
             (void)hipGetLastError();
             v = 1;
         }
-        occ[rpt] = std::max(1, v);
+        occ = std::max(1, v);
     }
-    return occ[rpt];
+    return occ;
+}
+
+// Wide form: fits with at most kWideMaxGroups groups of 1024 rows, one per
+// CU the leaf may use.  0: does not fit.
+static int64_t wide_leaf_groups(int64_t m, const LeafDevice &d) {
+    const int64_t cus = d.cap > 0 ? std::min<int64_t>(d.cap, d.cus) : d.cus;
+    const int64_t G = (m + 1023) / 1024;
+    return G <= kWideMaxGroups && G <= cus ? G : 0;
 }
 
 // Device facts the leaf planner needs, for the caller's group cap.
@@ -757,8 +648,10 @@ template <typename T>
 static int leaf_device(int cap, mxlu::LeafDevice *d) {
     d->cap = cap;
     d->cus = compute_units();
-    d->occ_reg1 = sizeof(T) == 8 ? reg_leaf_occupancy(1) : 0;
-    d->occ_reg2 = sizeof(T) == 8 ? reg_leaf_occupancy(2) : 0;
+    // the planner's one-row geometry is served by the wide form, which holds
+    // at least as many rows per CU as the two-row form
+    d->occ_reg2 = sizeof(T) == 8 ? reg_leaf_occupancy() : 0;
+    d->occ_reg1 = d->occ_reg2;
     d->elem_bytes = (int)sizeof(T);
     return leaf_lds_budget<T>(&d->lds_budget);
 }
@@ -822,28 +715,24 @@ int panel_leaf(int64_t m, int w, T *P, int64_t ldp, int64_t r0, int32_t *ipiv,
     }
     LeafDevice dev;
     MXLU_TRY(leaf_device<T>(ex.group_cap, &dev));
-    if (w != kLeafW) dev.occ_reg1 = dev.occ_reg2 = 0;   // the register form takes full leaves
+    if (const int64_t Gw = wide_leaf_groups(m, dev))
+        return panel_leaf_wide<T>(m, w, P, ldp, r0, ipiv, (int)Gw, ex, s);
+    // taller than the wide form: two rows per thread in 256-thread groups
+    // (full FP64 leaves), else the rows in LDS
+    dev.occ_reg1 = 0;
+    if (w != kLeafW) dev.occ_reg2 = 0;
     int64_t R = 0, G = 0;
     const int form = leaf_plan(m, dev, &R, &G);
     if (form == kLeafNone) {
         set_error_msg("panel_leaf: panel too tall for the LDS of the device");
         return MXLU_E_NOMEM;
     }
-    if (form == kLeafReg1 || form == kLeafReg2) {
-        const int64_t Gr = G;
-        {
-            double *Pd = reinterpret_cast<double *>(P);
-            if (form == kLeafReg1)
-                hipLaunchKernelGGL(panel_leaf_reg_kernel<1>, dim3((unsigned)Gr), dim3(256), 0, s,
-                                   (int)m, w, Pd, ldp, (int)Gr, r0, ipiv + r0, ex.slots, ex.rowj,
-                                   ex.flags);
-            else
-                hipLaunchKernelGGL(panel_leaf_reg_kernel<2>, dim3((unsigned)Gr), dim3(256), 0, s,
-                                   (int)m, w, Pd, ldp, (int)Gr, r0, ipiv + r0, ex.slots, ex.rowj,
-                                   ex.flags);
-            MXLU_LAUNCH_CHECK();
-            return 0;
-        }
+    if (form == kLeafReg2) {
+        double *Pd = reinterpret_cast<double *>(P);
+        hipLaunchKernelGGL(panel_leaf_reg_kernel<2>, dim3((unsigned)G), dim3(256), 0, s, (int)m, w,
+                           Pd, ldp, (int)G, r0, ipiv + r0, ex.slots, ex.rowj, ex.flags);
+        MXLU_LAUNCH_CHECK();
+        return 0;
     }
     const size_t lds = (size_t)sizeof(T) * kLeafW * R;
     static bool attr_set = false;

@@ -1,0 +1,8 @@
+// The PFACT leaf's wide form for FP32 panels (a source of its own: it compiles
+// beside the other precision).
+#include "panel_wide.h"
+
+namespace mxlu {
+template int panel_leaf_wide<float>(int64_t, int, float *, int64_t, int64_t, int32_t *, int,
+                                  const PanelExchange &, hipStream_t);
+}  // namespace mxlu

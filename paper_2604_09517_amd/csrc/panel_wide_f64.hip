@@ -1,0 +1,8 @@
+// The PFACT leaf's wide form for FP64 panels (a source of its own: it compiles
+// beside the other precision).
+#include "panel_wide.h"
+
+namespace mxlu {
+template int panel_leaf_wide<double>(int64_t, int, double *, int64_t, int64_t, int32_t *, int,
+                                  const PanelExchange &, hipStream_t);
+}  // namespace mxlu

@@ -454,3 +454,42 @@ def test_results_independent_of_scratch_contents(api, lookahead):
     assert torch.equal(out[0][1], out[1][1])
     assert torch.equal(out[0][0], out[1][0])
     assert torch.equal(out[0][2], out[1][2])
+
+
+# ----------------------------------------------- leaf on few workgroups
+@pytest.mark.parametrize("m,nb", [(1, 1), (33, 33), (64, 32), (255, 7), (256, 40), (257, 32),
+                                  (1023, 33), (1024, 64), (1025, 31), (2049, 72), (9000, 32),
+                                  (65536, 32)])
+def test_panel_leaf_geometries_match_oracle(api, m, nb):
+    """The leaf at the edges of its geometries: one workgroup of 256 threads
+    (up to 256 rows), one of 512 with two rows each (up to 1024), several with
+    an exchange (up to 65536 rows), leaves narrower than 32 columns.  Pivots
+    identical to the oracle's; values within the 1e-12 of the other panel
+    test (the in-panel products differ from the oracle's in rounding only)."""
+    note(f"panel leaf m={m} nb={nb}")
+    P = inputs.uniform_matrix(900 + m % 97, 0, m, nb)
+    dP = to_dev(P, ld=m + (3 if m % 2 else 0))
+    _, ipiv, info = api.panel_factor(dP)
+    torch.cuda.synchronize()
+    Pref, piv_ref, info_ref = oracle.panel_getrf(P)
+    assert info == info_ref == 0
+    assert np.array_equal(ipiv.cpu().numpy(), piv_ref)
+    assert np.abs(dP.cpu().numpy() - Pref).max() <= 1e-12 * max(1.0, np.abs(Pref).max())
+
+
+@pytest.mark.parametrize("m", [200, 900, 3000])
+def test_panel_leaf_ties_and_zero_column(api, m):
+    """Equal magnitudes take the smallest current row in every geometry, and
+    an exactly zero column (column 5 repeats column 2; whether its remainder
+    is exactly zero depends on the pivots, the oracle says) is reported and
+    left unscaled."""
+    rng = np.random.default_rng(m)
+    P = rng.integers(-1, 2, (m, 32)).astype(np.float64)
+    P[:, 5] = P[:, 2]
+    dP = to_dev(P)
+    _, ipiv, info = api.panel_factor(dP)
+    torch.cuda.synchronize()
+    Pref, piv_ref, info_ref = oracle.panel_getrf(P)
+    note(f"panel leaf ties m={m} info {info_ref}")
+    assert info == info_ref
+    assert np.array_equal(ipiv.cpu().numpy(), piv_ref)
