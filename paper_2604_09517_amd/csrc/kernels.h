@@ -84,9 +84,6 @@ int swap_compose(const int32_t *ipiv, int64_t j0, int cnt, int64_t nrows, int *m
 // The interchanges of every step applied to the columns left of its panel,
 // deferred to after the factorization (each element moves once).  q, r: n
 // ints of scratch; T: (n - nb) x nb doubles of scratch.
-// y -= A x (one right-hand side; A is M x K, column-major), deterministic.
-int gemv_f64_sub(int64_t M, int64_t K, const double *A, int64_t lda, const double *x, double *y,
-                 hipStream_t s);
 int laswp_left_deferred_f64(double *A, int64_t lda, int64_t n, int64_t nb,
                             const int32_t *ipiv, int *moves, int32_t *q, int32_t *r, double *T,
                             hipStream_t s);
@@ -105,18 +102,6 @@ int laswp_f64(double *A, int64_t lda, int64_t nrows, const int32_t *ipiv, int64_
 // B(kb x ncols) = L^-1 B with L unit lower (kb x kb), kb <= 256.
 int trsm_llnu_f64(int kb, int64_t ncols, const double *L, int64_t ldl, double *B,
                   int64_t ldb, hipStream_t s);
-// B(kb x ncols) = U^-1 B with U upper, non-unit (kb <= 256).
-// One right-hand side y (bb <= 256 values) through the diagonal block T:
-// lower = unit lower forward, else upper (non-unit) backward.
-int trsv_block_f64(int bb, bool lower, const double *T, int64_t ldt, double *y, hipStream_t s);
-int trsm_lunn_f64(int kb, int64_t ncols, const double *U, int64_t ldu, double *B,
-                  int64_t ldb, hipStream_t s);
-// B(kb x ncols) = U^-T B (U upper non-unit) and B = L^-T B (L unit lower).
-int trsm_lutn_f64(int kb, int64_t ncols, const double *U, int64_t ldu, double *B,
-                  int64_t ldb, hipStream_t s);
-int trsm_lltu_f64(int kb, int64_t ncols, const double *L, int64_t ldl, double *B,
-                  int64_t ldb, hipStream_t s);
-
 class Scratch;
 extern std::atomic<int> g_expire_waits;
 // Zeroed exchange area of the panel kernels for a matrix of order n.
@@ -129,18 +114,13 @@ template <typename T>
 int panel_factor(T *P, int64_t ldp, int64_t m, int64_t kb, int64_t ibase, int32_t *ipiv,
                  const PanelExchange &ex, int *moves, hipStream_t s);
 
-// C(M x N) -= A(K x M)^T * B(K x N), N <= 16 (transposed solves' updates).
-int gemm_f64_sub_tn_skinny(int64_t M, int64_t N, int64_t K, const double *A, int64_t lda,
-                           const double *B, int64_t ldb, double *C, int64_t ldc,
-                           hipStream_t s);
-
 // perm[i] = original row at position i after the interchanges ipiv[0..n).
 int perm_from_ipiv(int64_t n, const int32_t *ipiv, int32_t *perm, hipStream_t s);
-// Y(i, c) = B(perm[i], c)  (gather)   /   B(perm[i], c) = Y(i, c)  (scatter)
-int gather_rows_f64(int64_t n, int64_t nrhs, const int32_t *perm, const double *B,
-                    int64_t ldb, double *Y, int64_t ldy, hipStream_t s);
-int scatter_rows_f64(int64_t n, int64_t nrhs, const int32_t *perm, const double *Y,
-                     int64_t ldy, double *B, int64_t ldb, hipStream_t s);
+// A X = B (trans: A^T X = B) in place for nr <= 16 right-hand sides from the
+// factors LU and the gather map perm of their interchanges; E: n x nr doubles
+// of scratch (leading dimension lde).
+int tri_solve_f64(int64_t n, int nr, const double *LU, int64_t lda, const int32_t *perm, double *B,
+                  int64_t ldb, int trans, double *E, int64_t lde, hipStream_t s);
 
 // Streams of the mixed-precision factorization's look-ahead: `panel` factors
 // the next panel while the rest of the trailing update runs on the caller's

@@ -565,71 +565,9 @@ int solve_impl(int64_t n, int64_t nrhs, const double *LU, int64_t lda, const int
                double *B, int64_t ldb, int trans, hipStream_t s, int32_t *perm, double *Y) {
     PhaseScope ph(kPhaseSolve, s, 8.0 * (double)n * (double)n);
     MXLU_TRY(perm_from_ipiv(n, ipiv, perm, s));
-    // Work on strips of at most 16 right-hand sides.
-    const int64_t bs = 256;
-    const int64_t ldy = n;
-    for (int64_t r0 = 0; r0 < nrhs; r0 += 16) {
-        const int64_t nr = std::min<int64_t>(16, nrhs - r0);
-        double *Bc = B + (size_t)r0 * (size_t)ldb;
-        if (trans == 0) {
-            MXLU_TRY(gather_rows_f64(n, nr, perm, Bc, ldb, Y, ldy, s));
-            // L y = P b: diagonal blocks forward, updates below
-            for (int64_t b0 = 0; b0 < n; b0 += bs) {
-                const int64_t bb = std::min(bs, n - b0);
-                if (nr == 1)
-                    MXLU_TRY(trsv_block_f64((int)bb, true, &MXLU_AT(LU, b0, b0, lda), lda, Y + b0, s));
-                else
-                    MXLU_TRY(trsm_llnu_f64((int)bb, nr, &MXLU_AT(LU, b0, b0, lda), lda, Y + b0, ldy,
-                                           s));
-                if (b0 + bb < n && nr == 1)
-                    MXLU_TRY(gemv_f64_sub(n - b0 - bb, bb, &MXLU_AT(LU, b0 + bb, b0, lda), lda, Y + b0,
-                                          Y + b0 + bb, s));
-                else if (b0 + bb < n)
-                    MXLU_TRY(gemm_f64_sub(n - b0 - bb, nr, bb, &MXLU_AT(LU, b0 + bb, b0, lda), lda,
-                                     Y + b0, ldy, Y + b0 + bb, ldy, s));
-            }
-            // U x = y: diagonal blocks backward, updates above
-            const int64_t nblk = (n + bs - 1) / bs;
-            for (int64_t bi = nblk - 1; bi >= 0; --bi) {
-                const int64_t b0 = bi * bs, bb = std::min(bs, n - b0);
-                if (nr == 1)
-                    MXLU_TRY(trsv_block_f64((int)bb, false, &MXLU_AT(LU, b0, b0, lda), lda, Y + b0, s));
-                else
-                    MXLU_TRY(trsm_lunn_f64((int)bb, nr, &MXLU_AT(LU, b0, b0, lda), lda, Y + b0, ldy,
-                                           s));
-                if (b0 > 0 && nr == 1)
-                    MXLU_TRY(gemv_f64_sub(b0, bb, &MXLU_AT(LU, 0, b0, lda), lda, Y + b0, Y, s));
-                else if (b0 > 0)
-                    MXLU_TRY(gemm_f64_sub(b0, nr, bb, &MXLU_AT(LU, 0, b0, lda), lda, Y + b0, ldy, Y,
-                                     ldy, s));
-            }
-            // copy back
-            MXLU_HIP_TRY(hipMemcpy2DAsync(Bc, sizeof(double) * ldb, Y, sizeof(double) * ldy,
-                                          sizeof(double) * n, nr, hipMemcpyDeviceToDevice, s));
-        } else {
-            MXLU_HIP_TRY(hipMemcpy2DAsync(Y, sizeof(double) * ldy, Bc, sizeof(double) * ldb,
-                                          sizeof(double) * n, nr, hipMemcpyDeviceToDevice, s));
-            // U^T y = b: forward; block b0 first takes the contributions of
-            // the solved rows above it
-            for (int64_t b0 = 0; b0 < n; b0 += bs) {
-                const int64_t bb = std::min(bs, n - b0);
-                if (b0 > 0)
-                    MXLU_TRY(gemm_f64_sub_tn_skinny(bb, nr, b0, &MXLU_AT(LU, 0, b0, lda), lda, Y, ldy,
-                                               Y + b0, ldy, s));
-                MXLU_TRY(trsm_lutn_f64((int)bb, nr, &MXLU_AT(LU, b0, b0, lda), lda, Y + b0, ldy, s));
-            }
-            // L^T z = y: backward; block first takes the rows below it
-            const int64_t nblk = (n + bs - 1) / bs;
-            for (int64_t bi = nblk - 1; bi >= 0; --bi) {
-                const int64_t b0 = bi * bs, bb = std::min(bs, n - b0);
-                if (b0 + bb < n)
-                    MXLU_TRY(gemm_f64_sub_tn_skinny(bb, nr, n - b0 - bb, &MXLU_AT(LU, b0 + bb, b0, lda),
-                                               lda, Y + b0 + bb, ldy, Y + b0, ldy, s));
-                MXLU_TRY(trsm_lltu_f64((int)bb, nr, &MXLU_AT(LU, b0, b0, lda), lda, Y + b0, ldy, s));
-            }
-            MXLU_TRY(scatter_rows_f64(n, nr, perm, Y, ldy, Bc, ldb, s));
-        }
-    }
+    for (int64_t r0 = 0; r0 < nrhs; r0 += 16)   // strips of at most 16 right-hand sides
+        MXLU_TRY(tri_solve_f64(n, (int)std::min<int64_t>(16, nrhs - r0), LU, lda, perm,
+                               B + (size_t)r0 * (size_t)ldb, ldb, trans, Y, n, s));
     return 0;
 }
 

@@ -1,0 +1,456 @@
+// Triangular solves with the FP64 factors (the solve phase of Sec. III-A.1 and
+// its transpose) for up to 16 right-hand sides at a time, and the row
+// permutation that the interchanges amount to.
+#include <hip/hip_runtime.h>
+
+#include <climits>
+#include <type_traits>
+
+#include "common.h"
+#include "kernels.h"
+
+namespace {
+
+typedef double v4d __attribute__((ext_vector_type(4)));
+
+// Barrier that orders LDS only, so that global loads issued before it stay in
+// flight across it.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// LDS written by some lanes of a wave is read by others after this
+__device__ __forceinline__ void wave_sync_lds() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// ---------------------------------------------------------------------------
+// perm: the gather map of all interchanges of ipiv applied in order (row i of
+// P b is b[perm[i]]).  Each lane follows one row back through the
+// interchanges, last to first, to the row its content comes from; a row below
+// i is not touched by the interchanges after i, so a wave starts at its last
+// row.  The interchanges are uniform over the wave (scalar loads); a step is
+// two compares and two selects, about 20 cycles.  One workgroup that composed
+// them 256 at a time took 67 us at n = 1024 and 2430 us at n = 32768; this
+// form takes 9 and 280.  An entry outside [u, n) is taken as no interchange.
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(64) void perm_from_ipiv_kernel(int n, const int32_t *__restrict__ ipiv,
+                                                            int32_t *__restrict__ perm) {
+    const int i = (int)blockIdx.x * 64 + (int)threadIdx.x;
+    int src = i;
+    int u = (int)min((int64_t)n, ((int64_t)blockIdx.x + 1) * 64) - 1;
+    auto step = [&](int uu, int qq) {
+        const int q = (qq >= uu && qq < n) ? qq : uu;
+        src = (src == uu) ? q : ((src == q) ? uu : src);
+    };
+    for (; (u & 15) != 15 && u >= 0; --u) step(u, ipiv[u]);
+    for (; u >= 0; u -= 16) {
+        int q[16];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) q[e] = ipiv[u - 15 + e];
+#pragma unroll
+        for (int e = 15; e >= 0; --e) step(u - 15 + e, q[e]);
+    }
+    if (i < n) perm[i] = src;
+}
+
+// ---------------------------------------------------------------------------
+// T X = B for up to 16 right-hand sides in one launch, T one of
+//   KIND 0: L (unit lower), forward      KIND 1: U (upper), backward
+//   KIND 2: U^T (lower), forward         KIND 3: L^T (unit upper), backward
+// Workgroup w owns the w-th block of kTriRows rows in solve order; wave v of
+// it owns 16 of those rows, with all right-hand sides as one 16 x 16 FP64
+// matrix-core accumulator.  It applies the solutions of the earlier blocks as
+// they appear (their factor entries are loaded one block ahead), then solves
+// its own block 16 rows at a time: the owning wave by substitution, four rows
+// a step, the later waves apply the result with the matrix cores.
+//
+// What bounds it is the chain of blocks, not the n^2 / 2 factor entries: per
+// block one trip of the solution from workgroup to workgroup and eight
+// dependent 16-row solves.  Blocks of 128 rows share that trip among more
+// rows than smaller ones and still leave n / 128 compute units streaming the
+// factor.  Before, every 256 rows took two launches (a diagonal block on one
+// workgroup with a barrier per row, and a row-per-thread update):
+// n = 8192, 16 right-hand sides: 18.0 -> 1.45 ms; n = 32768, one: 12.4 -> 6.
+// (measured with the factors of a matrix of the benchmark recipe).
+// A block takes about 9 us (L) and 10 us (U): eight strips of 2200 to 2600
+// cycles (about 1400 or 1900 of them the substitution's instructions, at four
+// cycles each, the rest the way to the next strip through LDS) and 2 us for
+// the way to the next workgroup.  A substitution with a lane per right-hand
+// side (16 values in registers, factor entries broadcast from LDS) waited for
+// an LDS read every other multiply-add and took 2.5 times as long.
+//
+// A solution value goes to `out` as one 64-bit word, written and read with
+// agent-scope relaxed atomics; the words start as kTriEmpty, a signalling NaN
+// that no arithmetic produces, and a reader polls a word until it holds
+// anything else, so no flags and fences are needed.  Workgroups wait only for
+// smaller ids, which are dispatched first, so the chain advances even when not
+// all are resident.  The polling is bounded: a wait that expires goes on with
+// NaN.
+// ---------------------------------------------------------------------------
+constexpr int kTriRows = 128;
+constexpr int kTriLd = 17;   // LDS row of 16 right-hand sides (odd: columns spread over the banks)
+constexpr uint64_t kTriEmpty = 0x7FF000005EED0001ull;
+
+__global__ __launch_bounds__(256) void tri_clear_kernel(int64_t n, int nr, double *__restrict__ X,
+                                                        int64_t ldx) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+    for (int c = 0; c < nr; ++c)
+        X[(size_t)i + (size_t)c * (size_t)ldx] = __longlong_as_double((long long)kTriEmpty);
+}
+
+__device__ __forceinline__ uint64_t tri_load(const double *p) {
+    return __hip_atomic_load(reinterpret_cast<const uint64_t *>(p), __ATOMIC_RELAXED,
+                             __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// y[q] <- the value that lane (lane % 16) + 16 q of the wave holds
+__device__ __forceinline__ void quarters(double v, double (&y)[4]) {
+    const uint64_t b = (uint64_t)__double_as_longlong(v);
+    uint32_t o[2][4];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const uint32_t d = (uint32_t)(b >> (32 * h));
+        const auto eo = __builtin_amdgcn_permlane16_swap(d, d, false, false);   // rows 0 0 2 2, 1 1 3 3
+        const auto e = __builtin_amdgcn_permlane32_swap(eo[0], eo[0], false, false);
+        const auto f = __builtin_amdgcn_permlane32_swap(eo[1], eo[1], false, false);
+        o[h][0] = e[0];
+        o[h][2] = e[1];
+        o[h][1] = f[0];
+        o[h][3] = f[1];
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+        y[q] = __longlong_as_double((long long)(((uint64_t)o[1][q] << 32) | o[0][q]));
+}
+
+template <int KIND>
+__global__ __launch_bounds__(512) void tri_chain_f64_kernel(
+    int64_t n, int nr, const double *__restrict__ T, int64_t ldt, const double *in, int64_t ldin,
+    const int32_t *__restrict__ inperm, double *out, int64_t ldo,
+    const int32_t *__restrict__ outperm, int nblk) {
+    constexpr bool TR = KIND >= 2, FWD = KIND == 0 || KIND == 2, UNIT = KIND == 0 || KIND == 3;
+    constexpr int BS = kTriRows, NS = BS / 16;
+    __shared__ double Xs[2][BS][kTriLd];
+    // tiles of -F of the own block between different strips, in operand order
+    __shared__ double Ot[NS * (NS - 1) / 2][4][64];
+    __shared__ __attribute__((aligned(16))) double Dg[NS][16][16];   // Dg[s][k][i] = F[16s+i][16s+k]
+    __shared__ double Rd[BS];           // reciprocals of the diagonal
+    __shared__ int s_range[NS];         // the strip's diagonal is in the normal range
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int v = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int li = lane & 15, lq = lane >> 4;
+    const int w = blockIdx.x;
+    const int64_t r0 = (int64_t)(FWD ? w : nblk - 1 - w) * BS;
+    const int64_t row = r0 + 16 * v + li;     // this lane's factor row
+    const int64_t rowc = row < n ? row : n - 1;
+    auto block_row = [&](int t) { return (int64_t)(FWD ? t : nblk - 1 - t) * BS; };
+    auto tile = [&](int vv, int s) {   // of strip vv's rows and strip s's columns, s solved before vv
+        const int i = FWD ? vv : NS - 1 - vv, j = FWD ? s : NS - 1 - s;
+        return i * (i - 1) / 2 + j;
+    };
+
+    // -F of the wave's 16 rows, columns p0 .. p0 + BS: lane (li, lq), entry kk
+    // is -F[row][p0 + 4 kk + lq] (F: the effective lower or upper factor);
+    // rows and columns past n are zero
+    auto load_f = [&](int64_t p0, double (&a)[BS / 4]) {
+        if (p0 + BS <= n && r0 + 16 * v + 16 <= n) {   // uniform
+            const double *src = TR ? T + (size_t)(p0 + lq) + (size_t)row * (size_t)ldt
+                                   : T + (size_t)row + (size_t)(p0 + lq) * (size_t)ldt;
+            const size_t st = TR ? 4 : 4 * (size_t)ldt;
+#pragma unroll
+            for (int kk = 0; kk < BS / 4; ++kk) a[kk] = -src[kk * st];
+        } else {
+#pragma unroll
+            for (int kk = 0; kk < BS / 4; ++kk) {
+                const int64_t k = p0 + 4 * kk + lq, kc = k < n ? k : n - 1;
+                const double f = TR ? T[(size_t)kc + (size_t)rowc * (size_t)ldt]
+                                    : T[(size_t)rowc + (size_t)kc * (size_t)ldt];
+                a[kk] = row < n && k < n ? -f : 0.0;
+            }
+        }
+    };
+    auto word = [&](int64_t g, int c) -> const double * {
+        return out + (size_t)(outperm ? outperm[g] : g) + (size_t)c * (size_t)ldo;
+    };
+    // solution words of the block at p0: thread (row tid % BS, right-hand
+    // sides tid / BS + 4 e); rows and columns that do not exist are zero
+    const int xr = tid & (BS - 1), xc = tid / BS;
+    uint64_t xw[4];
+    auto load_x = [&](int64_t p0) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            xw[e] = (p0 + xr < n && xc + 4 * e < nr) ? tri_load(word(p0 + xr, xc + 4 * e)) : 0ull;
+    };
+    // wait for them: one lane of the workgroup watches the word that appears
+    // last, with long pauses, so that the many workgroups further down the
+    // chain do not crowd the producer's stores; then every thread reads its
+    // own (looking again at the few that are not there yet)
+    auto await_x = [&](int64_t p0) {
+        if (tid == 0) {
+            const int64_t last = FWD ? (p0 + BS < n ? p0 + BS - 1 : n - 1) : p0;
+            const double *p = word(last, nr - 1);
+            for (int k = 0; k < (1 << 24) && tri_load(p) == kTriEmpty; ++k)   // about 16 s
+                __builtin_amdgcn_s_sleep(16);
+        }
+        __syncthreads();
+        load_x(p0);
+        for (int rounds = 0;; ++rounds) {
+            bool late = false;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) late = late || xw[e] == kTriEmpty;
+            if (__builtin_amdgcn_ballot_w64(late) == 0) return;
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (xw[e] == kTriEmpty)
+                    xw[e] = rounds > 4096 ? 0x7FF8000000000000ull
+                                          : tri_load(word(p0 + xr, xc + 4 * e));
+        }
+    };
+
+    double a[BS / 4], an[BS / 4];
+    // the own block: off-diagonal tiles and the diagonal tile of each strip
+    // (rows past n as the identity) wait in LDS
+    load_f(r0, a);
+#pragma unroll
+    for (int s = 0; s < NS; ++s)
+        if (FWD ? s < v : s > v) {
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk) Ot[tile(v, s)][kk][lane] = a[4 * s + kk];
+        }
+#pragma unroll
+    for (int kk = 0; kk < 4; ++kk) {
+        const int64_t k = r0 + 16 * v + 4 * kk + lq, kc = k < n ? k : n - 1;
+        const double f = TR ? T[(size_t)kc + (size_t)rowc * (size_t)ldt]
+                            : T[(size_t)rowc + (size_t)kc * (size_t)ldt];
+        Dg[v][4 * kk + lq][li] = row < n && k < n ? f : (row == k ? 1.0 : 0.0);
+    }
+    if (!UNIT) {
+        wave_sync_lds();
+        const double d = Dg[v][li][li];
+        if (lq == 0) Rd[16 * v + li] = 1.0 / d;
+        const bool in_range = fabs(d) >= 0x1p-500 && fabs(d) <= 0x1p500;
+        const uint64_t all = __builtin_amdgcn_ballot_w64(in_range);
+        if (lane == 0) s_range[v] = all == ~0ull;
+    }
+    v4d acc;                   // lane (li, lq), register r: row lq + 4 r, right-hand side li
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        const int64_t g = r0 + 16 * v + lq + 4 * r;
+        acc[r] = (g < n && li < nr) ? in[(size_t)(inperm ? inperm[g] : g) + (size_t)li * (size_t)ldin]
+                                    : 0.0;
+    }
+    if (w > 0) load_f(block_row(0), a);
+    for (int t = 0; t + 1 < w; ++t) {
+        await_x(block_row(t));
+        double(*X)[kTriLd] = Xs[t & 1];
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            X[xr][xc + 4 * e] = __longlong_as_double((long long)xw[e]);
+        lds_barrier();
+        load_f(block_row(t + 1), an);
+        // a block's products are summed by themselves: n / 128 partial sums
+        // round less than one running sum of n terms
+        v4d sum = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int kk = 0; kk < BS / 4; ++kk)
+            sum = __builtin_amdgcn_mfma_f64_16x16x4f64(a[kk], X[4 * kk + lq][li], sum, 0, 0, 0);
+        acc += sum;
+#pragma unroll
+        for (int kk = 0; kk < BS / 4; ++kk) a[kk] = an[kk];
+    }
+    // The strip's diagonal tile for the substitution, in solve order: step b
+    // takes rows o(4 b) .. o(4 b + 3).  tri: its 4 x 4 triangle (uniform),
+    // ta: the tile's rows still to come against the step's four columns, as a
+    // matrix-core operand (zero for rows already solved).
+    auto ord = [](int e) { return FWD ? e : 15 - e; };   // row or column of solve order e
+    double tri[4][6], ta[4], dv[4][4], rv[4][4];
+    wave_sync_lds();   // Dg[v], Rd: this wave's own
+#pragma unroll
+    for (int b = 0; b < 4; ++b) {
+#pragma unroll
+        for (int i = 1, e = 0; i < 4; ++i)
+#pragma unroll
+            for (int k = 0; k < i; ++k, ++e) tri[b][e] = Dg[v][ord(4 * b + k)][ord(4 * b + i)];
+        if (!UNIT) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                dv[b][i] = Dg[v][ord(4 * b + i)][ord(4 * b + i)];
+                rv[b][i] = Rd[16 * v + ord(4 * b + i)];
+            }
+        }
+        const int g = FWD ? b : 3 - b;   // rows and columns 4 g .. 4 g + 3
+        ta[b] = (FWD ? li > 4 * g + 3 : li < 4 * g) ? -Dg[v][4 * g + lq][li] : 0.0;
+    }
+    if (w > 0) {
+        // the last earlier block is on the chain's critical path: its strips
+        // are taken one by one as they appear, so that after the last of them
+        // only four matrix instructions per wave remain
+        const int64_t p0 = block_row(w - 1);
+        double(*X)[kTriLd] = Xs[(w - 1) & 1];
+        const int sr = tid & 15, sc = (tid >> 4) & 15;
+        v4d sum = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int j = 0; j < NS; ++j) {
+            const int s = FWD ? j : NS - 1 - j;
+            if (tid < 256) {
+                const int64_t g = p0 + 16 * s + sr;
+                uint64_t x = 0;
+                if (g < n && sc < nr) {
+                    const double *p = word(g, sc);
+                    x = tri_load(p);
+                    for (int spins = 0; x == kTriEmpty; ++spins) {
+                        __builtin_amdgcn_s_sleep(1);
+                        x = tri_load(p);
+                        if (spins > (1 << 24)) x = 0x7FF8000000000000ull;   // about 16 s
+                    }
+                }
+                X[16 * s + sr][sc] = __longlong_as_double((long long)x);
+            }
+            lds_barrier();
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk)
+                sum = __builtin_amdgcn_mfma_f64_16x16x4f64(a[4 * s + kk], X[16 * s + 4 * kk + lq][li],
+                                                           sum, 0, 0, 0);
+        }
+        acc += sum;
+    }
+    // own block, 16 rows at a time
+    double(*X)[kTriLd] = Xs[w & 1];
+    lds_barrier();   // Ot is complete; Xs[w & 1] was last read two blocks ago
+    // Substitution with the wave's tile, four rows a step: the accumulator
+    // keeps rows 4 g .. 4 g + 3 in its register g, one per quarter wave; the
+    // quarters exchange them (lane permutes), every lane solves the four, and
+    // one matrix instruction takes them to the rows still to come.  x: the
+    // solution in accumulator layout.
+    // U: the quotient x / d through r = RN(1 / d), formed ahead of the chain:
+    // q0 = RN(x r), q = RN(q0 + (x - q0 d) r), the correctly rounded quotient
+    // while everything stays in the normal range (Markstein's theorem); DIV
+    // divides.
+    auto substitute = [&](auto div, double (&x)[4]) -> uint32_t {
+        constexpr bool DIV = decltype(div)::value;
+        v4d c = acc;
+        uint32_t top = 0;
+#pragma unroll
+        for (int b = 0; b < 4; ++b) {
+            const int g = FWD ? b : 3 - b;
+            double y[4];
+            quarters(c[g], y);
+            if (!FWD) {   // solve order within the step
+                double t = y[0];
+                y[0] = y[3];
+                y[3] = t;
+                t = y[1];
+                y[1] = y[2];
+                y[2] = t;
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (!UNIT) {
+                    if (DIV) {
+                        y[i] = y[i] / dv[b][i];
+                    } else {
+                        const double q0 = y[i] * rv[b][i];
+                        y[i] = fma(fma(-q0, dv[b][i], y[i]), rv[b][i], q0);
+                        top = max(top, (uint32_t)((uint64_t)__double_as_longlong(y[i]) >> 32) &
+                                           0x7fffffffu);
+                    }
+                }
+#pragma unroll
+                for (int k = i + 1; k < 4; ++k)
+                    y[k] = fma(-tri[b][k * (k - 1) / 2 + i], y[i], y[k]);
+            }
+            const int q = FWD ? lq : 3 - lq;
+            x[g] = q == 0 ? y[0] : q == 1 ? y[1] : q == 2 ? y[2] : y[3];
+            if (b < 3) c = __builtin_amdgcn_mfma_f64_16x16x4f64(ta[b], x[g], c, 0, 0, 0);
+        }
+        return top;
+    };
+    for (int j = 0; j < NS; ++j) {
+        const int s = FWD ? j : NS - 1 - j;
+        if (v == s) {
+            double x[4];
+            const uint32_t top = substitute(std::false_type{}, x);
+            // a diagonal outside [2^-500, 2^500], or a result that is not
+            // finite or above 2^900: with the division (wave-uniform)
+            if (!UNIT && (!__all(top < 0x78300000u) || !s_range[s])) substitute(std::true_type{}, x);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) X[16 * s + lq + 4 * r][li] = x[r];
+        }
+        lds_barrier();
+        if (FWD ? v > s : v < s) {   // wave-uniform: later strips take strip s's solution
+            const double(*O)[64] = Ot[tile(v, s)];
+#pragma unroll
+            for (int kk = 0; kk < 4; ++kk)
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(O[kk][lane], X[16 * s + 4 * kk + lq][li], acc,
+                                                           0, 0, 0);
+        } else if (v == s) {
+            // publish: 16 rows of one right-hand side per quarter wave
+            uint64_t b[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                b[e] = (uint64_t)__double_as_longlong(X[16 * s + li][lq + 4 * e]);
+                if (b[e] == kTriEmpty) b[e] |= 0x0008000000000000ull;   // a quiet NaN then
+            }
+            const int64_t g = r0 + 16 * s + li;
+            if (g < n) {
+                double *o = out + (size_t)(outperm ? outperm[g] : g);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    if (lq + 4 * e < nr)
+                        __hip_atomic_store(
+                            reinterpret_cast<uint64_t *>(o + (size_t)(lq + 4 * e) * (size_t)ldo), b[e],
+                            __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+        }
+    }
+}
+
+template <int KIND>
+int tri_chain(int64_t n, int nr, const double *T, int64_t ldt, const double *in, int64_t ldin,
+              const int32_t *inperm, double *out, int64_t ldo, const int32_t *outperm,
+              hipStream_t s) {
+    const int64_t nblk = (n + kTriRows - 1) / kTriRows;
+    hipLaunchKernelGGL(tri_clear_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, n, nr,
+                       out, ldo);
+    MXLU_LAUNCH_CHECK();
+    hipLaunchKernelGGL(tri_chain_f64_kernel<KIND>, dim3((unsigned)nblk), dim3(512), 0, s, n, nr, T,
+                       ldt, in, ldin, inperm, out, ldo, outperm, (int)nblk);
+    MXLU_LAUNCH_CHECK();
+    return 0;
+}
+
+}  // namespace
+
+namespace mxlu {
+
+int perm_from_ipiv(int64_t n, const int32_t *ipiv, int32_t *perm, hipStream_t s) {
+    if (n <= 0) return 0;
+    hipLaunchKernelGGL(perm_from_ipiv_kernel, dim3((unsigned)((n + 63) / 64)), dim3(64), 0, s,
+                       (int)n, ipiv, perm);
+    MXLU_LAUNCH_CHECK();
+    return 0;
+}
+
+int tri_solve_f64(int64_t n, int nr, const double *LU, int64_t lda, const int32_t *perm, double *B,
+                  int64_t ldb, int trans, double *E, int64_t lde, hipStream_t s) {
+    if (n <= 0 || nr <= 0) return 0;
+    if (nr > 16) {
+        set_error_msg("tri_solve_f64: more than 16 right-hand sides");
+        return MXLU_E_NOMEM;
+    }
+    if (trans == 0) {   // L y = P b, U x = y
+        MXLU_TRY(tri_chain<0>(n, nr, LU, lda, B, ldb, perm, E, lde, nullptr, s));
+        return tri_chain<1>(n, nr, LU, lda, E, lde, nullptr, B, ldb, nullptr, s);
+    }
+    // U^T y = b, L^T z = y, x = P^T z
+    MXLU_TRY(tri_chain<2>(n, nr, LU, lda, B, ldb, nullptr, E, lde, nullptr, s));
+    return tri_chain<3>(n, nr, LU, lda, E, lde, nullptr, B, ldb, perm, s);
+}
+
+}  // namespace mxlu

@@ -493,3 +493,83 @@ def test_panel_leaf_ties_and_zero_column(api, m):
     note(f"panel leaf ties m={m} info {info_ref}")
     assert info == info_ref
     assert np.array_equal(ipiv.cpu().numpy(), piv_ref)
+
+
+# ------------------------------------------------------- solve chain edges
+@pytest.mark.parametrize("trans", [0, 1])
+@pytest.mark.parametrize("n,nrhs", [(2, 1), (15, 16), (16, 3), (17, 2), (127, 5), (128, 16),
+                                    (129, 15), (255, 1), (257, 33), (640, 7)])
+def test_lu_solve_block_edges(api, n, nrhs, trans):
+    """Sizes around the 16-row strips and 128-row blocks of the solve, ragged
+    right-hand-side strips, an odd leading dimension: within the forward-error
+    bound of the other solve test (64 n eps kappa)."""
+    A_h = inputs.uniform_matrix(1500 + n, 0, n, n)
+    B_h = inputs.uniform_matrix(1500 + n, 1, n, nrhs)
+    dA = to_dev(A_h, ld=n + 1)
+    _, ipiv, _ = api.lu_factor(dA, 64)
+    dB = to_dev(B_h, ld=n + 3)
+    api.lu_solve(dA, ipiv, dB, trans=bool(trans))
+    torch.cuda.synchronize()
+    X = dB.cpu().numpy()
+    X_ref = oracle.getrs(dA.cpu().numpy(), ipiv.cpu().numpy(), B_h, trans=bool(trans))
+    kappa = np.linalg.cond(A_h, np.inf)
+    assert np.abs(X - X_ref).max() <= 64 * n * EPS * kappa * np.abs(X_ref).max()
+
+
+@pytest.mark.parametrize("trans", [0, 1])
+def test_lu_solve_quotients_outside_the_reciprocal_range(api, trans):
+    """U scaled by 2^600 takes the division instead of the reciprocal; the
+    scaling is exact, so the solution is the unscaled one times 2^-600 bit for
+    bit (both forms give the correctly rounded quotient)."""
+    n, nrhs = 300, 5
+    A_h = inputs.uniform_matrix(77, 0, n, n)
+    B_h = inputs.uniform_matrix(77, 1, n, nrhs)
+    dA = to_dev(A_h)
+    _, ipiv, _ = api.lu_factor(dA, 64)
+    LU = dA.cpu().numpy()
+    scaled = np.tril(LU, -1) + np.triu(LU) * 2.0 ** 600
+    out = []
+    for F in (LU, scaled):
+        dB = to_dev(B_h)
+        api.lu_solve(to_dev(F), ipiv, dB, trans=bool(trans))
+        torch.cuda.synchronize()
+        out.append(dB.cpu().numpy())
+    assert np.array_equal(out[1], out[0] * 2.0 ** -600)
+
+
+def test_lu_solve_passes_special_values(api):
+    """Infinities and NaNs (the solve's own marker pattern among them) in one
+    right-hand side stay in it and do not stop the chain."""
+    n = 200
+    LU = np.eye(n)
+    B_h = np.ones((n, 3))
+    B_h[3, 1] = np.inf
+    B_h[150, 1] = np.nan
+    marker = np.array([0x7FF000005EED0001], dtype=np.uint64).view(np.float64)[0]
+    dB = to_dev(B_h)
+    dB.view(torch.int64)[0, 2] = 0x7FF000005EED0001
+    ipiv = torch.arange(n, dtype=torch.int32, device="cuda")
+    api.lu_solve(to_dev(LU), ipiv, dB)
+    torch.cuda.synchronize()
+    X = dB.cpu().numpy()
+    assert np.isnan(marker)
+    assert np.array_equal(X[:, 0], np.ones(n))
+    assert np.isnan(X[0, 2]) and not np.isfinite(X[3, 1]) and np.isnan(X[150, 1])
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 1000, 4097])
+def test_solve_permutation_replays_interchanges(api, n):
+    """The gather map of the interchanges against their replay: solving with
+    the identity as factors returns the permuted right-hand side."""
+    rng = np.random.default_rng(n)
+    piv = np.array([rng.integers(i, n) for i in range(n)], dtype=np.int32)
+    perm = np.arange(n)
+    for i, p in enumerate(piv):
+        perm[[i, p]] = perm[[p, i]]
+    b = rng.standard_normal(n)
+    db = torch.from_numpy(b.copy()).cuda()
+    LU = api.fortran_empty(n, n)
+    LU.copy_(torch.eye(n, dtype=torch.float64))
+    api.lu_solve(LU, torch.from_numpy(piv).cuda(), db)
+    torch.cuda.synchronize()
+    assert np.array_equal(db.cpu().numpy(), b[perm])
