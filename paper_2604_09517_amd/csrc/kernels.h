@@ -42,11 +42,6 @@ struct PanelExchange {
 constexpr int kLeafW = 32;        // columns factored by one leaf kernel
 constexpr int kMaxGroups = 256;   // workgroups of one leaf kernel (<= CUs)
 
-// Factor the m x w (w <= kLeafW) leaf whose top-left element is P (leading
-// dimension ldp) with partial pivoting.  r0 is the leaf's first row/column
-// index within the caller's numbering: ipiv[r0 .. r0+w) receives r0 + the
-// pivot row within the leaf; the column numbers r0 + j + 1 are the values of
-// the workgroups' sequence flags, so they must grow from leaf to leaf.
 // Workgroups the leaf kernel launches for an m-row leaf with group cap `cap`
 // (they must all be resident at once), or -1 when no geometry fits.
 template <typename T> int panel_leaf_groups(int64_t m, int cap);
@@ -65,15 +60,30 @@ int leaf_plan(int64_t m, const LeafDevice &d, int64_t *R, int64_t *G);
 // The current device's facts for the FP64 leaf with group cap `cap`.
 int leaf_device_f64(int cap, LeafDevice *d);
 
-// The leaf's wide form (panel_wide.h) on G = ceil(m / 1024) workgroups.
+// The leaf's wide form (panel_wide.h) on G = ceil(m / 1024) workgroups.  *split:
+// as of panel_leaf.
 constexpr int kWideMaxGroups = 64;
 template <typename T>
 int panel_leaf_wide(int64_t m, int w, T *P, int64_t ldp, int64_t r0, int32_t *ipiv, int G,
-                    const PanelExchange &ex, hipStream_t s);
+                    const PanelExchange &ex, int *split, hipStream_t s);
+// Interchanges of the leaf at column c0 (width w) of the m x kb panel P (whose
+// column c0 is row and column rbase of the caller's numbering) on the panel's
+// other columns, and those from column `split` on (split > 0) on the leaf's
+// columns before it.
+template <typename T>
+int panel_leaf_swap(T *P, int64_t ldp, int64_t m, int64_t kb, int64_t c0, int w, int split,
+                    const int32_t *ipiv, int64_t rbase, hipStream_t s);
 
+// Factor the m x w (w <= kLeafW) leaf whose top-left element is P (leading
+// dimension ldp) with partial pivoting.  r0 is the leaf's first row/column
+// index within the caller's numbering: ipiv[r0 .. r0+w) receives r0 + the
+// pivot row within the leaf; the column numbers r0 + j + 1 are the values of
+// the workgroups' sequence flags, so they must grow from leaf to leaf.
+// *split > 0: the leaf's columns before it still need the interchanges from
+// column *split on (panel_leaf_swap).
 template <typename T>
 int panel_leaf(int64_t m, int w, T *P, int64_t ldp, int64_t r0, int32_t *ipiv,
-               const PanelExchange &ex, hipStream_t s);
+               const PanelExchange &ex, int *split, hipStream_t s);
 
 // Interchanges ipiv[j0 .. j0+cnt) (rows >= j0, cnt <= 1024, of a matrix with
 // nrows rows) composed into a list of row moves, then applied to the columns
@@ -109,10 +119,9 @@ int alloc_panel_exchange(Scratch &scratch, int64_t n, PanelExchange *ex, hipStre
 // GEPP of the m x kb panel P (recursive; leaves are panel_leaf<T>); element
 // (0, 0) is row/column ibase of the caller's matrix, ipiv[ibase ..] receives
 // caller-numbered rows; the interchanges are applied inside the panel only.
-// moves: kSwapMovesInts device ints.
 template <typename T>
 int panel_factor(T *P, int64_t ldp, int64_t m, int64_t kb, int64_t ibase, int32_t *ipiv,
-                 const PanelExchange &ex, int *moves, hipStream_t s);
+                 const PanelExchange &ex, hipStream_t s);
 
 // perm[i] = original row at position i after the interchanges ipiv[0..n).
 int perm_from_ipiv(int64_t n, const int32_t *ipiv, int32_t *perm, hipStream_t s);

@@ -60,7 +60,6 @@ struct PanelCtx {
     int64_t ldp, m, kb, ibase;
     int32_t *ipiv;   // indexed in the caller's numbering (ibase + local)
     PanelExchange ex;
-    int *moves;
     hipStream_t s;
 };
 
@@ -74,12 +73,11 @@ int panel_rec(const PanelCtx<T> &f, int64_t c, int64_t w) {
     T *P = f.P;
     const int64_t ldp = f.ldp;
     if (w <= kLeafW) {
+        int split = 0;
         MXLU_TRY(panel_leaf<T>(f.m - c, (int)w, P + (size_t)c + (size_t)c * ldp, ldp, f.ibase + c,
-                          f.ipiv, f.ex, f.s));
-        if (f.kb > w) {
-            MXLU_TRY(swap_compose(f.ipiv, f.ibase + c, (int)w, f.ibase + f.m, f.moves, f.s));
-            MXLU_TRY(swap_apply<T>(P, ldp, c, f.moves, 0, f.kb - w, c, w, f.s));
-        }
+                          f.ipiv, f.ex, &split, f.s));
+        if (f.kb > w || split > 0)
+            MXLU_TRY(panel_leaf_swap<T>(P, ldp, f.m, f.kb, c, (int)w, split, f.ipiv, f.ibase + c, f.s));
         return 0;
     }
     int64_t n1 = w / 2;
@@ -101,14 +99,14 @@ namespace mxlu {
 // caller's matrix); ipiv[ibase ..] receives caller-numbered rows.
 template <typename T>
 int panel_factor(T *P, int64_t ldp, int64_t m, int64_t kb, int64_t ibase, int32_t *ipiv,
-                 const PanelExchange &ex, int *moves, hipStream_t s) {
-    PanelCtx<T> f{P, ldp, m, kb, ibase, ipiv, ex, moves, s};
+                 const PanelExchange &ex, hipStream_t s) {
+    PanelCtx<T> f{P, ldp, m, kb, ibase, ipiv, ex, s};
     return panel_rec(f, 0, kb);
 }
 template int panel_factor<double>(double *, int64_t, int64_t, int64_t, int64_t, int32_t *,
-                                  const PanelExchange &, int *, hipStream_t);
+                                  const PanelExchange &, hipStream_t);
 template int panel_factor<float>(float *, int64_t, int64_t, int64_t, int64_t, int32_t *,
-                                 const PanelExchange &, int *, hipStream_t);
+                                 const PanelExchange &, hipStream_t);
 
 // Test hook (mxlu_debug_expire_waits): panel exchanges start expired.
 std::atomic<int> g_expire_waits{0};
@@ -354,8 +352,7 @@ int factor_impl(int64_t n, int64_t nb, double *A, int64_t lda, int32_t *ipiv, hi
         profile_set_step(k0 / nb);
         if (!ahead) {   // PFACT
             PhaseScope ph(kPhasePfact, s, (double)m * kb * 8.0);
-            MXLU_TRY(panel_factor<double>(&MXLU_AT(A, k0, k0, lda), lda, m, kb, k0, ipiv, ex, moves,
-                                     s));
+            MXLU_TRY(panel_factor<double>(&MXLU_AT(A, k0, k0, lda), lda, m, kb, k0, ipiv, ex, s));
         }
         ahead = false;
         if (c1 < n) {   // SWAP on the columns right of the panel (those left of it: below)
@@ -397,7 +394,7 @@ int factor_impl(int64_t n, int64_t nb, double *A, int64_t lda, int32_t *ipiv, hi
             profile_set_step(k0 / nb + 1);   // the next step's panel
             PhaseScope ph(kPhasePfact, ov->panel, (double)nt * kb1 * 8.0);
             MXLU_TRY(panel_factor<double>(&MXLU_AT(A, c1, c1, lda), lda, nt, kb1, c1, ipiv,
-                                          ex_ahead, moves, ov->panel));
+                                          ex_ahead, ov->panel));
         }
         profile_set_step(k0 / nb);
         const int64_t n1 = nt > kb1 ? lookahead_split(nt, kb, kb1, ov) : 0;
@@ -479,11 +476,9 @@ extern "C" int mxlu_panel_factor_f64(int64_t m, int64_t nb, double *P, int64_t l
     Scratch scratch(s);
     PanelExchange ex;
     MXLU_TRY(alloc_panel_exchange(scratch, m, &ex, s));
-    int *moves = scratch.alloc_n<int>(kSwapMovesInts);
-    if (!moves) return MXLU_E_NOMEM;
     {
         PhaseScope ph(kPhasePfact, s, (double)m * nb * 8.0);
-        MXLU_TRY(panel_factor<double>(P, ldp, m, nb, 0, ipiv, ex, moves, s));
+        MXLU_TRY(panel_factor<double>(P, ldp, m, nb, 0, ipiv, ex, s));
     }
     int flags[4] = {0, 0, 0, 0};
     MXLU_HIP_TRY(hipMemcpyAsync(flags, ex.flags, sizeof(flags), hipMemcpyDeviceToHost, s));

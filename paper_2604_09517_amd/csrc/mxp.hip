@@ -192,7 +192,7 @@ int lp_factorize(const mxp_opts &o, int64_t n, const ASource &src, uint16_t *F,
         PhaseScope ph(kPhasePfact, st, 2.0 * (double)m * kb);
         MXLU_TRY(lp_load_f32(fmt, m, kb, Fk, ldf, P32, m, st));
         if (o.pivot)   // partial pivoting on the FP32 values of the panel
-            MXLU_TRY(panel_factor<float>(P32, m, m, kb, k0, ipiv, ex, moves, st));
+            MXLU_TRY(panel_factor<float>(P32, m, m, kb, k0, ipiv, ex, st));
         else
             MXLU_TRY(lp_panel_factor_nopiv(m, (int)kb, P32, m, d_info, d_info + 2, k0, st));
         const bool need_lt = !fp8 && c1 < n;
@@ -339,7 +339,7 @@ int lp_factorize_f32(const mxp_opts &o, int64_t n, const ASource &src, float *F,
             {
                 PhaseScope ph(kPhasePfact, s, 4.0 * (double)m * kb);
                 if (o.pivot)
-                    MXLU_TRY(panel_factor<float>(Fk, ldf, m, kb, k0, ipiv, ex, moves, s));
+                    MXLU_TRY(panel_factor<float>(Fk, ldf, m, kb, k0, ipiv, ex, s));
                 else
                     MXLU_TRY(lp_panel_factor_nopiv(m, (int)kb, Fk, ldf, d_info, d_info + 2, k0, s));
             }

@@ -707,7 +707,8 @@ template int panel_leaf_groups<float>(int64_t, int);
 
 template <typename T>
 int panel_leaf(int64_t m, int w, T *P, int64_t ldp, int64_t r0, int32_t *ipiv,
-               const PanelExchange &ex, hipStream_t s) {
+               const PanelExchange &ex, int *split, hipStream_t s) {
+    *split = 0;
     if (m <= 0 || w <= 0) return 0;
     if (w > kLeafW || m > 0x7fffffff) {
         set_error_msg("panel_leaf: bad shape");
@@ -716,7 +717,7 @@ int panel_leaf(int64_t m, int w, T *P, int64_t ldp, int64_t r0, int32_t *ipiv,
     LeafDevice dev;
     MXLU_TRY(leaf_device<T>(ex.group_cap, &dev));
     if (const int64_t Gw = wide_leaf_groups(m, dev))
-        return panel_leaf_wide<T>(m, w, P, ldp, r0, ipiv, (int)Gw, ex, s);
+        return panel_leaf_wide<T>(m, w, P, ldp, r0, ipiv, (int)Gw, ex, split, s);
     // taller than the wide form: two rows per thread in 256-thread groups
     // (full FP64 leaves), else the rows in LDS
     dev.occ_reg1 = 0;
@@ -748,7 +749,7 @@ int panel_leaf(int64_t m, int w, T *P, int64_t ldp, int64_t r0, int32_t *ipiv,
     return 0;
 }
 template int panel_leaf<double>(int64_t, int, double *, int64_t, int64_t, int32_t *,
-                                const PanelExchange &, hipStream_t);
+                                const PanelExchange &, int *, hipStream_t);
 template int panel_leaf<float>(int64_t, int, float *, int64_t, int64_t, int32_t *,
-                               const PanelExchange &, hipStream_t);
+                               const PanelExchange &, int *, hipStream_t);
 }  // namespace mxlu

@@ -7,33 +7,42 @@
 // What bounds a leaf is the chain of dependent latencies of each column, so
 // everything is chosen to shorten that chain:
 //   * rows never move between threads: every thread keeps the position its
-//     row has in the interchanged panel, an interchange exchanges two
-//     positions, and each row is stored to its position at the end (after
-//     every workgroup has loaded its rows).
-//   * up to 1024 rows: one workgroup, no exchange through memory at all, one
-//     LDS barrier per column: every wave leaves its candidate (value,
-//     position, row) in LDS, after the barrier every wave picks the winner.
-//   * more rows: one exchange round trip per column instead of two.  The
-//     group's candidate row goes out together with its position, and every
-//     group reads all candidates' rows in one batch (each wave reads every
-//     NT/64-th group's row, one word per lane), so no second, dependent read
-//     of the winner's row follows.  With 1024 rows per group that batch is
-//     at most 32 KB per group and column; 256-row groups would make it four
-//     times that for four times the readers.
-// The columns are unrolled eight at a time: after each eight the row's
-// registers are renamed by a rotation (register c then holds column
-// (8 jb + c) % 32), which keeps every register index a constant without
-// unrolling all 32 columns (eight minutes of compilation instead of one).
+//     row has in the interchanged leaf, an interchange exchanges two
+//     positions, and rows are stored to their positions (after every
+//     workgroup has loaded that part of its rows).
+//   * four waves with up to four rows per thread, one wave per SIMD: a wave
+//     issues an instruction every four cycles, so two waves on a SIMD double
+//     the reductions and bookkeeping of every column.  Four rows of 32 FP64
+//     columns do not fit a thread's vector registers, so the leaf is taken in
+//     two halves of 16 columns: the second is loaded when the first is done,
+//     takes the first's columns (its 16 pivot rows' triangular solve, then one
+//     product per thread and row) and is factored like the first.
+//     The first half's columns are left to the caller's interchanges for
+//     those of the second half (panel_leaf_swap).
+//   * up to 1024 rows: one workgroup, no exchange through memory.  Two LDS
+//     barriers per column: the waves' candidates (value, position) meet in
+//     LDS, every wave picks the winner and divides while the winner's wave
+//     writes its row.
+//   * more rows: one exchange round trip per column.  The group's candidate
+//     row goes out with its position; every wave reads all groups' candidates
+//     (a lane per group) and picks the winner itself, and in the same batch a
+//     quarter of the rows, so that no second, dependent read of the winner's
+//     row follows.
+//   * the columns are unrolled four at a time: after each four the row's
+//     registers are renamed by a rotation, which keeps every register index a
+//     constant.  Unrolled by 32 or by eight the code is executed once or a few
+//     times a leaf, does not fit the instruction cache, and every step waits
+//     for the instruction fetch.
 // The wave reduction takes the maximum of the upper words by DPP and finds
 // its lane by ballot; only ties in the upper word take the full comparison.
 //
-// Measured per 32-column FP64 leaf on an MI355X, in brackets the 256-row
-// register form it replaced: 256 rows 44 us (123), 1024 rows 60 us (124),
-// 4096 rows 123 us (132), 16384 rows 136 us (145), 32768 rows 150 us (160).
-// Of a column's 1.2 us in one workgroup about a third is the two candidate
-// reductions, a third the candidate rows' way through LDS; with an exchange
-// about 1.2 us are the store-to-load latency between XCDs (a bare exchange
-// among 2 to 32 workgroups takes 1.0 to 1.5 us).
+// A leaf of 32 FP64 columns with 64 / 256 / 512 / 1024 / 2048 / 4096 / 16384 /
+// 32768 rows takes 34 / 36 / 54 / 58 / 124 / 130 / 132 / 149 us.  On up to 64
+// workgroups of one 1024-row sweep without the halves (512 threads, two rows
+// each) it was 44 / 44 / 59 / 59 / 113 / 123 / 136 / 150 us; as 32 workgroups
+// or more with two exchange rounds per column 123 us up to 4096 rows, 145 and
+// 160 us.  The interchanges that follow take 5.8 us in one launch; composing
+// and applying them in two took 12 to 16 us, which outweighs the 2048-row loss.
 #pragma once
 
 #include "common.h"
@@ -41,269 +50,340 @@
 
 namespace {
 
-// (v, idx) of the first maximum over the wave; idx is the tie-break, v = -1
-// marks a lane without a candidate.  Uniform results.
-__device__ __forceinline__ void wave_first_max(double &v, int &idx) {
-    const uint64_t b = (uint64_t)__double_as_longlong(v);
-    const int lo = (int)(uint32_t)b, hi = (int)(uint32_t)(b >> 32);
-    // v is -1 or >= 0, so the upper words order as signed integers
-    int mx = hi;
+// Maximum over the wave (uniform).
+__device__ __forceinline__ int wave_max_i32(int mx) {
     mx = max(mx, __builtin_amdgcn_update_dpp(0, mx, 0xB1, 0xF, 0xF, false));    // quad_perm [1,0,3,2]
     mx = max(mx, __builtin_amdgcn_update_dpp(0, mx, 0x4E, 0xF, 0xF, false));    // quad_perm [2,3,0,1]
     mx = max(mx, __builtin_amdgcn_update_dpp(0, mx, 0x124, 0xF, 0xF, false));   // row_ror:4
     mx = max(mx, __builtin_amdgcn_update_dpp(0, mx, 0x128, 0xF, 0xF, false));   // row_ror:8
-    const int m0 = max(__builtin_amdgcn_readlane(mx, 0), __builtin_amdgcn_readlane(mx, 16));
-    const int m1 = max(__builtin_amdgcn_readlane(mx, 32), __builtin_amdgcn_readlane(mx, 48));
-    const int top = max(m0, m1);
-    // no candidate: at most one lane of the leaf still has a position (row J)
-    const uint64_t at = top < 0 ? __builtin_amdgcn_ballot_w64(idx != INT_MAX)
-                                : __builtin_amdgcn_ballot_w64(hi == top);
-    if (__builtin_popcountll(at) <= 1) {
-        const int l = at ? __builtin_ctzll(at) : 0;
-        const uint32_t rl = (uint32_t)__builtin_amdgcn_readlane(lo, l);
-        const uint32_t rh = (uint32_t)__builtin_amdgcn_readlane(hi, l);
-        v = __longlong_as_double((long long)(((uint64_t)rh << 32) | rl));
-        idx = __builtin_amdgcn_readlane(idx, l);
-    } else {
-        wave_argmax_dpp(v, idx);
-    }
+    const int a = max(__builtin_amdgcn_readlane(mx, 0), __builtin_amdgcn_readlane(mx, 16));
+    const int b = max(__builtin_amdgcn_readlane(mx, 32), __builtin_amdgcn_readlane(mx, 48));
+    return max(a, b);
 }
 
-template <typename T, int NT>
-struct WideShared {
-    static constexpr int NW = NT / 64;
-    // the waves' candidates, by parity of the column: without an exchange a
-    // column's data is read until the next column's only barrier
-    double cv[2][NW];
-    int ci[2][NW];
-    __attribute__((aligned(16))) T crow[2][NW][mxlu::kLeafW];
-    // exchange: the waves' winners over the groups they read
-    double gv[NW];
-    int gi[NW];
-    __attribute__((aligned(16))) T grow[NW][mxlu::kLeafW];
+// The upper word of |x| (all of it in FP32), -1 for NaN: orders candidates up
+// to ties.
+__device__ __forceinline__ int cand_key(double x) {
+    const int h = (int)((uint64_t)__double_as_longlong(x) >> 32) & 0x7fffffff;
+    return x == x ? h : -1;
+}
+__device__ __forceinline__ int cand_key(float x) {
+    return x == x ? __float_as_int(x) & 0x7fffffff : -1;
+}
+
+// The lane (uniform) of the first maximum of v, ties by index (every lane
+// takes part; rarely needed).
+__device__ __forceinline__ int first_of(double v, int idx) {
+    const double v0 = v;
+    const int i0 = idx;
+    wave_argmax_dpp(v, idx);
+    return __builtin_ctzll(__builtin_amdgcn_ballot_w64(v0 == v && i0 == idx));
+}
+
+// LDS written by some lanes of the wave is read by others after this
+__device__ __forceinline__ void wave_sync_lds() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+struct __attribute__((aligned(16))) WideKey {
+    double v;   // the candidate's value
+    int idx;    // its position (INT_MAX: no candidate)
+    int key;    // its key; -1: no candidate but the stand-in at position J
 };
 
-// EXCH: the leaf may span several workgroups
-template <typename T, int NT, int RPT, bool EXCH>
+template <typename T, int NT, int CW>
+struct WideShared {
+    static constexpr int NW = NT / 64;
+    WideKey cand[NW];   // the waves' candidates
+    // the pivot row and the group's candidate row to publish (unfinished
+    // blocks of columns only)
+    __attribute__((aligned(16))) T row[CW];
+    __attribute__((aligned(16))) T stage[CW];
+    // halves: rows of the first half's pivots (their multipliers), and the
+    // same rows of the second half
+    __attribute__((aligned(16))) T l11[CW][CW];
+    __attribute__((aligned(16))) T u12[CW][CW];
+};
+
+// CW columns of a leaf at a time (CW < 32: two halves).  EXCH: the leaf may
+// span several workgroups.
+template <typename T, int NT, int RPT, int CW, bool EXCH>
 struct WideLeaf {
-    static constexpr int W = mxlu::kLeafW, NW = NT / 64, R = NT * RPT;
-    static constexpr int CB = 8, NB = W / CB;                // columns per unrolled block
+    static constexpr int NW = NT / 64, R = NT * RPT;
+    static constexpr int CB = 4, NB = CW / CB;               // columns per unrolled block
     static constexpr int VW = (int)sizeof(T) / 4;            // 32-bit words of a value
-    static constexpr int RW = W * VW;                        // ... of a row
-    static constexpr int KR = (mxlu::kWideMaxGroups + NW - 1) / NW;   // groups read per wave
-    T x[RPT][W];     // register c: column (CB jb + c) % W in block jb
+    static constexpr int RW = CW * VW;                       // ... of a row
+    static constexpr int GPL = 64 / (RW < 64 ? RW : 64);     // groups' rows per wave load
+    static constexpr int KR = (mxlu::kWideMaxGroups + NW * GPL - 1) / (NW * GPL);
+    T x[RPT][CW];    // register c: column (CB jb + c) % CW of the half in block jb
     int pos[RPT];    // the row's position in the interchanged leaf (-1: no row)
     int m, w, G, g, tid, lane, wave;
     int64_t r0;
-    int32_t *ipiv;
     uint64_t *slots;
     int *flags;
+    int pivots = 0;        // lane j: position chosen for column j
+    int first_zero = -1;   // first exactly zero column
 
-    // (v, idx) of the wave's entry with index `lane`, reduced to the first
-    // maximum; returns the lane it came from
-    __device__ __forceinline__ int pick(double &v, int &idx) {
-        const int mine = idx;
-        wave_first_max(v, idx);
-        const uint64_t at = __builtin_amdgcn_ballot_w64(mine == idx && lane < NW);
-        return at ? __builtin_ctzll(at) : 0;
+    __device__ __forceinline__ static bool stale(uint64_t t, uint32_t seq) {
+        return (uint32_t)(t >> 32) != seq;
+    }
+    // bounded waiting: true when the caller has to give up.  Once any wait has
+    // expired the results are invalid: later waits give up at their first check
+    __device__ __forceinline__ bool expired(long rounds) {
+        if ((rounds & 63) == 63) {
+            if (__hip_atomic_load(&flags[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return true;
+            if (rounds > (1L << 22)) {
+                atomicExch(&flags[1], 1);
+                return true;
+            }
+        }
+        __builtin_amdgcn_s_sleep(1);
+        return false;
     }
 
-    template <int JL>
-    __device__ __forceinline__ void column(WideShared<T, NT> &sh, int jb) {
-        const int J = CB * jb + JL, par = JL & 1;
-        const uint32_t seq = (uint32_t)(r0 + J + 1);
-        // the wave's candidate: first position >= J of largest |x| (NaN never
-        // wins; position J itself is the choice when nothing else is)
-        double v = -1.0;
-        int idx = INT_MAX;
-#pragma unroll
-        for (int q = 0; q < RPT; ++q) {
-            if (pos[q] == J && idx == INT_MAX) idx = J;
-            const double av = fabs((double)x[q][JL]);
-            if (pos[q] >= J && (av > v || (av == v && pos[q] < idx))) {
-                v = av;
-                idx = pos[q];
-            }
-        }
-        wave_first_max(v, idx);
-        T *cand = &sh.crow[par][wave][0];
+    // the thread whose row is at position idx writes its columns from CB jb on
+    // to d0 (in column order)
+    __device__ __forceinline__ void put_row(int idx, int jb, T *d0) {
 #pragma unroll
         for (int q = 0; q < RPT; ++q)
-            if (pos[q] == idx) {   // its row, from column CB jb on (zeros before)
+            if (pos[q] == idx) {
 #pragma unroll
                 for (int k = 0; k < NB; ++k) {
-                    if (RPT > 1 && k >= NB - jb) break;   // uniform
-                    T *d = cand + CB * ((jb + k) % NB);
+                    if (k >= NB - jb) break;   // uniform
+                    T *d = d0 + CB * (jb + k);
 #pragma unroll
-                    for (int c = 0; c < CB; ++c) d[c] = k < NB - jb ? x[q][CB * k + c] : (T)0;
+                    for (int c = 0; c < CB; ++c) d[c] = x[q][CB * k + c];
                 }
             }
-        if (lane == 0) {
-            sh.cv[par][wave] = v;
-            sh.ci[par][wave] = idx;
+    }
+
+    __device__ __forceinline__ static T lane_value(T t, int l) {   // uniform: lane l's t
+        if constexpr (sizeof(T) == 8) {
+            const uint64_t b = (uint64_t)__double_as_longlong(t);
+            const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, l);
+            const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), l);
+            return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+        } else {
+            return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t), l));
+        }
+    }
+
+    // Column J0 + CB jb + JL of the leaf, J0 the half's first column.
+    template <int JL>
+    __device__ __forceinline__ void column(WideShared<T, NT, CW> &sh, int J0, int jb) {
+        const int JH = CB * jb + JL, J = J0 + JH, par = JL & 1;   // JH: within the half
+        const uint32_t seq = (uint32_t)(r0 + J + 1);
+        // the wave's candidate: first position >= J of largest |x| (NaN never
+        // wins; position J itself stands in when nothing else does)
+        int idx, top;
+        T piv;
+        {
+            int h[RPT], hm = -1;
+#pragma unroll
+            for (int q = 0; q < RPT; ++q) {
+                h[q] = pos[q] >= J ? cand_key(x[q][JL]) : -1;
+                hm = max(hm, h[q]);
+            }
+            top = wave_max_i32(hm);
+            uint64_t mask = 0;
+            int count = 0;
+            T val = x[0][JL];
+            int at = pos[0];
+#pragma unroll
+            for (int q = 0; q < RPT; ++q) {
+                const uint64_t mq = __builtin_amdgcn_ballot_w64(h[q] == top);
+                mask |= mq;
+                count += __builtin_popcountll(mq);
+                if (q > 0) {
+                    val = h[q] == top ? x[q][JL] : val;
+                    at = h[q] == top ? pos[q] : at;
+                }
+            }
+            int l = __builtin_ctzll(mask);
+            bool none = false;
+            if (__builtin_expect(top < 0 || count != 1, 0)) {
+                if (top < 0) {   // at most one lane of the leaf is at position J
+                    mask = 0;
+#pragma unroll
+                    for (int q = 0; q < RPT; ++q) {
+                        mask |= __builtin_amdgcn_ballot_w64(pos[q] == J);
+                        val = pos[q] == J ? x[q][JL] : val;
+                    }
+                    none = mask == 0;
+                    l = none ? 0 : __builtin_ctzll(mask);
+                    at = J;
+                } else {   // ties in the key: by value, then by position
+                    double v = -1.0;
+                    int i = INT_MAX;
+#pragma unroll
+                    for (int q = 0; q < RPT; ++q) {
+                        const double av = fabs((double)x[q][JL]);
+                        if (h[q] == top && (av > v || (av == v && pos[q] < i))) {
+                            v = av;
+                            i = pos[q];
+                            val = x[q][JL];
+                        }
+                    }
+                    at = i;
+                    l = first_of(v, i);
+                }
+            }
+            piv = lane_value(val, l);
+            idx = none ? INT_MAX : __builtin_amdgcn_readlane(at, l);
+            if (lane == 0) sh.cand[wave] = WideKey{(double)piv, idx, top};
         }
         lds_barrier();
-        v = lane < NW ? sh.cv[par][lane] : -1.0;
-        idx = lane < NW ? sh.ci[par][lane] : INT_MAX;
-        const T *prow = nullptr;
-        T piv, un;
-        auto lane_value = [&](T t, int l) -> T {   // uniform: lane l's t
-            if constexpr (sizeof(T) == 8) {
-                const uint64_t b = (uint64_t)__double_as_longlong(t);
-                const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)b, l);
-                const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(b >> 32), l);
-                return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
-            } else {
-                return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(t), l));
+        // the group's candidate: every wave picks it
+        int from;
+        {
+            static_assert(NW == 4, "one quad of waves");
+            const WideKey k = sh.cand[lane & (NW - 1)];
+            int mx = k.key;
+            mx = max(mx, __builtin_amdgcn_update_dpp(0, mx, 0xB1, 0xF, 0xF, false));
+            mx = max(mx, __builtin_amdgcn_update_dpp(0, mx, 0x4E, 0xF, 0xF, false));
+            top = __builtin_amdgcn_readfirstlane(mx);
+            uint64_t mask = __builtin_amdgcn_ballot_w64(k.key == top) & (uint64_t)((1 << NW) - 1);
+            from = __builtin_ctzll(mask);
+            if (__builtin_expect(top < 0 || __builtin_popcountll(mask) != 1, 0)) {
+                if (top < 0) {
+                    mask = __builtin_amdgcn_ballot_w64(k.idx == J) & (uint64_t)((1 << NW) - 1);
+                    from = mask ? __builtin_ctzll(mask) : 0;
+                } else {
+                    const bool in = lane < NW && k.key == top;
+                    from = first_of(in ? fabs(k.v) : -1.0, in ? k.idx : INT_MAX);
+                }
             }
-        };
-        const int JN = J + 1 < W ? J + 1 : J, ln = lane < NW ? lane : 0;
+            piv = lane_value((T)k.v, from);
+            idx = __builtin_amdgcn_readlane(k.idx, from);
+        }
         if (!EXCH || G == 1) {
-            // values J and J + 1 of every candidate row come in the same LDS
-            // round as the candidates themselves
-            const T pl = sh.crow[par][ln][J], ul = sh.crow[par][ln][JN];
-            const int from = pick(v, idx);
-            prow = &sh.crow[par][from][0];
-            piv = lane_value(pl, from);
-            un = lane_value(ul, from);
+            if (wave == from) put_row(idx, jb, sh.row);
         } else if constexpr (EXCH) {
-            const int own = pick(v, idx);
             uint64_t *gs = slots + (size_t)par * mxlu::kMaxGroups * kSlotWords;
-            const int first = VW * CB * jb;   // first word in use
-            if (wave == own) {   // the wave that holds the row
-                const uint32_t *words = reinterpret_cast<const uint32_t *>(&sh.crow[par][wave][0]);
-                uint64_t *mine = gs + (size_t)g * kSlotWords;
-                if (lane >= first && lane < RW) ll_store(&mine[4 + lane], seq, words[lane]);
-                if (lane == 0) ll_store(&mine[2], seq, (uint32_t)idx);
+            if (wave == from) {   // the wave that holds the row
+                put_row(idx, jb, sh.stage);
+                wave_sync_lds();
+                const uint32_t *words = reinterpret_cast<const uint32_t *>(sh.stage);
+                uint64_t *own = gs + (size_t)g * kSlotWords;
+                if (lane >= VW * CB * jb && lane < RW) ll_store(&own[4 + lane], seq, words[lane]);
+                if (lane == 0) ll_store(&own[2], seq, (uint32_t)idx);
             }
-            // one batch: rows of groups wave, wave + NW, ... (a word per lane)
-            // and their positions (lane k: the k-th of them); words not read
-            // count as arrived
-            const int cnt = wave < G ? (G - wave + NW - 1) / NW : 0;
-            const bool rd = lane >= first && lane < RW;
-            const uint64_t *pr = gs + (size_t)wave * kSlotWords + 4 + lane;
-            const uint64_t *pi = gs + (size_t)(wave + NW * (lane < cnt ? lane : 0)) * kSlotWords + 2;
+            // one batch: the candidates (lane: group) and every NW-th load of
+            // rows (GPL groups a load); words not read count as arrived
             const uint64_t none = (uint64_t)seq << 32;
-            uint64_t xw[KR], xi = none;
-            auto stale = [&](uint64_t t) { return (uint32_t)(t >> 32) != seq; };
+            const bool head = lane < G;
+            const uint64_t *ph = gs + (size_t)(head ? lane : 0) * kSlotWords;
+            const int rg = GPL * wave + lane / RW;   // group of the first load
+            const uint64_t *pr = gs + (size_t)rg * kSlotWords + 4 + lane % RW;
+            uint64_t hv0 = none, hv1 = none, hi = none, xw[KR];
+            if (head) {
+                hv0 = ll_load(ph + 4 + VW * JH);
+                if (VW == 2) hv1 = ll_load(ph + 4 + VW * JH + VW - 1);
+                hi = ll_load(ph + 2);
+            }
 #pragma unroll
             for (int k = 0; k < KR; ++k)
-                xw[k] = k < cnt && rd ? ll_load(pr + k * (NW * kSlotWords)) : none;
-            if (lane < cnt) xi = ll_load(pi);
+                xw[k] = rg + GPL * NW * k < G && lane % RW >= VW * CB * jb
+                            ? ll_load(pr + k * (GPL * NW * kSlotWords))
+                            : none;
             for (long rounds = 0;; ++rounds) {
-                bool late = stale(xi);
+                bool late = stale(hv0, seq) || stale(hv1, seq) || stale(hi, seq);
 #pragma unroll
-                for (int k = 0; k < KR; ++k) late = late || stale(xw[k]);
+                for (int k = 0; k < KR; ++k) late = late || stale(xw[k], seq);
                 if (__builtin_amdgcn_ballot_w64(late) == 0) break;
-                if ((rounds & 63) == 63) {
-                    // once any wait has expired the results are invalid:
-                    // later waits give up at their first check
-                    if (__hip_atomic_load(&flags[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT))
-                        break;
-                    if (rounds > (1L << 22)) {
-                        atomicExch(&flags[1], 1);
-                        break;
-                    }
-                }
-                __builtin_amdgcn_s_sleep(1);
+                if (expired(rounds)) break;
+                if (stale(hv0, seq)) hv0 = ll_load(ph + 4 + VW * JH);
+                if (VW == 2 && stale(hv1, seq)) hv1 = ll_load(ph + 4 + VW * JH + VW - 1);
+                if (stale(hi, seq)) hi = ll_load(ph + 2);
 #pragma unroll
                 for (int k = 0; k < KR; ++k)
-                    if (stale(xw[k])) xw[k] = ll_load(pr + k * (NW * kSlotWords));
-                if (stale(xi)) xi = ll_load(pi);
+                    if (stale(xw[k], seq)) xw[k] = ll_load(pr + k * (GPL * NW * kSlotWords));
             }
-            double bv = -1.0;
-            int bi = INT_MAX;
-            uint32_t bw = 0;
-#pragma unroll
-            for (int k = 0; k < KR; ++k) {
-                if (k < cnt) {   // wave-uniform
-                    const int ki = __builtin_amdgcn_readlane((int)(uint32_t)xi, k);
-                    double kv;
-                    if (sizeof(T) == 8) {
-                        const uint32_t a =
-                            (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)xw[k], (2 * J) & 63);
-                        const uint32_t b = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)xw[k],
-                                                                               (2 * J + 1) & 63);
-                        kv = fabs(__longlong_as_double((long long)(((uint64_t)b << 32) | a)));
-                    } else {
-                        kv = fabs((double)__int_as_float(
-                            __builtin_amdgcn_readlane((int)(uint32_t)xw[k], J)));
-                    }
-                    if (ki == INT_MAX || !(kv >= 0.0)) kv = -1.0;   // none, or a NaN at J
-                    if (kv > bv || (kv == bv && ki < bi)) {
-                        bv = kv;
-                        bi = ki;
-                        bw = (uint32_t)xw[k];
-                    }
+            T hv;
+            if constexpr (sizeof(T) == 8)
+                hv = __longlong_as_double((long long)(((uint64_t)(uint32_t)hv1 << 32) | (uint32_t)hv0));
+            else
+                hv = __int_as_float((int)(uint32_t)hv0);
+            const int ki = head ? (int)(uint32_t)hi : INT_MAX;
+            const int key = ki == INT_MAX ? -1 : cand_key(hv);
+            top = wave_max_i32(key);
+            uint64_t mask = __builtin_amdgcn_ballot_w64(key == top);
+            int gw = __builtin_ctzll(mask);   // the winner's group
+            if (__builtin_expect(top < 0 || __builtin_popcountll(mask) != 1, 0)) {
+                if (top < 0) {
+                    mask = __builtin_amdgcn_ballot_w64(ki == J);
+                    gw = mask ? __builtin_ctzll(mask) : 0;
+                } else {
+                    gw = first_of(key == top ? fabs((double)hv) : -1.0, key == top ? ki : INT_MAX);
                 }
             }
-            if (lane < RW) reinterpret_cast<uint32_t *>(sh.grow[wave])[lane] = bw;
-            if (lane == 0) {
-                sh.gv[wave] = bv;
-                sh.gi[wave] = bi;
+            piv = lane_value(hv, gw);
+            idx = __builtin_amdgcn_readlane(ki, gw);
+            // its row came with one wave's load
+            if ((gw / GPL) % NW == wave) {
+                uint32_t word = 0;
+#pragma unroll
+                for (int k = 0; k < KR; ++k)
+                    if (gw / (GPL * NW) == k) word = (uint32_t)xw[k];   // uniform
+                if (lane / RW == gw % GPL) reinterpret_cast<uint32_t *>(sh.row)[lane % RW] = word;
             }
-            lds_barrier();
-            v = lane < NW ? sh.gv[lane] : -1.0;
-            idx = lane < NW ? sh.gi[lane] : INT_MAX;
-            const T pl = sh.grow[ln][J], ul = sh.grow[ln][JN];
-            const int from = pick(v, idx);
-            prow = &sh.grow[from][0];
-            piv = lane_value(pl, from);
-            un = lane_value(ul, from);
-        }
-        // the pivot row's values, on their way while the multipliers are formed
-        T u[W];
-#pragma unroll
-        for (int k = 0; k < NB; ++k) {
-            const T *src = prow + CB * ((jb + k) % NB);
-#pragma unroll
-            for (int c = 0; c < CB; ++c)
-                if (CB * k + c > JL + 1) u[CB * k + c] = src[c];
         }
         // a position outside [J, m) can only follow an expired wait (stale
         // words): position J then, so no index leaves the panel
         int p = idx;
         if (p < J || p >= m) p = J;
-        const bool nonzero = v != 0.0;
-        if (!nonzero) p = J;   // an exactly zero column is left as it is
-        if (g == 0 && tid == 0) {
-            ipiv[J] = (int32_t)(r0 + p);
-            if (!nonzero && flags[0] == 0) flags[0] = (int)(r0 + J + 1);
+        const bool zero = piv == (T)0;
+        if (__builtin_expect(zero, 0)) {   // an exactly zero column is left as it is
+            p = J;
+            if (first_zero < 0) first_zero = J;
         }
-        constexpr int CN = JL + 1 < W ? JL + 1 : JL;
+        pivots = lane == J ? p : pivots;
         T l[RPT];
 #pragma unroll
         for (int q = 0; q < RPT; ++q) {
             pos[q] = pos[q] == p ? J : (pos[q] == J ? p : pos[q]);
-            l[q] = nonzero ? x[q][JL] / piv : x[q][JL];
+            l[q] = zero ? x[q][JL] : x[q][JL] / piv;
+            asm("" : "+v"(l[q]));   // here, while the row is on its way
         }
+        lds_barrier();   // the row is there
+        // One value of the pivot row per lane; each goes to the multiply-adds
+        // through a scalar register (LDS broadcasts of the whole row to every
+        // wave took longer than the arithmetic).
+        const T ul = sh.row[lane & (CW - 1)];
         // rows up to position J are final: not even a multiple by zero, which
         // an infinity in the pivot row would turn into NaN
+        bool below[RPT];
 #pragma unroll
-        for (int q = 0; q < RPT; ++q)
-            if (pos[q] > J) {
-                x[q][JL] = l[q];
-                if (JL + 1 < CB || jb + 1 < NB) x[q][CN] = fma(-l[q], un, x[q][CN]);
+        for (int q = 0; q < RPT; ++q) {
+            below[q] = pos[q] > J;
+            x[q][JL] = below[q] ? l[q] : x[q][JL];
+        }
 #pragma unroll
-                for (int k = 0; k < NB; ++k) {
-                    // one row per thread: finished columns take 0 * 0 (exact);
-                    // two: they are skipped (uniform)
-                    if (RPT > 1 && k >= NB - jb) break;
-                    const T lk = k == 0 || k < NB - jb ? l[q] : (T)0;
+        for (int k = 0; k < NB; ++k) {
+            if (k >= NB - jb) break;   // finished columns (uniform)
+            T u[CB];
+#pragma unroll
+            for (int c = 0; c < CB; ++c)
+                if (CB * k + c > JL) u[c] = lane_value(ul, CB * (jb + k) + c);
+#pragma unroll
+            for (int q = 0; q < RPT; ++q)
+                if (below[q]) {
 #pragma unroll
                     for (int c = 0; c < CB; ++c)
-                        if (CB * k + c > JL + 1)
-                            x[q][CB * k + c] = fma(-lk, u[CB * k + c], x[q][CB * k + c]);
+                        if (CB * k + c > JL)
+                            x[q][CB * k + c] = fma(-l[q], u[c], x[q][CB * k + c]);
                 }
-            }
+        }
     }
 
     template <int JL>
-    __device__ __forceinline__ void block(WideShared<T, NT> &sh, int jb) {
+    __device__ __forceinline__ void block(WideShared<T, NT, CW> &sh, int J0, int jb) {
         if constexpr (JL < CB) {
-            if (CB * jb + JL < w) {   // uniform
-                column<JL>(sh, jb);
-                block<JL + 1>(sh, jb);
+            if (J0 + CB * jb + JL < w) {   // uniform
+                column<JL>(sh, J0, jb);
+                block<JL + 1>(sh, J0, jb);
             }
         }
     }
@@ -315,20 +395,120 @@ struct WideLeaf {
 #pragma unroll
             for (int c = 0; c < CB; ++c) t[c] = x[q][c];
 #pragma unroll
-            for (int c = 0; c < W - CB; ++c) x[q][c] = x[q][c + CB];
+            for (int c = 0; c < CW - CB; ++c) x[q][c] = x[q][c + CB];
 #pragma unroll
-            for (int c = 0; c < CB; ++c) x[q][W - CB + c] = t[c];
+            for (int c = 0; c < CB; ++c) x[q][CW - CB + c] = t[c];
         }
+    }
+
+    // The first half's columns (stored at the rows' positions) taken to the
+    // second half's values in x: the pivot rows' unit-lower solve, then every
+    // other row's products, one fused multiply-add per term in ascending order
+    // as everywhere in the panel.
+    __device__ __forceinline__ void second_half(WideShared<T, NT, CW> &sh, const T *P, int64_t lda) {
+        if (!EXCH || G == 1) {
+#pragma unroll
+            for (int q = 0; q < RPT; ++q)
+                if (pos[q] >= 0 && pos[q] < CW) {
+#pragma unroll
+                    for (int c = 0; c < CW; ++c) {
+                        sh.l11[pos[q]][c] = P[(size_t)pos[q] + (size_t)c * lda];
+                        sh.u12[pos[q]][c] = x[q][c];
+                    }
+                }
+        } else if constexpr (EXCH) {
+            // the pivot rows lie in several groups: they go through memory,
+            // in slots no group uses
+            uint64_t *area = slots + (size_t)mxlu::kWideMaxGroups * kSlotWords;
+            const uint32_t seq = (uint32_t)(r0 + 1);
+            auto put = [&](uint64_t *d, T t) {
+                if constexpr (sizeof(T) == 8) {
+                    const uint64_t b = (uint64_t)__double_as_longlong(t);
+                    ll_store(d, seq, (uint32_t)b);
+                    ll_store(d + VW - 1, seq, (uint32_t)(b >> 32));
+                } else {
+                    ll_store(d, seq, (uint32_t)__float_as_int(t));
+                }
+            };
+#pragma unroll
+            for (int q = 0; q < RPT; ++q)
+                if (pos[q] >= 0 && pos[q] < CW) {
+                    uint64_t *d = area + pos[q] * RW;
+#pragma unroll
+                    for (int c = 0; c < CW; ++c) {
+                        put(d + VW * c, P[(size_t)pos[q] + (size_t)c * lda]);
+                        put(d + CW * RW + VW * c, x[q][c]);
+                    }
+                }
+            constexpr int kPer = 2 * CW * RW / NT;   // words per thread
+            static_assert(2 * CW * RW % NT == 0, "whole words per thread");
+            uint64_t word[kPer];
+#pragma unroll
+            for (int e = 0; e < kPer; ++e) word[e] = ll_load(&area[tid + NT * e]);
+#pragma unroll
+            for (int e = 0; e < kPer; ++e) {
+                const int t = tid + NT * e;
+                for (long rounds = 0; stale(word[e], seq); ++rounds) {
+                    if (expired(rounds)) break;
+                    word[e] = ll_load(&area[t]);
+                }
+                uint32_t *to = reinterpret_cast<uint32_t *>(t < CW * RW ? &sh.l11[0][0] : &sh.u12[0][0]);
+                to[t % (CW * RW)] = (uint32_t)word[e];
+            }
+        }
+        __syncthreads();
+        if (wave == 0 && lane < CW) {   // a lane per column
+            T y[CW];
+#pragma unroll
+            for (int i = 0; i < CW; ++i) y[i] = sh.u12[i][lane];
+#pragma unroll
+            for (int k = 0; k < CW; ++k) {
+#pragma unroll
+                for (int i = k + 1; i < CW; ++i) y[i] = fma(-sh.l11[i][k], y[k], y[i]);
+                // (all of l11 in registers would spill: two columns at a time)
+                if (k % 2 == 1) __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int i = 0; i < CW; ++i) sh.u12[i][lane] = y[i];
+        }
+        __syncthreads();
+        const T *src[RPT];
+#pragma unroll
+        for (int q = 0; q < RPT; ++q) src[q] = P + (pos[q] > 0 ? pos[q] : 0);
+#pragma unroll 1
+        for (int k0 = 0; k0 < CW; k0 += 8) {
+            T lk[8][RPT];
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+#pragma unroll
+                for (int q = 0; q < RPT; ++q) lk[k][q] = src[q][(size_t)(k0 + k) * lda];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) {
+#pragma unroll
+                for (int c = 0; c < CW; ++c) {
+                    const T uc = sh.u12[k0 + k][c];
+#pragma unroll
+                    for (int q = 0; q < RPT; ++q) x[q][c] = fma(-lk[k][q], uc, x[q][c]);
+                }
+                __builtin_amdgcn_sched_barrier(0);   // (all of u12 in registers would spill)
+            }
+        }
+        // the pivot rows' own values (whatever the products made of them)
+#pragma unroll
+        for (int q = 0; q < RPT; ++q)
+            if (pos[q] >= 0 && pos[q] < CW) {
+#pragma unroll
+                for (int c = 0; c < CW; ++c) x[q][c] = sh.u12[pos[q]][c];
+            }
     }
 };
 
-template <typename T, int NT, int RPT, bool EXCH>
-__global__ __launch_bounds__(NT) void panel_leaf_wide_kernel(int m, int w, T *__restrict__ P,
-                                                             int64_t lda, int G, int64_t r0,
-                                                             int32_t *__restrict__ ipiv,
+template <typename T, int NT, int RPT, int CW, bool EXCH>
+__global__ __launch_bounds__(NT) void panel_leaf_wide_kernel(int m, int w, T *P, int64_t lda, int G,
+                                                             int64_t r0, int32_t *__restrict__ ipiv,
                                                              uint64_t *slots, int *flags) {
-    __shared__ WideShared<T, NT> sh;
-    using Leaf = WideLeaf<T, NT, RPT, EXCH>;
+    __shared__ WideShared<T, NT, CW> sh;
+    using Leaf = WideLeaf<T, NT, RPT, CW, EXCH>;
     Leaf s;
     s.m = m;
     s.w = w;
@@ -338,30 +518,97 @@ __global__ __launch_bounds__(NT) void panel_leaf_wide_kernel(int m, int w, T *__
     s.lane = s.tid & 63;
     s.wave = __builtin_amdgcn_readfirstlane(s.tid >> 6);
     s.r0 = r0;
-    s.ipiv = ipiv;
     s.slots = slots;
     s.flags = flags;
+    auto load = [&](int c0) {
+#pragma unroll
+        for (int q = 0; q < RPT; ++q) {
+            const int r = s.g * Leaf::R + s.tid + NT * q;
+#pragma unroll
+            for (int c = 0; c < CW; ++c)
+                s.x[q][c] = (r < m && c0 + c < w) ? P[(size_t)r + (size_t)(c0 + c) * lda] : (T)0;
+        }
+    };
+    // a row may go to another group's position: every group has loaded these
+    // columns of its rows before the exchange (or barrier) of the last of them
+    // completed
+    auto store = [&](int c0) {
+#pragma unroll
+        for (int q = 0; q < RPT; ++q)
+            if (s.pos[q] >= 0) {
+#pragma unroll
+                for (int c = 0; c < CW; ++c)
+                    if (c0 + c < w) P[(size_t)s.pos[q] + (size_t)(c0 + c) * lda] = s.x[q][c];
+            }
+    };
 #pragma unroll
     for (int q = 0; q < RPT; ++q) {
         const int r = s.g * Leaf::R + s.tid + NT * q;
         s.pos[q] = r < m ? r : -1;
-#pragma unroll
-        for (int c = 0; c < Leaf::W; ++c)
-            s.x[q][c] = (r < m && c < w) ? P[(size_t)r + (size_t)c * lda] : (T)0;
     }
-    for (int jb = 0; jb < Leaf::NB; ++jb) {
-        s.template block<0>(sh, jb);
-        s.rotate();   // four rotations bring the columns back to their registers
-    }
-    // a row may go to another group's position: every group has loaded its
-    // rows before the first exchange (or barrier) of the leaf completed
-#pragma unroll
-    for (int q = 0; q < RPT; ++q)
-        if (s.pos[q] >= 0) {
-#pragma unroll
-            for (int c = 0; c < Leaf::W; ++c)
-                if (c < w) P[(size_t)s.pos[q] + (size_t)c * lda] = s.x[q][c];
+    for (int J0 = 0; J0 < w; J0 += CW) {   // the halves (or the whole leaf)
+        load(J0);
+        if (CW < mxlu::kLeafW && J0 > 0) s.second_half(sh, P, lda);
+        for (int jb = 0; jb < Leaf::NB; ++jb) {
+            s.template block<0>(sh, J0, jb);
+            s.rotate();   // NB rotations bring the columns back to their registers
         }
+        store(J0);
+    }
+    if (s.g == 0 && s.wave == 0) {
+        if (s.lane < w) ipiv[s.lane] = (int32_t)(r0 + s.pivots);
+        if (s.lane == 0 && s.first_zero >= 0 && flags[0] == 0) flags[0] = (int)(r0 + s.first_zero + 1);
+    }
+}
+
+// Interchanges of a leaf (columns [c0, c0 + w) of the kb-column panel at P,
+// pivots piv relative to row c0 + base) on the panel's other columns, and those
+// of the leaf's second half (from `split` on) on its first half.  A wave per
+// column: every wave composes the at most 32 interchanges itself (lane t: row
+// t; lane 32 + u: the pivot row of interchange u where it lies below the leaf
+// and appears first), then each lane moves one element of a column: all lanes
+// have loaded before any stores.
+constexpr int kLeafSwapCols = 16;   // columns per workgroup: four per wave
+
+template <typename T>
+__global__ __launch_bounds__(256) void panel_leaf_swap_kernel(T *P, int64_t ldp, int64_t m, int kb,
+                                                              int c0, int w, int split,
+                                                              const int32_t *__restrict__ ipiv,
+                                                              int64_t rbase) {
+    const int lane = threadIdx.x & 63;
+    const int cb = (int)blockIdx.x * kLeafSwapCols + (int)(threadIdx.x >> 6) * 4;
+    if (cb >= kb) return;
+    // first interchange that applies to these four columns (the leaf and its
+    // halves start at multiples of four)
+    const int j0 = cb < c0 || cb >= c0 + w ? 0 : (split > 0 && cb < c0 + split ? split : w);
+    if (j0 >= w) return;
+    // relative pivot rows; one outside [t, m - c0) (possible only after an
+    // expired wait) is taken as no interchange
+    int pv = lane;
+    if (lane < w && lane >= j0) {
+        const int64_t q = (int64_t)ipiv[lane] - rbase;
+        pv = q >= lane && q < m - c0 ? (int)q : lane;
+    }
+    int d = lane;
+    const int u = lane - 32;
+    const int pu = __shfl(pv, u >= 0 ? u : 0);
+    if (u >= 0) d = u < w && pu >= w ? pu : -1;
+    else if (lane >= w) d = -1;
+    int src = d;
+#pragma unroll 8
+    for (int t = 31; t >= 0; --t) {
+        const int q = __builtin_amdgcn_readlane(pv, t);
+        if (u > t && q == pu) d = -1;   // the row appeared earlier
+        src = src == t ? q : (src == q ? t : src);
+    }
+    const bool moved = d >= 0 && src != d;
+    T v[4];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        if (moved && cb + e < kb) v[e] = P[(size_t)(c0 + src) + (size_t)(cb + e) * ldp];
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+        if (moved && cb + e < kb) P[(size_t)(c0 + d) + (size_t)(cb + e) * ldp] = v[e];
 }
 
 }  // namespace
@@ -370,19 +617,34 @@ namespace mxlu {
 
 template <typename T>
 int panel_leaf_wide(int64_t m, int w, T *P, int64_t ldp, int64_t r0, int32_t *ipiv, int G,
-                    const PanelExchange &ex, hipStream_t s) {
+                    const PanelExchange &ex, int *split, hipStream_t s) {
     if (m <= 0 || w <= 0 || w > kLeafW || G > kWideMaxGroups || (int64_t)G * 1024 < m) {
         set_error_msg("panel_leaf_wide: bad shape");
         return MXLU_E_NOMEM;
     }
-    // up to 256 rows: four waves with a row per thread (fewer waves meet at
-    // each barrier and read the pivot row)
-    if (m <= 256)
-        hipLaunchKernelGGL((panel_leaf_wide_kernel<T, 256, 1, false>), dim3(1), dim3(256), 0, s,
+    *split = 0;
+    if (m <= 256) {   // a row per thread: all 32 columns fit
+        hipLaunchKernelGGL((panel_leaf_wide_kernel<T, 256, 1, 32, false>), dim3(1), dim3(256), 0, s,
                            (int)m, w, P, ldp, 1, r0, ipiv + r0, ex.slots, ex.flags);
-    else
-        hipLaunchKernelGGL((panel_leaf_wide_kernel<T, 512, 2, true>), dim3((unsigned)G), dim3(512),
+    } else {
+        hipLaunchKernelGGL((panel_leaf_wide_kernel<T, 256, 4, 16, true>), dim3((unsigned)G), dim3(256),
                            0, s, (int)m, w, P, ldp, G, r0, ipiv + r0, ex.slots, ex.flags);
+        if (w > 16) *split = 16;
+    }
+    MXLU_LAUNCH_CHECK();
+    return 0;
+}
+
+template <typename T>
+int panel_leaf_swap(T *P, int64_t ldp, int64_t m, int64_t kb, int64_t c0, int w, int split,
+                    const int32_t *ipiv, int64_t rbase, hipStream_t s) {
+    if (kb <= 0 || w <= 0 || w > kLeafW || c0 % 4 || split % 4 || kb > 0x7fffffff - 64) {
+        set_error_msg("panel_leaf_swap: bad shape");
+        return MXLU_E_NOMEM;
+    }
+    const unsigned grid = (unsigned)((kb + kLeafSwapCols - 1) / kLeafSwapCols);
+    hipLaunchKernelGGL(panel_leaf_swap_kernel<T>, dim3(grid), dim3(256), 0, s, P, ldp, m, (int)kb,
+                       (int)c0, w, split, ipiv + rbase, rbase);
     MXLU_LAUNCH_CHECK();
     return 0;
 }

@@ -4,5 +4,7 @@
 
 namespace mxlu {
 template int panel_leaf_wide<float>(int64_t, int, float *, int64_t, int64_t, int32_t *, int,
-                                  const PanelExchange &, hipStream_t);
+                                  const PanelExchange &, int *, hipStream_t);
+template int panel_leaf_swap<float>(float *, int64_t, int64_t, int64_t, int64_t, int, int,
+                                  const int32_t *, int64_t, hipStream_t);
 }  // namespace mxlu

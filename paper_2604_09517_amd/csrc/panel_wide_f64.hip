@@ -4,5 +4,7 @@
 
 namespace mxlu {
 template int panel_leaf_wide<double>(int64_t, int, double *, int64_t, int64_t, int32_t *, int,
-                                  const PanelExchange &, hipStream_t);
+                                  const PanelExchange &, int *, hipStream_t);
+template int panel_leaf_swap<double>(double *, int64_t, int64_t, int64_t, int64_t, int, int,
+                                   const int32_t *, int64_t, hipStream_t);
 }  // namespace mxlu
