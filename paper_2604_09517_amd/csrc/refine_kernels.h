@@ -9,7 +9,7 @@
 
 namespace mxlu {
 
-constexpr int kTrsvBs = 256;   // block rows of the FP32 triangular solves
+constexpr int kTrsvBs = 256;   // rows per workgroup of the FP32 triangular solves
 
 // y = A x (b == NULL) or y = b - A x; op(A) = A (trans 0) or A^T (trans 1),
 // A in memory or regenerated from its seed (ASource).
@@ -36,6 +36,10 @@ struct TrsvChain {
     int *expired;
     uint32_t tag;
 };
+
+// v <- T^-1 v with the stored factors F, T = L, U, U^T, L^T (kind 0, 1, 2, 3).
+int trsv_lp(int fmt, int kind, int64_t n, const uint16_t *F, int64_t ldf, float *v, TrsvChain &ch,
+            hipStream_t s);
 
 // d = M r (trans 0) or M^T r (trans 1) with M = U^-1 L^-1 P from the stored
 // factors F; perm (optional) is the row order of P.  v32: n floats scratch;

@@ -318,357 +318,6 @@ __global__ void precond_out_kernel(int64_t n, const float *__restrict__ v32,
     d[perm ? perm[i] : i] = s > 0.0 ? s * (double)v32[i] : 0.0;
 }
 
-// Blocked triangular solve in FP32 with the stored factor F (16-bit), blocks
-// of kTrsvBs rows, in one launch.  Workgroup w owns the w-th block in solve
-// order: it stages its diagonal block in LDS, then, for every earlier block
-// in solve order, waits for that block's solution and applies it to its own
-// rows (thread = row), then solves its diagonal block with one wave and
-// publishes the solution.  Every element accumulates its terms in the order
-// of the textbook substitution (column-oriented for L and U: ascending k for
-// L, descending k for U; ascending i for the transposed forms).
-//   kind 0: L (unit lower), forward;   kind 1: U (upper), backward
-//   kind 2: U^T (lower), forward;      kind 3: L^T (unit upper), backward
-// Publication: each solved value goes to xs as a 64-bit word holding the
-// float's bits and, in the upper half, the launch's tag; writers and readers
-// use agent-scope relaxed atomics and a reader polls each word until it
-// carries the tag, so no fences are needed.  Tags are unique per launch, so
-// words of earlier solves never match.  Workgroup w waits only on
-// workgroups with smaller ids, which are dispatched first, so the chain
-// always progresses even when not all workgroups are resident.  The polling
-// is bounded: on expiry *expired is set and the solve completes with
-// invalid values.
-__device__ __forceinline__ uint64_t ll_load(const uint64_t *p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Barrier that orders LDS only, so that global loads issued before it stay in
-// flight across it (a full __syncthreads would wait for them).
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
-template <int FMT, int KIND>
-__global__ __launch_bounds__(256) void trsv_chain_kernel(int64_t n, const uint16_t *__restrict__ F,
-                                                         int64_t ldf, float *__restrict__ v,
-                                                         uint64_t *xs, uint32_t tag, int nblk,
-                                                         int *expired) {
-    constexpr int BS = kTrsvBs;
-    constexpr bool FWD = (KIND == 0 || KIND == 2);
-    constexpr bool UNIT = (KIND == 0 || KIND == 3);
-    __shared__ uint16_t Ld[BS][BS + 2];   // raw stored values (129 KB)
-    __shared__ float xprev[BS];
-    // column-major kinds: 32 columns x 256 rows of an earlier block, staged
-    // with 16-byte loads so that each thread can read its row
-    __shared__ __attribute__((aligned(16))) uint16_t stg[32][BS];
-    const int tid = threadIdx.x;
-    const int w = blockIdx.x;
-    const int64_t myblk = FWD ? w : nblk - 1 - w;
-    const int64_t r0 = myblk * BS;
-    const int rows = (int)((n - r0 < BS) ? n - r0 : BS);
-    const int64_t i = r0 + tid;          // this thread's row
-
-    // diagonal block, staged as the effective lower/upper factor
-    for (int t = tid; t < rows * rows; t += 256) {
-        const int ii = t % rows, k = t / rows;
-        const uint16_t f = F[(size_t)(r0 + ii) + (size_t)(r0 + k) * ldf];
-        if (KIND == 0 || KIND == 1) Ld[ii][k] = f;
-        else Ld[k][ii] = f;     // transposed forms: Ld[i][k] = F[k][i]
-    }
-    float acc = (tid < rows) ? v[i] : 0.0f;
-    constexpr bool COLMAJOR = (KIND == 0 || KIND == 1);
-    // column-major kinds, full blocks: chunk cc (32 columns of the earlier
-    // block) is loaded as 4 x 16 bytes per thread (8 rows of one column each)
-    auto ld_chunk = [&](int64_t p0, int cc, uint4 (&g)[4]) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int idx = tid + 256 * q, col = idx >> 5, rg = idx & 31;
-            const uint16_t *src = &F[(size_t)(r0 + 8 * rg) + (size_t)(p0 + 32 * cc + col) * ldf];
-            if (8 * rg + 8 <= rows) {
-                g[q] = *reinterpret_cast<const uint4 *>(src);
-            } else {   // rows past the matrix (last block): zeros
-                uint16_t h[8];
-#pragma unroll
-                for (int e = 0; e < 8; ++e) h[e] = (8 * rg + e < rows) ? src[e] : (uint16_t)0;
-                g[q] = make_uint4(h[0] | ((uint32_t)h[1] << 16), h[2] | ((uint32_t)h[3] << 16),
-                                  h[4] | ((uint32_t)h[5] << 16), h[6] | ((uint32_t)h[7] << 16));
-            }
-        }
-    };
-    auto chunk_of = [&](int c) { return (KIND == 1) ? 7 - c : c; };   // solve order
-    auto apply_chunk = [&](int cc, const uint4 (&g)[4]) {
-        lds_barrier();   // the previous chunk is consumed
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int idx = tid + 256 * q, col = idx >> 5, rg = idx & 31;
-            *reinterpret_cast<uint4 *>(&stg[col][8 * rg]) = g[q];
-        }
-    };
-    auto fma_chunk = [&](int cc) {
-        if (KIND == 0) {
-#pragma unroll
-            for (int kk = 0; kk < 32; ++kk)
-                acc = fmaf(-lp_to_f32<FMT>(stg[kk][tid]), xprev[32 * cc + kk], acc);
-        } else {
-#pragma unroll
-            for (int kk = 31; kk >= 0; --kk)
-                acc = fmaf(-lp_to_f32<FMT>(stg[kk][tid]), xprev[32 * cc + kk], acc);
-        }
-    };
-    // transposed kinds: fr holds the thread's row of the earlier block, F
-    // values for k = 2j, 2j+1 packed in one word, loaded before the wait
-    uint32_t fr[COLMAJOR ? 1 : BS / 2];
-    // column-major kinds: gb holds the 8 chunks of the next full earlier
-    // block; slot c is refilled with the following block's chunk c as soon
-    // as it is staged, so a whole block of loads is in flight while the
-    // current one is applied
-    constexpr int NG = COLMAJOR ? 8 : 1;
-    uint4 gb[NG][4];
-    uint32_t cr[NG][16];
-    bool have = false;   // gb holds the current earlier block
-    for (int t = 0; t < w; ++t) {
-        const int64_t pb = FWD ? t : nblk - 1 - t;
-        const int64_t p0 = pb * BS;
-        const int pr = (int)((n - p0 < BS) ? n - p0 : BS);
-        const bool full = (pr == BS);   // the earlier block is full
-        // the last earlier block is on the chain's critical path: its values
-        // move into registers (the thread's row, two values per word) while
-        // its solution is still awaited, so that only its multiply-adds follow
-        // the arrival
-        const bool last = COLMAJOR && full && t == w - 1;
-        if (full) {
-            if (COLMAJOR) {
-                if (!have)
-#pragma unroll
-                    for (int c = 0; c < NG; ++c) ld_chunk(p0, chunk_of(c), gb[c]);
-                if (last) {
-#pragma unroll
-                    for (int c = 0; c < NG; ++c) {
-                        apply_chunk(chunk_of(c), gb[c]);
-                        lds_barrier();
-#pragma unroll
-                        for (int q = 0; q < 16; ++q)
-                            cr[c][q] = (uint32_t)stg[2 * q][tid] | ((uint32_t)stg[2 * q + 1][tid] << 16);
-                    }
-                }
-            } else if (tid < rows) {   // F[k][i] for k in the earlier block: contiguous in k
-                const uint4 *q = reinterpret_cast<const uint4 *>(&F[(size_t)p0 + (size_t)i * ldf]);
-#pragma unroll
-                for (int j = 0; j < BS / 8; ++j) {
-                    const uint4 u = q[j];
-                    fr[4 * j] = u.x;
-                    fr[4 * j + 1] = u.y;
-                    fr[4 * j + 2] = u.z;
-                    fr[4 * j + 3] = u.w;
-                }
-            }
-        }
-        lds_barrier();   // the previous block's values are consumed
-        // one thread watches the block's first word (many pollers on the same
-        // lines would slow the producer's stores); then every thread reads
-        // its word, which has normally arrived by then
-        if (tid == 0) {
-            const uint64_t *src = &xs[p0];
-            uint64_t x = ll_load(src);
-            long spins = 0;
-            while ((uint32_t)(x >> 32) != tag) {
-                __builtin_amdgcn_s_sleep(2);
-                if (++spins > (1L << 26)) {
-                    atomicExch(expired, 1);
-                    break;
-                }
-                x = ll_load(src);
-            }
-        }
-        lds_barrier();
-        if (tid < pr) {
-            const uint64_t *src = &xs[p0 + tid];
-            uint64_t x = ll_load(src);
-            long spins = 0;
-            while ((uint32_t)(x >> 32) != tag) {
-                __builtin_amdgcn_s_sleep(2);
-                if (++spins > (1L << 26)) {
-                    atomicExch(expired, 1);
-                    break;
-                }
-                x = ll_load(src);
-            }
-            xprev[tid] = __uint_as_float((uint32_t)x);
-        }
-        lds_barrier();
-        if (last) {
-            // the same terms in the same order as fma_chunk over the chunks
-#pragma unroll
-            for (int c = 0; c < NG; ++c) {
-                const int cc = chunk_of(c);
-                if (KIND == 0) {
-#pragma unroll
-                    for (int kk = 0; kk < 32; ++kk)
-                        acc = fmaf(-lp_to_f32<FMT>((uint16_t)(cr[c][kk >> 1] >> (16 * (kk & 1)))),
-                                   xprev[32 * cc + kk], acc);
-                } else {
-#pragma unroll
-                    for (int kk = 31; kk >= 0; --kk)
-                        acc = fmaf(-lp_to_f32<FMT>((uint16_t)(cr[c][kk >> 1] >> (16 * (kk & 1)))),
-                                   xprev[32 * cc + kk], acc);
-                }
-            }
-            have = false;
-        } else if (full && COLMAJOR) {
-            // chunks in solve order; each staged chunk's slot takes the next
-            // earlier block's chunk (when that block is full)
-            const int64_t pn = FWD ? t + 1 : nblk - 2 - t;
-            const bool next = t + 1 < w && (n - pn * BS >= BS);
-#pragma unroll
-            for (int c = 0; c < NG; ++c) {
-                apply_chunk(chunk_of(c), gb[c]);
-                if (next) ld_chunk(pn * BS, chunk_of(c), gb[c]);
-                lds_barrier();
-                fma_chunk(chunk_of(c));
-            }
-            have = next;
-        } else if (full && tid < rows) {
-            // U^T, L^T: k ascending
-#pragma unroll
-            for (int j = 0; j < BS / 2; ++j) {
-                acc = fmaf(-lp_to_f32<FMT>((uint16_t)fr[j]), xprev[2 * j], acc);
-                acc = fmaf(-lp_to_f32<FMT>((uint16_t)(fr[j] >> 16)), xprev[2 * j + 1], acc);
-            }
-        } else if (tid < rows) {   // a partial block (the last one of n)
-            if (KIND == 0) {
-                for (int k = 0; k < pr; ++k)
-                    acc = fmaf(-lp_to_f32<FMT>(F[(size_t)i + (size_t)(p0 + k) * ldf]), xprev[k], acc);
-            } else if (KIND == 1) {
-                for (int k = pr - 1; k >= 0; --k)
-                    acc = fmaf(-lp_to_f32<FMT>(F[(size_t)i + (size_t)(p0 + k) * ldf]), xprev[k], acc);
-            } else {
-                for (int k = 0; k < pr; ++k)
-                    acc = fmaf(-lp_to_f32<FMT>(F[(size_t)(p0 + k) + (size_t)i * ldf]), xprev[k], acc);
-            }
-        }
-    }
-    // Diagonal block: four sub-blocks of 64 rows in solve order.  Wave sb
-    // owns the rows of sub-block sb (thread = row, as above): it solves them
-    // (step j finishes x_k on its owner lane, division for U, and broadcasts
-    // it with readlane; the LDS value of step j + 1 is read during step j),
-    // publishes them in LDS, and the waves of the sub-blocks still to be
-    // solved apply them to their rows, k in solve order.  Every element still
-    // takes its terms in the textbook order.
-    constexpr int NSB = BS / 64;
-    const int wave = tid >> 6;
-    float x = acc;
-    const bool mine = tid < rows;
-    __syncthreads();   // xprev is reused for the solution
-#pragma unroll
-    for (int s = 0; s < NSB; ++s) {
-        const int sb = FWD ? s : NSB - 1 - s;
-        const int base = sb * 64;
-        const int len = min(64, rows - base);   // rows of this sub-block (<= 0: none)
-        if (wave == sb && len == 64) {
-            // full sub-block: the lane's row of it in registers, steps unrolled
-            const int lane = tid & 63;
-            uint32_t rr[32];
-#pragma unroll
-            for (int p = 0; p < 32; ++p)
-                rr[p] = *reinterpret_cast<const uint32_t *>(&Ld[tid][base + 2 * p]);
-            // every lane applies every step (the update of a lane already
-            // solved is never read again); each lane's finished value is kept
-            // aside at its own step, off the dependency chain
-            //
-            // U (non-unit): the quotient x / d of a step comes from r = RN(1/d),
-            // the reciprocal of the lane's own diagonal entry computed ahead of
-            // the chain: q0 = RN(x r), q = RN(q0 + (x - q0 d) r) with both
-            // corrections fused multiply-adds.  While every value stays in the
-            // normal range that is the correctly rounded quotient (Markstein's
-            // theorem for a reciprocal rounded to nearest; also checked against
-            // the division on 4e8 operand pairs, quotients at rounding
-            // midpoints and divisors with all-ones significands included, and
-            // scale-invariant away from underflow and overflow).  Each lane
-            // keeps the value it divided; after the 64 steps one vote checks
-            // |x| >= 2^-100 (or x == 0), |q| within [2^-99, 2^99] and |d| within
-            // [2^-100, 2^100], and if any lane is outside, the sub-block is
-            // solved again with the division: the result is the division's bit
-            // for bit either way.
-            const float x_in = x;
-            const float dl = lp_to_f32<FMT>(Ld[tid][tid]);
-            const float rdiag = UNIT ? 1.0f : 1.0f / dl;
-            float xfin = x, xo = x;
-#pragma unroll
-            for (int j = 0; j < 64; ++j) {
-                const int kl = FWD ? j : 63 - j;
-                const uint32_t w2 = rr[kl >> 1];
-                const float lv = lp_to_f32<FMT>((uint16_t)((kl & 1) ? (w2 >> 16) : w2));
-                // on the owner lane lv is the diagonal entry
-                float own = x;
-                if (!UNIT) {
-                    const float q0 = x * rdiag;
-                    own = fmaf(fmaf(-q0, lv, x), rdiag, q0);
-                    xo = (lane == kl) ? x : xo;
-                }
-                const float xk = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(own), kl));
-                xfin = (lane == kl) ? xk : xfin;
-                x = fmaf(-lv, xk, x);
-            }
-            x = xfin;
-            if (!UNIT) {
-                const float ax = fabsf(xo), aq = fabsf(xfin), ad = fabsf(dl);
-                const bool in = (xo == 0.0f || (ax >= 0x1p-100f && aq >= 0x1p-99f && aq <= 0x1p99f)) &&
-                                ad >= 0x1p-100f && ad <= 0x1p100f;
-                if (!__all(in)) {   // wave-uniform; never taken on scaled inputs
-                    x = x_in;
-                    xfin = x;
-                    for (int j = 0; j < 64; ++j) {
-                        const int kl = FWD ? j : 63 - j;
-                        const float lv = lp_to_f32<FMT>(Ld[tid][base + kl]);
-                        const float own = x / lv;
-                        const float xk =
-                            __int_as_float(__builtin_amdgcn_readlane(__float_as_int(own), kl));
-                        xfin = (lane == kl) ? xk : xfin;
-                        x = fmaf(-lv, xk, x);
-                    }
-                    x = xfin;
-                }
-            }
-            xprev[tid] = x;
-        } else if (wave == sb && len > 0) {
-            auto kat = [&](int j) { return FWD ? base + j : base + len - 1 - j; };
-            // raw values of step j + 1 are read during step j (unconditionally:
-            // every thread's row is inside the LDS block; rows past the
-            // matrix are never stored)
-            uint16_t lc = Ld[tid][kat(0)], dc = Ld[kat(0)][kat(0)];
-            for (int j = 0; j < len; ++j) {
-                const int k = kat(j);
-                const int k1 = kat(j + 1 < len ? j + 1 : j);
-                const uint16_t ln = Ld[tid][k1], dn = Ld[k1][k1];
-                const float own = UNIT ? x : x / lp_to_f32<FMT>(dc);
-                const float xk = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(own), k - base));
-                const float upd = fmaf(-lp_to_f32<FMT>(lc), xk, x);
-                const bool later = FWD ? tid > k : tid < k;
-                x = (tid == k) ? xk : (later ? upd : x);
-                lc = ln;
-                dc = dn;
-            }
-            xprev[tid] = x;
-        }
-        __syncthreads();
-        if (len > 0 && (FWD ? wave > sb : wave < sb) && mine) {
-            if (FWD) {
-                for (int j = 0; j < len; ++j)
-                    x = fmaf(-lp_to_f32<FMT>(Ld[tid][base + j]), xprev[base + j], x);
-            } else {
-                for (int j = len - 1; j >= 0; --j)
-                    x = fmaf(-lp_to_f32<FMT>(Ld[tid][base + j]), xprev[base + j], x);
-            }
-        }
-    }
-    if (mine) {
-        v[i] = x;
-        __hip_atomic_store(&xs[i], ((uint64_t)tag << 32) | __float_as_uint(x), __ATOMIC_RELAXED,
-                           __HIP_MEMORY_SCOPE_AGENT);
-    }
-}
-
 unsigned g1(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 // FP32-storage preconditioner: the factors are FP32 numbers, solved block by
@@ -817,25 +466,6 @@ int absmax_f64(int64_t n, const double *v, unsigned long long *out, hipStream_t 
     return 0;
 }
 
-template <int FMT, int KIND>
-static int trsv_run(int64_t n, const uint16_t *F, int64_t ldf, float *v, TrsvChain &ch,
-                    hipStream_t s) {
-    const int64_t nblk = (n + kTrsvBs - 1) / kTrsvBs;
-    if (nblk > 0x7fffffff) {
-        set_error_msg("trsv: too many blocks");
-        return MXLU_E_NOMEM;
-    }
-    if (((uintptr_t)F % 16) || (ldf % 8)) {
-        set_error_msg("trsv: factor storage must be 16-byte aligned with ldf % 8 == 0");
-        return MXLU_E_NOMEM;
-    }
-    const uint32_t tag = ++ch.tag;
-    hipLaunchKernelGGL((trsv_chain_kernel<FMT, KIND>), dim3((unsigned)nblk), dim3(256), 0, s, n, F,
-                       ldf, v, ch.xs, tag, (int)nblk, ch.expired);
-    MXLU_LAUNCH_CHECK();
-    return 0;
-}
-
 int lp_precond_apply_f32(int64_t n, const float *F, int64_t ldf, const int32_t *perm,
                          const double *r, double *d, float *v32, unsigned long long *smax,
                          hipStream_t s) {
@@ -883,15 +513,8 @@ int lp_precond_apply(int fmt, int trans, int64_t n, const uint16_t *F, int64_t l
     hipLaunchKernelGGL(precond_in_kernel, dim3(g1(n)), dim3(256), 0, s, n, r,
                        trans ? nullptr : perm, smax, v32);
     MXLU_LAUNCH_CHECK();
-    int rc;
-    if (fmt == kFmtBf16) {
-        rc = trans ? trsv_run<kFmtBf16, 2>(n, F, ldf, v32, ch, s) : trsv_run<kFmtBf16, 0>(n, F, ldf, v32, ch, s);
-        if (!rc) rc = trans ? trsv_run<kFmtBf16, 3>(n, F, ldf, v32, ch, s) : trsv_run<kFmtBf16, 1>(n, F, ldf, v32, ch, s);
-    } else {
-        rc = trans ? trsv_run<kFmtFp16, 2>(n, F, ldf, v32, ch, s) : trsv_run<kFmtFp16, 0>(n, F, ldf, v32, ch, s);
-        if (!rc) rc = trans ? trsv_run<kFmtFp16, 3>(n, F, ldf, v32, ch, s) : trsv_run<kFmtFp16, 1>(n, F, ldf, v32, ch, s);
-    }
-    if (rc) return rc;
+    MXLU_TRY(trsv_lp(fmt, trans ? 2 : 0, n, F, ldf, v32, ch, s));
+    MXLU_TRY(trsv_lp(fmt, trans ? 3 : 1, n, F, ldf, v32, ch, s));
     hipLaunchKernelGGL(precond_out_kernel, dim3(g1(n)), dim3(256), 0, s, n, v32,
                        trans ? perm : nullptr, smax, d);
     MXLU_LAUNCH_CHECK();

@@ -282,6 +282,37 @@ def test_preconditioner_bitwise_on_oracle_factors(api, prec, trans):
         assert np.abs(x0 - ref).max() <= 1e-5 * np.abs(ref).max()
 
 
+@pytest.mark.parametrize("prec", ["bf16", "fp16"])
+@pytest.mark.parametrize("n", [1, 2, 15, 63, 64, 65, 129, 255, 256, 257, 511, 769, 1029])
+def test_preconditioner_strip_edges(api, prec, n):
+    """Sizes around the 16-row groups, 64-row strips and 256-row workgroups of
+    the chained triangular solves, with the rest of the workspace (the storage
+    below row n of every column included) full of NaN: bit for bit equal to the
+    oracle forward; transposed within the 1e-5 of the test above (the order of
+    terms differs)."""
+    note(f"preconditioner edges n={n} {prec}")
+    A = inputs.diag_dominant_matrix(177 + n, 0, n)
+    b = inputs.uniform_matrix(177 + n, 1, n, 1)[:, 0]
+    F_ref, _, _ = oracle.lp_getrf(A, 64, PREC_ID[prec], pivot=False)
+    dA, db = to_dev(A), to_dev(b)
+    for trans in (0, 1):
+        opts = api.mxp_options(prec=prec, nb=64, max_outer=0, reuse_factors=True, trans=bool(trans))
+        work = torch.full((api.mxp_workspace_bytes(n, opts, n),), 255, dtype=torch.uint8, device="cuda")
+        api.mxp_factors(work, n, prec).copy_(torch.from_numpy(F_ref).to(
+            torch.bfloat16 if prec == "bf16" else torch.float16))
+        X, rep, _, _ = api.mxp_solve(dA, db, work=work, opts=opts, allow_notconv=True)
+        torch.cuda.synchronize()
+        ref = oracle.lp_precond(F_ref, None, b, trans=bool(trans))
+        if trans == 0:
+            assert np.array_equal(X.cpu().numpy(), ref)
+        else:
+            # (n = 1: the generated matrix is zero and both are infinite)
+            x = X.cpu().numpy()
+            same = x == ref
+            far = np.abs(np.where(same, 0.0, x) - np.where(same, 0.0, ref))
+            assert np.all(far <= 1e-5 * np.abs(ref).max())
+
+
 def test_preconditioner_bitwise_outside_the_reciprocal_range(api):
     """The U solve's diagonal steps divide through a reciprocal only while
     every value is in the normal range; with some diagonal entries of U scaled
