@@ -110,8 +110,8 @@ int laswp_f64(double *A, int64_t lda, int64_t nrows, const int32_t *ipiv, int64_
               int *moves, hipStream_t s);
 
 // B(kb x ncols) = L^-1 B with L unit lower (kb x kb), kb <= 256.
-int trsm_llnu_f64(int kb, int64_t ncols, const double *L, int64_t ldl, double *B,
-                  int64_t ldb, hipStream_t s);
+template <typename T>
+int trsm_llnu(int kb, int64_t ncols, const T *L, int64_t ldl, T *B, int64_t ldb, hipStream_t s);
 class Scratch;
 extern std::atomic<int> g_expire_waits;
 // Zeroed exchange area of the panel kernels for a matrix of order n.

@@ -20,18 +20,11 @@
 
 #include "asource.h"
 #include "common.h"
+#include "kernels.h"
 #include "lp_common.h"
 #include "lp_kernels.h"
 
 namespace {
-
-// Barrier that orders LDS only, so that global loads issued before it stay in
-// flight across it (a full __syncthreads would wait for them).
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
 
 using namespace mxlu;
 
@@ -501,59 +494,6 @@ __global__ __launch_bounds__(256) void gemm_f32_mfma_kernel(int64_t M, int64_t N
             }
 }
 
-// ---------------------------------------------------------------- FP32 TRSM
-// B (kb x ncols) <- L^-1 B, L unit lower kb x kb (kb <= 256), thread per row,
-// NC columns per workgroup, one LDS barrier per step; each thread reads its
-// row of L 32 columns at a time into registers, the next 32 in flight.  More
-// columns per workgroup spread each barrier over more multiply-adds.
-template <int NC>
-__global__ __launch_bounds__(256) void trsm_f32_llnu_kernel(int kb, int64_t ncols,
-                                                            const float *__restrict__ L,
-                                                            int64_t ldl, float *__restrict__ B,
-                                                            int64_t ldb) {
-    __shared__ float xs[2][NC];
-    const int i = threadIdx.x;
-    const int64_t c0 = (int64_t)blockIdx.x * NC;
-    const int nc = (int)((ncols - c0 < NC) ? ncols - c0 : NC);
-    float b[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c)
-        b[c] = (i < kb && c < nc) ? B[(size_t)i + (size_t)(c0 + c) * ldb] : 0.0f;
-    // the thread's row of L in chunks of 32 columns, the next chunk in flight
-    // while the current one is used
-    float lc[32], ln[32];
-    auto load_chunk = [&](int k0, float (&l)[32]) {
-#pragma unroll
-        for (int kk = 0; kk < 32; ++kk) {
-            const int k = k0 + kk;
-            l[kk] = (i < kb && k < kb && i > k) ? L[(size_t)i + (size_t)k * ldl] : 0.0f;
-        }
-    };
-    load_chunk(0, lc);
-    for (int k0 = 0; k0 < kb; k0 += 32) {
-        if (k0 + 32 < kb) load_chunk(k0 + 32, ln);
-#pragma unroll
-        for (int kk = 0; kk < 32; ++kk) {
-            const int k = k0 + kk;
-            if (k < kb) {
-                if (i == k)
-#pragma unroll
-                    for (int c = 0; c < NC; ++c) xs[k & 1][c] = b[c];
-                lds_barrier();
-                if (i > k && i < kb)
-#pragma unroll
-                    for (int c = 0; c < NC; ++c) b[c] = fmaf(-lc[kk], xs[k & 1][c], b[c]);
-            }
-        }
-#pragma unroll
-        for (int kk = 0; kk < 32; ++kk) lc[kk] = ln[kk];
-    }
-    if (i < kb)
-#pragma unroll
-        for (int c = 0; c < NC; ++c)
-            if (c < nc) B[(size_t)i + (size_t)(c0 + c) * ldb] = b[c];
-}
-
 // ---------------------------------------------------------------- store
 // F[i, c] <- round(P[i, c]) for the m x kb panel; for rows i >= kb also the
 // chunk-packed copy of L21 (line i - kb, value c, Mp lines) when LT is given.
@@ -1016,17 +956,7 @@ int trsm_f32_llnu(int64_t kb, int64_t ncols, const float *L, int64_t ldl, float 
     for (int64_t b0 = 0; b0 < kb; b0 += 256) {
         const int bb = (int)((kb - b0 < 256) ? kb - b0 : 256);
         const float *Lb = L + (size_t)b0 + (size_t)b0 * ldl;
-        // wide blocks (the U12 TRSM of every step): 32 columns per workgroup,
-        // which halves the workgroups re-reading the 256 x 256 diagonal block
-        // (measured: 319 against 336 ms per FP8 solve at N = 131072; 64
-        // columns, 357 ms); narrow ones (inside the panel): 16
-        if (ncols >= 8192)
-            hipLaunchKernelGGL(trsm_f32_llnu_kernel<32>, dim3((unsigned)((ncols + 31) / 32)),
-                               dim3(256), 0, s, bb, ncols, Lb, ldl, B + b0, ldb);
-        else
-            hipLaunchKernelGGL(trsm_f32_llnu_kernel<16>, dim3((unsigned)((ncols + 15) / 16)),
-                               dim3(256), 0, s, bb, ncols, Lb, ldl, B + b0, ldb);
-        MXLU_LAUNCH_CHECK();
+        MXLU_TRY(trsm_llnu<float>(bb, ncols, Lb, ldl, B + b0, ldb, s));
         if (b0 + bb < kb) {
             int rc = gemm_f32_sub(kb - b0 - bb, ncols, bb, L + (size_t)(b0 + bb) + (size_t)b0 * ldl,
                                   ldl, B + b0, ldb, B + b0 + bb, ldb, s);

@@ -31,7 +31,7 @@ template <> struct PanelOps<double> {
                     int64_t ldb, hipStream_t s) {
         for (int64_t b0 = 0; b0 < kb; b0 += 256) {
             const int64_t bb = std::min<int64_t>(256, kb - b0);
-            MXLU_TRY(trsm_llnu_f64((int)bb, ncols, &MXLU_AT(L, b0, b0, ldl), ldl, B + b0, ldb, s));
+            MXLU_TRY(trsm_llnu<double>((int)bb, ncols, &MXLU_AT(L, b0, b0, ldl), ldl, B + b0, ldb, s));
             if (b0 + bb < kb)
                 MXLU_TRY(gemm_f64_sub(kb - b0 - bb, ncols, bb, &MXLU_AT(L, b0 + bb, b0, ldl), ldl,
                                  B + b0, ldb, B + b0 + bb, ldb, s));

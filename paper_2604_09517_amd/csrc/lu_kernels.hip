@@ -1,8 +1,5 @@
-// FP64 kernels of the right-looking LU other than the panel leaves
-// (panel_leaf.hip) and the trailing GEMM (gemm_f64.hip):
-//   SWAP   row interchanges (composed, then applied column-strip-wise),
-//   DTRSM  triangular solves with a diagonal block (row per thread),
-// plus the permutation helpers of the solve (Sec. III-A.1).
+// SWAP of the right-looking LU: row interchanges, composed, then applied
+// column-strip-wise, and the deferred ones left of the panels (Sec. III-A.1).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -12,14 +9,6 @@
 #include "kernels.h"
 
 namespace {
-
-// Barrier that orders LDS only, so that global loads issued before it stay in
-// flight across it.
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
 
 // ---------------------------------------------------------------------------
 // SWAP.  compose: one workgroup turns the interchange sequence
@@ -183,78 +172,6 @@ __global__ void put_panel_rows_kernel(const double *__restrict__ T, int64_t rows
     if (i < rows) MXLU_AT(A, r0 + i, c0 + c, lda) = T[i + c * rows];
 }
 
-// ---------------------------------------------------------------------------
-// DTRSM family, kb <= 256 rows: thread i owns row i of a strip of NC columns
-// of B in registers.  Step k broadcasts the finished row k through LDS (one
-// LDS barrier per k, double-buffered) and every row still to be solved takes
-// one fused multiply-add with its factor entry, so each entry accumulates its
-// terms in the same order as the textbook substitution.  The factor entries
-// are prefetched 8 steps ahead.
-// ---------------------------------------------------------------------------
-template <int NC, bool LOWER, bool UNIT, bool TRANS>
-__global__ __launch_bounds__(256) void trsm_kernel(int kb, int64_t ncols,
-                                                   const double *__restrict__ T, int64_t ldt,
-                                                   double *__restrict__ B, int64_t ldb) {
-    __shared__ double xs[2][NC];
-    const int i = threadIdx.x;
-    const int64_t c0 = (int64_t)blockIdx.x * NC;
-    const int nc = (int)((ncols - c0 < NC) ? ncols - c0 : NC);
-    double b[NC];
-#pragma unroll
-    for (int c = 0; c < NC; ++c) b[c] = (i < kb && c < nc) ? MXLU_AT(B, i, c0 + c, ldb) : 0.0;
-
-    // Effective factor F: column k of F is the k-th column used by the
-    // substitution.  LOWER && !TRANS: L (forward).  !LOWER && !TRANS: U
-    // (backward).  !LOWER && TRANS: U^T, lower (forward).  LOWER && TRANS: L^T,
-    // upper (backward).
-    constexpr bool FORWARD = (LOWER != TRANS);
-    auto fentry = [&](int row, int k) -> double {
-        // F[row][k]
-        return TRANS ? MXLU_AT(T, k, row, ldt) : MXLU_AT(T, row, k, ldt);
-    };
-    auto needs = [&](int row, int k) -> bool { return FORWARD ? (row > k) : (row < k); };
-
-    double lbuf[8], lnext[8];
-    auto prefetch = [&](int s0, double *dst) {
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int s = s0 + q;
-            const int k = FORWARD ? s : kb - 1 - s;
-            dst[q] = (s < kb && i < kb && (needs(i, k) || (!UNIT && i == k))) ? fentry(i, k) : 0.0;
-        }
-    };
-    prefetch(0, lbuf);
-    for (int s0 = 0; s0 < kb; s0 += 8) {
-        prefetch(s0 + 8, lnext);
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int s = s0 + q;
-            if (s >= kb) break;
-            const int k = FORWARD ? s : kb - 1 - s;
-            if (i == k) {
-                if (!UNIT) {
-#pragma unroll
-                    for (int c = 0; c < NC; ++c) b[c] = b[c] / lbuf[q];
-                }
-#pragma unroll
-                for (int c = 0; c < NC; ++c) xs[s & 1][c] = b[c];
-            }
-            lds_barrier();
-            if (i < kb && needs(i, k)) {
-                const double f = lbuf[q];
-#pragma unroll
-                for (int c = 0; c < NC; ++c) b[c] = fma(-f, xs[s & 1][c], b[c]);
-            }
-        }
-#pragma unroll
-        for (int q = 0; q < 8; ++q) lbuf[q] = lnext[q];
-    }
-    if (i < kb)
-#pragma unroll
-        for (int c = 0; c < NC; ++c)
-            if (c < nc) MXLU_AT(B, i, c0 + c, ldb) = b[c];
-}
-
 }  // namespace
 
 namespace mxlu {
@@ -331,28 +248,4 @@ int laswp_left_deferred_f64(double *A, int64_t lda, int64_t n, int64_t nb,
     return 0;
 }
 
-template <bool LOWER, bool UNIT, bool TRANS>
-static int trsm_launch(int kb, int64_t ncols, const double *T, int64_t ldt, double *B,
-                       int64_t ldb, hipStream_t s) {
-    if (kb <= 0 || ncols <= 0) return 0;
-    if (kb > 256) {
-        set_error_msg("trsm: diagonal block larger than 256");
-        return MXLU_E_NOMEM;
-    }
-    if (ncols <= 4) {
-        hipLaunchKernelGGL((trsm_kernel<1, LOWER, UNIT, TRANS>), dim3((unsigned)ncols), dim3(256),
-                           0, s, kb, ncols, T, ldt, B, ldb);
-    } else {
-        const unsigned grid = (unsigned)((ncols + 15) / 16);
-        hipLaunchKernelGGL((trsm_kernel<16, LOWER, UNIT, TRANS>), dim3(grid), dim3(256), 0, s, kb,
-                           ncols, T, ldt, B, ldb);
-    }
-    MXLU_LAUNCH_CHECK();
-    return 0;
-}
-
-int trsm_llnu_f64(int kb, int64_t ncols, const double *L, int64_t ldl, double *B, int64_t ldb,
-                  hipStream_t s) {
-    return trsm_launch<true, true, false>(kb, ncols, L, ldl, B, ldb, s);
-}
 }  // namespace mxlu

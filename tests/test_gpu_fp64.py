@@ -137,6 +137,25 @@ def test_lu_factor_matches_oracle(api, n, nb):
         assert np.abs(LU - LU_ref).max() <= 1e-9 * scale
 
 
+@pytest.mark.parametrize("n,nb", [(40, 15), (45, 17), (100, 31), (290, 127), (311, 129), (420, 143),
+                                  (530, 255), (600, 257)])
+def test_lu_row_panel_solve_strip_edges(api, n, nb):
+    """Row-panel solves with diagonal blocks around the 16-row strips and the
+    128-row groups of them; bounds as in the test above."""
+    note(f"row panel solve n={n} nb={nb}")
+    A_h = inputs.uniform_matrix(391 + n, 0, n, n)
+    dA = to_dev(A_h)
+    _, ipiv, info = api.lu_factor(dA, nb)
+    torch.cuda.synchronize()
+    LU = dA.cpu().numpy()
+    LU_ref, piv_ref, info_ref = oracle.getrf(A_h, nb)
+    assert info == info_ref
+    same = assert_pivots_match(A_h, ipiv.cpu().numpy(), piv_ref)
+    assert checks.factorization_ratio(A_h, LU, ipiv.cpu().numpy()) < 10
+    if same:
+        assert np.abs(LU - LU_ref).max() <= 1e-9 * max(1.0, np.abs(LU_ref).max())
+
+
 # Sizes where depth-1 look-ahead applies (n, nb multiples of 128): the next
 # panel is factored on its own CU-masked stream while the rest of the update
 # runs on another.  Each element takes the same operations in the same order

@@ -636,6 +636,23 @@ def test_fp32_storage_factors_bitwise(api, n, nb, pivot):
     assert np.array_equal(F, F_ref)
 
 
+@pytest.mark.parametrize("n,nb", [(33, 32), (45, 32), (129, 96), (290, 128), (311, 160), (420, 224),
+                                  (530, 256), (601, 288)])
+def test_fp32_row_panel_solve_strip_edges_bitwise(api, n, nb):
+    """Row-panel solves with diagonal blocks around the 16-row strips and the
+    128-row groups of them (kb = nb for U12, smaller ones inside the panel),
+    ragged numbers of columns: bit for bit the oracle's factorization."""
+    note(f"row panel solve n={n} nb={nb}")
+    A = inputs.diag_dominant_matrix(391 + n, 0, n)
+    b = inputs.uniform_matrix(391 + n, 1, n, 1)[:, 0]
+    X, rep, work, _ = api.mxp_solve(to_dev(A), to_dev(b), prec="fp32", nb=nb, max_outer=0,
+                                    allow_notconv=True)
+    torch.cuda.synchronize()
+    F_ref, _, info = oracle.lp_getrf(A, nb, 4, pivot=False)
+    assert rep["info"] == info == 0
+    assert np.array_equal(factors_to_host(api, work, n, "fp32"), F_ref)
+
+
 @pytest.mark.parametrize("n,nb,steps,pivot", [(3200, 128, 1, False), (3200, 96, 1, False),
                                                (3400, 256, 2, False), (3200, 128, 1, True)])
 def test_fp32_matrix_core_update_bitwise(api, n, nb, steps, pivot):
