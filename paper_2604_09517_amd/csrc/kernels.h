@@ -85,29 +85,20 @@ template <typename T>
 int panel_leaf(int64_t m, int w, T *P, int64_t ldp, int64_t r0, int32_t *ipiv,
                const PanelExchange &ex, int *split, hipStream_t s);
 
-// Interchanges ipiv[j0 .. j0+cnt) (rows >= j0, cnt <= 1024, of a matrix with
-// nrows rows) composed into a list of row moves, then applied to the columns
-// c_begin + q (q < ncols, skipping [skip_begin, skip_begin + skip_len)) of a
-// matrix of T.  An interchange row outside [j0 + t, nrows) counts as none.
-int swap_compose(const int32_t *ipiv, int64_t j0, int cnt, int64_t nrows, int *moves,
-                 hipStream_t s);
-// The interchanges of every step applied to the columns left of its panel,
-// deferred to after the factorization (each element moves once).  q, r: n
-// ints of scratch; T: (n - nb) x nb doubles of scratch.
-int laswp_left_deferred_f64(double *A, int64_t lda, int64_t n, int64_t nb,
-                            const int32_t *ipiv, int *moves, int32_t *q, int32_t *r, double *T,
-                            hipStream_t s);
+// Apply the interchanges ipiv[j0 .. j0+cnt) (rows >= j0 of a matrix with nrows
+// rows, cnt <= 1024) to the columns c_begin + q (q < ncols, skipping
+// [skip_begin, skip_begin + skip_len)).  An interchange row outside [j0 + t,
+// nrows) counts as none.
 template <typename T>
-int swap_apply(T *A, int64_t lda, int64_t j0, const int *moves, int64_t c_begin, int64_t ncols,
-               int64_t skip_begin, int64_t skip_len, hipStream_t s);
-
-// Apply the interchanges ipiv[j0 .. j0+cnt) (absolute rows, cnt <= 1024) to
-// the columns c_begin + q (q < ncols, skipping [skip_begin, skip_begin +
-// skip_len)).  `moves` is a device buffer of kSwapMovesInts ints.
-constexpr int kSwapMovesInts = 1 + 4 * 1024;
-int laswp_f64(double *A, int64_t lda, int64_t nrows, const int32_t *ipiv, int64_t j0, int cnt,
-              int64_t c_begin, int64_t ncols, int64_t skip_begin, int64_t skip_len,
-              int *moves, hipStream_t s);
+int swap_rows(T *A, int64_t lda, int64_t nrows, const int32_t *ipiv, int64_t j0, int cnt,
+              int64_t c_begin, int64_t ncols, int64_t skip_begin, int64_t skip_len, hipStream_t s);
+// The interchanges of every step applied to the columns left of its panel,
+// deferred to after the factorization (each element moves once).  Scratch:
+// maps of left_swap_map_ints ints, T of left_swap_rows x nb doubles.
+int64_t left_swap_map_ints(int64_t n, int64_t nb);
+int64_t left_swap_rows(int64_t n, int64_t nb);
+int laswp_left_deferred_f64(double *A, int64_t lda, int64_t n, int64_t nb, const int32_t *ipiv,
+                            int32_t *maps, double *T, hipStream_t s);
 
 // B(kb x ncols) = L^-1 B with L unit lower (kb x kb), kb <= 256.
 template <typename T>

@@ -148,11 +148,8 @@ int lp_factorize(const mxp_opts &o, int64_t n, const ASource &src, uint16_t *F,
     if (!P32 || !T32 || !d_info) return MXLU_E_NOMEM;
     MXLU_HIP_TRY(hipMemsetAsync(d_info, 0, 4 * sizeof(int), s));
     PanelExchange ex{};
-    int *moves = nullptr;
     if (o.pivot) {
         MXLU_TRY(alloc_panel_exchange(scratch, n, &ex, s));
-        moves = scratch.alloc_n<int>(kSwapMovesInts);
-        if (!moves) return MXLU_E_NOMEM;
     }
 
     Timer tc(s), tf(s);
@@ -252,8 +249,7 @@ int lp_factorize(const mxp_opts &o, int64_t n, const ASource &src, uint16_t *F,
             if (!ahead) MXLU_TRY(pfact(k0, kb, s, cur));
             if (o.pivot && n > kb) {   // the panel's interchanges on the other stored columns
                 PhaseScope ph(kPhaseSwap, s, 8.0 * kb * (double)(n - kb));
-                MXLU_TRY(swap_compose(ipiv, k0, (int)kb, n, moves, s));
-                MXLU_TRY(swap_apply<uint16_t>(F, ldf, k0, moves, 0, n - kb, k0, kb, s));
+                MXLU_TRY(swap_rows<uint16_t>(F, ldf, n, ipiv, k0, (int)kb, 0, n - kb, k0, kb, s));
             }
             if (c1 >= n) continue;
             if (!ahead) MXLU_TRY(finish(k0, kb, s, cur));
@@ -314,11 +310,8 @@ int lp_factorize_f32(const mxp_opts &o, int64_t n, const ASource &src, float *F,
     if (!d_info) return MXLU_E_NOMEM;
     MXLU_HIP_TRY(hipMemsetAsync(d_info, 0, 4 * sizeof(int), s));
     PanelExchange ex{};
-    int *moves = nullptr;
     if (o.pivot) {
         MXLU_TRY(alloc_panel_exchange(scratch, n, &ex, s));
-        moves = scratch.alloc_n<int>(kSwapMovesInts);
-        if (!moves) return MXLU_E_NOMEM;
     }
     Timer tc(s), tf(s);
     tc.start();
@@ -345,8 +338,7 @@ int lp_factorize_f32(const mxp_opts &o, int64_t n, const ASource &src, float *F,
             }
             if (o.pivot && n > kb) {
                 PhaseScope ph(kPhaseSwap, s, 16.0 * kb * (double)(n - kb));
-                MXLU_TRY(swap_compose(ipiv, k0, (int)kb, n, moves, s));
-                MXLU_TRY(swap_apply<float>(F, ldf, k0, moves, 0, n - kb, k0, kb, s));
+                MXLU_TRY(swap_rows<float>(F, ldf, n, ipiv, k0, (int)kb, 0, n - kb, k0, kb, s));
             }
             if (c1 >= n) continue;
             const int64_t nt = n - c1;

@@ -29,36 +29,6 @@ __device__ __forceinline__ void wave_sync_lds() {
 }
 
 // ---------------------------------------------------------------------------
-// perm: the gather map of all interchanges of ipiv applied in order (row i of
-// P b is b[perm[i]]).  Each lane follows one row back through the
-// interchanges, last to first, to the row its content comes from; a row below
-// i is not touched by the interchanges after i, so a wave starts at its last
-// row.  The interchanges are uniform over the wave (scalar loads); a step is
-// two compares and two selects, about 20 cycles.  One workgroup that composed
-// them 256 at a time took 67 us at n = 1024 and 2430 us at n = 32768; this
-// form takes 9 and 280.  An entry outside [u, n) is taken as no interchange.
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(64) void perm_from_ipiv_kernel(int n, const int32_t *__restrict__ ipiv,
-                                                            int32_t *__restrict__ perm) {
-    const int i = (int)blockIdx.x * 64 + (int)threadIdx.x;
-    int src = i;
-    int u = (int)min((int64_t)n, ((int64_t)blockIdx.x + 1) * 64) - 1;
-    auto step = [&](int uu, int qq) {
-        const int q = (qq >= uu && qq < n) ? qq : uu;
-        src = (src == uu) ? q : ((src == q) ? uu : src);
-    };
-    for (; (u & 15) != 15 && u >= 0; --u) step(u, ipiv[u]);
-    for (; u >= 0; u -= 16) {
-        int q[16];
-#pragma unroll
-        for (int e = 0; e < 16; ++e) q[e] = ipiv[u - 15 + e];
-#pragma unroll
-        for (int e = 15; e >= 0; --e) step(u - 15 + e, q[e]);
-    }
-    if (i < n) perm[i] = src;
-}
-
-// ---------------------------------------------------------------------------
 // T X = B for up to 16 right-hand sides in one launch, T one of
 //   KIND 0: L (unit lower), forward      KIND 1: U (upper), backward
 //   KIND 2: U^T (lower), forward         KIND 3: L^T (unit upper), backward
@@ -428,14 +398,6 @@ int tri_chain(int64_t n, int nr, const double *T, int64_t ldt, const double *in,
 }  // namespace
 
 namespace mxlu {
-
-int perm_from_ipiv(int64_t n, const int32_t *ipiv, int32_t *perm, hipStream_t s) {
-    if (n <= 0) return 0;
-    hipLaunchKernelGGL(perm_from_ipiv_kernel, dim3((unsigned)((n + 63) / 64)), dim3(64), 0, s,
-                       (int)n, ipiv, perm);
-    MXLU_LAUNCH_CHECK();
-    return 0;
-}
 
 int tri_solve_f64(int64_t n, int nr, const double *LU, int64_t lda, const int32_t *perm, double *B,
                   int64_t ldb, int trans, double *E, int64_t lde, hipStream_t s) {

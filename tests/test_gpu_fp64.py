@@ -156,6 +156,38 @@ def test_lu_row_panel_solve_strip_edges(api, n, nb):
         assert np.abs(LU - LU_ref).max() <= 1e-9 * max(1.0, np.abs(LU_ref).max())
 
 
+@pytest.mark.parametrize("n,nb", [(70, 1), (200, 7), (190, 64), (193, 64), (700, 100), (2100, 40),
+                                  (1300, 600), (1100, 1024)])
+def test_lu_deferred_interchanges(api, n, nb):
+    """Panel boundaries on and off multiples of 64 rows, many in one such chunk,
+    steps of up to 1024 interchanges: the multipliers end in the oracle's rows
+    (uniform matrix: a row out of place differs by O(1))."""
+    note(f"deferred interchanges n={n} nb={nb}")
+    A_h = inputs.uniform_matrix(791 + n, 0, n, n)
+    dA = to_dev(A_h, ld=n + 1)
+    _, ipiv, info = api.lu_factor(dA, nb)
+    torch.cuda.synchronize()
+    LU_ref, piv_ref, info_ref = oracle.getrf(A_h, nb)
+    assert info == info_ref
+    if assert_pivots_match(A_h, ipiv.cpu().numpy(), piv_ref):
+        assert np.abs(dA.cpu().numpy() - LU_ref).max() <= 1e-9 * max(1.0, np.abs(LU_ref).max())
+
+
+@pytest.mark.parametrize("n,nb", [(9000, 128), (33100, 64)])
+def test_lu_deferred_interchanges_tall(api, n, nb):
+    """Panels with more than 8192 rows below them, and with more than a
+    workgroup holds; at 33100 rows not all row maps fit their scratch at once."""
+    note(f"deferred interchanges n={n} nb={nb}")
+    dA = api.fortran_empty(n, n)
+    api.fill_uniform(dA, 4242, inputs.STREAM_A)
+    b = torch.ones(n, dtype=torch.float64, device="cuda")
+    A0 = dA.clone()
+    _, ipiv, info = api.lu_factor(dA, nb)
+    assert info == 0
+    x = api.lu_solve(dA, ipiv, b.clone())
+    assert api.scaled_residual(A0, x, b)[0] < 16
+
+
 # Sizes where depth-1 look-ahead applies (n, nb multiples of 128): the next
 # panel is factored on its own CU-masked stream while the rest of the update
 # runs on another.  Each element takes the same operations in the same order
