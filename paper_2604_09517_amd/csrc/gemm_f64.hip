@@ -284,39 +284,6 @@ __global__ __launch_bounds__(256) void pack_neg_transpose_kernel(int64_t K, int6
     }
 }
 
-// Tall-skinny update for few right-hand sides (N <= 16): C -= A * B with one
-// thread per row of C; B (K x N) is staged in LDS.  Memory-bound on A.
-template <int NMAX>
-__global__ __launch_bounds__(256) void gemm_f64_sub_skinny_kernel(
-    int64_t M, int N, int64_t K, const double *__restrict__ A, int64_t lda,
-    const double *__restrict__ B, int64_t ldb, double *__restrict__ C, int64_t ldc) {
-    __shared__ double Bs[256 * NMAX];
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    double acc[NMAX];
-#pragma unroll
-    for (int c = 0; c < NMAX; ++c) acc[c] = (i < M && c < N) ? MXLU_AT(C, i, c, ldc) : 0.0;
-    for (int64_t k0 = 0; k0 < K; k0 += 256) {
-        const int kc = (int)((K - k0 < 256) ? K - k0 : 256);
-        __syncthreads();
-        for (int t = threadIdx.x; t < kc * NMAX; t += 256) {
-            const int k = t % kc, c = t / kc;
-            Bs[k * NMAX + c] = (c < N) ? MXLU_AT(B, k0 + k, c, ldb) : 0.0;
-        }
-        __syncthreads();
-        if (i < M) {
-            for (int k = 0; k < kc; ++k) {
-                const double a = MXLU_AT(A, i, k0 + k, lda);
-#pragma unroll
-                for (int c = 0; c < NMAX; ++c) acc[c] = fma(-a, Bs[k * NMAX + c], acc[c]);
-            }
-        }
-    }
-    if (i < M)
-#pragma unroll
-        for (int c = 0; c < NMAX; ++c)
-            if (c < N) MXLU_AT(C, i, c, ldc) = acc[c];
-}
-
 }  // namespace
 
 namespace mxlu {
@@ -325,22 +292,17 @@ int gemm_f64_sub(int64_t M, int64_t N, int64_t K, const double *A, int64_t lda,
                  const double *B, int64_t ldb, double *C, int64_t ldc, hipStream_t s,
                  bool trailing) {
     if (M <= 0 || N <= 0 || K <= 0) return 0;
-    if (N <= 16) {
-        const unsigned grid = (unsigned)((M + 255) / 256);
-        if (N == 1)
-            hipLaunchKernelGGL(gemm_f64_sub_skinny_kernel<1>, dim3(grid), dim3(256), 0, s, M,
-                               (int)N, K, A, lda, B, ldb, C, ldc);
-        else
-            hipLaunchKernelGGL(gemm_f64_sub_skinny_kernel<16>, dim3(grid), dim3(256), 0, s, M,
-                               (int)N, K, A, lda, B, ldb, C, ldc);
-        MXLU_LAUNCH_CHECK();
-        return 0;
-    }
     const int64_t tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
     if (tiles_m * tiles_n > 0x7fffffff) {
         set_error_msg("gemm_f64_sub: grid too large");
         return MXLU_E_NOMEM;
     }
+    // fewer columns than a tile, or fewer tiles than CUs: 64 x 64 tiles (N = K
+    // = 32, 4000 rows 17 -> 4.9 us; 970 x 970, K = 64 29 -> 10.5; with more
+    // tiles the larger ones win, 2500 x 2500, K = 256 at 32 against 23
+    // TFLOP/s)
+    if (N <= 128 || tiles_m * tiles_n < 256)
+        return gemm_panel_sub<double>(M, N, K, A, lda, B, ldb, C, ldc, s);
     // the bounds-check-free instance serves the trailing update only, so that
     // its launches are exactly the DGEMM phase
     const bool full = trailing && (M % BM == 0) && (N % BN == 0) && (K % BK == 0);

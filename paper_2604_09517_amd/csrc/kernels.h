@@ -100,6 +100,11 @@ int64_t left_swap_rows(int64_t n, int64_t nb);
 int laswp_left_deferred_f64(double *A, int64_t lda, int64_t n, int64_t nb, const int32_t *ipiv,
                             int32_t *maps, double *T, hipStream_t s);
 
+// C (M x N) -= A (M x K) B (K x N), tiles of 64 x 64 (gemm_panel.hip).
+template <typename T>
+int gemm_panel_sub(int64_t M, int64_t N, int64_t K, const T *A, int64_t lda, const T *B, int64_t ldb,
+                   T *C, int64_t ldc, hipStream_t s);
+
 // B(kb x ncols) = L^-1 B with L unit lower (kb x kb), kb <= 256.
 template <typename T>
 int trsm_llnu(int kb, int64_t ncols, const T *L, int64_t ldl, T *B, int64_t ldb, hipStream_t s);

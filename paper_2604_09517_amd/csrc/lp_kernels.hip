@@ -258,153 +258,18 @@ __global__ __launch_bounds__(256) void lp_leaf_nopiv_kernel(int m, int kb, int c
 
 // ---------------------------------------------------------------- FP32 GEMM
 // C (M x N) -= A (M x K) B (K x N), FP32, one fused multiply-add per term in
-// ascending k starting from C (the elimination order).  64 x 64 tiles,
-// 256 threads, 4 x 4 outputs per thread, K staged in chunks of 16.
-__global__ __launch_bounds__(256) void gemm_f32_sub_kernel(int64_t M, int64_t N, int64_t K,
-                                                           const float *__restrict__ A,
-                                                           int64_t lda,
-                                                           const float *__restrict__ B,
-                                                           int64_t ldb, float *__restrict__ C,
-                                                           int64_t ldc, int tiles_m) {
-    __shared__ float As[16][64 + 1];
-    __shared__ float Bs[16][64 + 1];
-    const int tm = blockIdx.x % tiles_m, tn = blockIdx.x / tiles_m;
-    const int64_t row0 = (int64_t)tm * 64, col0 = (int64_t)tn * 64;
-    const int tid = threadIdx.x;
-    const int tr = tid & 15, tc = tid >> 4;
-    float acc[4][4];
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const int64_t r = row0 + tr + 16 * a, cc = col0 + tc + 16 * b;
-            acc[a][b] = (r < M && cc < N) ? C[(size_t)r + (size_t)cc * ldc] : 0.0f;
-        }
-    for (int64_t k0 = 0; k0 < K; k0 += 16) {
-        for (int t = tid; t < 16 * 64; t += 256) {
-            const int i = t % 64, k = t / 64;
-            const int64_t r = row0 + i, kk = k0 + k;
-            As[k][i] = (r < M && kk < K) ? A[(size_t)r + (size_t)kk * lda] : 0.0f;
-        }
-        for (int t = tid; t < 16 * 64; t += 256) {
-            const int k = t % 16, j = t / 16;
-            const int64_t cc = col0 + j, kk = k0 + k;
-            Bs[k][j] = (cc < N && kk < K) ? B[(size_t)kk + (size_t)cc * ldb] : 0.0f;
-        }
-        __syncthreads();
-        const int kc = (int)((K - k0 < 16) ? K - k0 : 16);
-        for (int k = 0; k < kc; ++k) {
-            float av[4], bv[4];
-#pragma unroll
-            for (int a = 0; a < 4; ++a) av[a] = As[k][tr + 16 * a];
-#pragma unroll
-            for (int b = 0; b < 4; ++b) bv[b] = Bs[k][tc + 16 * b];
-#pragma unroll
-            for (int a = 0; a < 4; ++a)
-#pragma unroll
-                for (int b = 0; b < 4; ++b) acc[a][b] = fmaf(-av[a], bv[b], acc[a][b]);
-        }
-        __syncthreads();
-    }
-#pragma unroll
-    for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const int64_t r = row0 + tr + 16 * a, cc = col0 + tc + 16 * b;
-            if (r < M && cc < N) C[(size_t)r + (size_t)cc * ldc] = acc[a][b];
-        }
-}
-
-// Large-tile form for the panel's big updates: 128 x 128 tiles, 256 threads,
-// 8 x 8 outputs per thread (rows 4 ty + {0..3} and 64 + 4 ty + {0..3},
-// columns 4 tx + {0..3} and 64 + 4 tx + {0..3}), K in chunks of 16 staged
-// through two LDS buffers; the next chunk's global loads are in flight in
-// registers while the current one is used.  The same order of terms as the
-// small-tile form: one fused multiply-add per term in ascending k from C.
-constexpr int kG32Tile = 128, kG32Kc = 16, kG32Ld = kG32Tile + 4;
-
-__global__ __launch_bounds__(256) void gemm_f32_sub_big_kernel(int64_t M, int64_t N, int64_t K,
-                                                               const float *__restrict__ A,
-                                                               int64_t lda,
-                                                               const float *__restrict__ B,
-                                                               int64_t ldb, float *__restrict__ C,
-                                                               int64_t ldc, int tiles_m) {
-    __shared__ __attribute__((aligned(16))) float As[2][kG32Kc][kG32Ld];
-    __shared__ __attribute__((aligned(16))) float Bs[2][kG32Kc][kG32Ld];
-    const int tm = blockIdx.x % tiles_m, tn = blockIdx.x / tiles_m;
-    const int64_t row0 = (int64_t)tm * kG32Tile, col0 = (int64_t)tn * kG32Tile;
-    const int tid = threadIdx.x;
-    const int tx = tid & 15, ty = tid >> 4;
-    // global load roles: A rows (tid % 128), k = tid / 128 + 2 q; B k = tid % 16,
-    // columns tid / 16 + 16 q (q < 8)
-    const int ar = tid & 127, ak = tid >> 7;
-    const int bk = tid & 15, bc = tid >> 4;
-    float ra[8], rb[8];
-    auto load = [&](int64_t k0) {
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int64_t r = row0 + ar, kk = k0 + ak + 2 * q;
-            ra[q] = (r < M && kk < K) ? A[(size_t)r + (size_t)kk * lda] : 0.0f;
-            const int64_t cc = col0 + bc + 16 * q, kb = k0 + bk;
-            rb[q] = (cc < N && kb < K) ? B[(size_t)kb + (size_t)cc * ldb] : 0.0f;
-        }
-    };
-    auto store = [&](int buf) {
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            As[buf][ak + 2 * q][ar] = ra[q];
-            Bs[buf][bk][bc + 16 * q] = rb[q];
-        }
-    };
-    float acc[8][8];
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int64_t r = row0 + (i < 4 ? 4 * ty + i : 64 + 4 * ty + i - 4);
-            const int64_t cc = col0 + (j < 4 ? 4 * tx + j : 64 + 4 * tx + j - 4);
-            acc[i][j] = (r < M && cc < N) ? C[(size_t)r + (size_t)cc * ldc] : 0.0f;
-        }
-    const int nk = (int)((K + kG32Kc - 1) / kG32Kc);
-    load(0);
-    store(0);
-    __syncthreads();
-    for (int kt = 0; kt < nk; ++kt) {
-        const int buf = kt & 1;
-        if (kt + 1 < nk) load((int64_t)(kt + 1) * kG32Kc);
-        const int kc = (int)((K - (int64_t)kt * kG32Kc < kG32Kc) ? K - (int64_t)kt * kG32Kc : kG32Kc);
-        for (int k = 0; k < kc; ++k) {
-            const float4 a0 = *reinterpret_cast<const float4 *>(&As[buf][k][4 * ty]);
-            const float4 a1 = *reinterpret_cast<const float4 *>(&As[buf][k][64 + 4 * ty]);
-            const float4 b0 = *reinterpret_cast<const float4 *>(&Bs[buf][k][4 * tx]);
-            const float4 b1 = *reinterpret_cast<const float4 *>(&Bs[buf][k][64 + 4 * tx]);
-            const float av[8] = {a0.x, a0.y, a0.z, a0.w, a1.x, a1.y, a1.z, a1.w};
-            const float bv[8] = {b0.x, b0.y, b0.z, b0.w, b1.x, b1.y, b1.z, b1.w};
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-#pragma unroll
-                for (int j = 0; j < 8; ++j) acc[i][j] = fmaf(-av[i], bv[j], acc[i][j]);
-        }
-        if (kt + 1 < nk) store(buf ^ 1);
-        __syncthreads();
-    }
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int64_t r = row0 + (i < 4 ? 4 * ty + i : 64 + 4 * ty + i - 4);
-            const int64_t cc = col0 + (j < 4 ? 4 * tx + j : 64 + 4 * tx + j - 4);
-            if (r < M && cc < N) C[(size_t)r + (size_t)cc * ldc] = acc[i][j];
-        }
-}
+// ascending k starting from C (the elimination order): the shapes inside a
+// panel and all small ones by gemm_panel_sub, the others here.
+constexpr int kG32Tile = 128, kG32Kc = 16;
 
 // Matrix-core form: 128 x 128 tiles, 256 threads, each wave a 64 x 64
 // quarter as 4 x 4 blocks of v_mfma_f32_16x16x4f32, K staged through LDS in
-// chunks of 16 like the large-tile form.  The instruction computes each
+// two buffers of 16 k, the next chunk's global loads in flight in registers
+// while the current one is used.  The instruction computes each
 // output as four fused multiply-adds in ascending k (measured bit for bit
 // against fmaf on millions of random operands), and the blocks walk k in
 // ascending groups of four from C with A negated, so every element takes the
-// same terms in the same order as the other forms.  K % 4 == 0: no padded
+// same terms in the same order as the panel form.  K % 4 == 0: no padded
 // term ever enters a sum.
 // Lane l of a block supplies A[row l % 16][k l / 16] and B[k l / 16][col
 // l % 16] and holds rows 4 (l / 16) + r of column l % 16 of the result.
@@ -888,26 +753,15 @@ int lp_store_f32(int fmt, int64_t rows, int64_t cols, const float *P, int64_t ld
 int gemm_f32_sub(int64_t M, int64_t N, int64_t K, const float *A, int64_t lda, const float *B,
                  int64_t ldb, float *C, int64_t ldc, hipStream_t s) {
     if (M <= 0 || N <= 0 || K <= 0) return 0;
-    {   // large-tile forms when they still give every CU a few tiles
-        const int64_t tm = (M + kG32Tile - 1) / kG32Tile, tn = (N + kG32Tile - 1) / kG32Tile;
-        if (K >= 32 && M >= 96 && N >= 96 && tm * tn >= 512 && tm * tn <= 0x7fffffff) {
-            if (K % 4 == 0)
-                hipLaunchKernelGGL(gemm_f32_mfma_kernel, dim3((unsigned)(tm * tn)), dim3(256), 0,
-                                   s, M, N, K, A, lda, B, ldb, C, ldc, (int)tm);
-            else
-                hipLaunchKernelGGL(gemm_f32_sub_big_kernel, dim3((unsigned)(tm * tn)), dim3(256), 0,
-                                   s, M, N, K, A, lda, B, ldb, C, ldc, (int)tm);
-            MXLU_LAUNCH_CHECK();
-            return 0;
-        }
-    }
-    const int64_t tm = (M + 63) / 64, tn = (N + 63) / 64;
-    if (tm * tn > 0x7fffffff) {
-        set_error_msg("gemm_f32_sub: grid too large");
-        return MXLU_E_NOMEM;
-    }
-    hipLaunchKernelGGL(gemm_f32_sub_kernel, dim3((unsigned)(tm * tn)), dim3(256), 0, s, M, N, K,
-                       A, lda, B, ldb, C, ldc, (int)tm);
+    // 128 x 128 tiles when they still give every CU a few of them and the
+    // panel form's 64 columns at a time would read A more than four times
+    // (N = K = 256, 65000 rows: 165 us by 64 columns, 170 to 200 by 128 x 128
+    // tiles)
+    const int64_t tm = (M + kG32Tile - 1) / kG32Tile, tn = (N + kG32Tile - 1) / kG32Tile;
+    if (N <= 256 || K < 32 || K % 4 != 0 || M < 96 || tm * tn < 512 || tm * tn > 0x7fffffff)
+        return gemm_panel_sub<float>(M, N, K, A, lda, B, ldb, C, ldc, s);
+    hipLaunchKernelGGL(gemm_f32_mfma_kernel, dim3((unsigned)(tm * tn)), dim3(256), 0, s, M, N, K, A,
+                       lda, B, ldb, C, ldc, (int)tm);
     MXLU_LAUNCH_CHECK();
     return 0;
 }

@@ -95,6 +95,30 @@ def test_schur_update_against_definition(api, M, N, K):
     assert np.all(np.abs(got - ref) <= bound)
 
 
+@pytest.mark.parametrize("M,N,K", [(63, 15, 31), (64, 16, 32), (65, 17, 33), (129, 32, 64),
+                                   (200, 33, 65), (64, 64, 96), (190, 65, 97), (1, 130, 5),
+                                   (3000, 128, 40), (1100, 1200, 70), (2100, 2200, 18)])
+def test_schur_update_narrow_tiles(api, M, N, K):
+    """Edges of the 64-row, 16/32/64-column tiles and of the 32-k chunks, and
+    the two sides of the choice between them and the large tiles: the bound of
+    the test above; an infinity in the last column of A stays in its row."""
+    note(f"schur narrow M={M} N={N} K={K}")
+    rng = np.random.default_rng(M * 7 + N * 3 + K)
+    A = rng.uniform(-1, 1, (M, K))
+    B = rng.uniform(0.5, 1, (K, N))
+    C = rng.uniform(-1, 1, (M, N))
+    A[M - 1, K - 1] = np.inf
+    dC = to_dev(C, ld=M + 1)
+    api.schur_update(dC, to_dev(A, ld=M + 3), to_dev(B))
+    torch.cuda.synchronize()
+    got = dC.cpu().numpy()
+    assert np.all(got[M - 1] == -np.inf)
+    A, C, got = A[:M - 1], C[:M - 1], got[:M - 1]
+    g = (K + 1) * EPS / (1 - (K + 1) * EPS)
+    bound = 2 * g * (np.abs(C) + np.abs(A) @ np.abs(B)) + 1e-300
+    assert np.all(np.abs(got - (C - A @ B)) <= bound)
+
+
 def test_schur_update_uses_each_product_once(api):
     """Integer data: every product and partial sum is exact, so the result is
     exactly C - AB (catches a dropped or doubled k step or a wrong layout)."""
