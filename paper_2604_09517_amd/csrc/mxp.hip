@@ -637,7 +637,15 @@ int mxp_impl(int64_t n, int64_t nrhs, const ASource &src, const double *B, int64
     }
     c.s = s;
     c.o = &o;
-    c.nsplit = (int)std::max<int64_t>(1, std::min<int64_t>(32, n / 2048));
+    // Splits of the columns in a residual product (a thread per row or two):
+    // enough for about 1024 workgroups of 512 rows, 32 columns each at least,
+    // 32 for the tallest.  One split per 2048 rows left n = 1000 on two
+    // workgroups (50 us a product, now 6) and n = 3001 on twelve (257 us,
+    // now 13).  The transposed product has a wave per column: splits only
+    // where a column is long.
+    c.nsplit = (int)std::max<int64_t>(
+        1, o.trans ? std::min<int64_t>(32, n / 2048)
+                   : std::min<int64_t>({n / 32, 64, std::max<int64_t>(32, 1024 * 512 / n)}));
     c.nchunks = (int)std::max<int64_t>(1, std::min<int64_t>(128, n / 1024));
     const int m1 = o.restart + 1;
     c.r = scratch.alloc_n<double>((size_t)n);

@@ -42,6 +42,18 @@ __global__ __launch_bounds__(256) void gemv_n_partial_kernel(int64_t n, ASource 
         const double *__restrict__ A = src.A;
         const int64_t lda = src.lda;
         int64_t j = j0;
+        // sixteen columns of 8-byte loads in flight
+        for (; j + 16 <= j1; j += 16) {
+            double a[16];
+#pragma unroll
+            for (int q = 0; q < 16; ++q) a[q] = MXLU_AT(A, i, j + q, lda);
+#pragma unroll
+            for (int q = 0; q < 16; ++q) acc = fma(a[q], x[j + q], acc);
+            if (asum_part)
+#pragma unroll
+                for (int q = 0; q < 16; q += 4)
+                    as += fabs(a[q]) + fabs(a[q + 1]) + fabs(a[q + 2]) + fabs(a[q + 3]);
+        }
         for (; j + 4 <= j1; j += 4) {
             const double a0 = MXLU_AT(A, i, j, lda), a1 = MXLU_AT(A, i, j + 1, lda);
             const double a2 = MXLU_AT(A, i, j + 2, lda), a3 = MXLU_AT(A, i, j + 3, lda);
@@ -201,15 +213,26 @@ __global__ void gemv_finish_kernel(int64_t n, int nsplit, const double *__restri
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     double m_y = 0.0, m_a = 0.0, m_x = 0.0;
     if (i < n) {
-        double s = 0.0;
-        for (int k = 0; k < nsplit; ++k) s += part[(size_t)k * n + i];
+        // the partial sums in order, sixteen loads in flight
+        auto total = [&](const double *__restrict__ p) {
+            double s = 0.0;
+            int k = 0;
+            for (; k + 16 <= nsplit; k += 16) {
+                double v[16];
+#pragma unroll
+                for (int q = 0; q < 16; ++q) v[q] = p[(size_t)(k + q) * n + i];
+#pragma unroll
+                for (int q = 0; q < 16; ++q) s += v[q];
+            }
+            for (; k < nsplit; ++k) s += p[(size_t)k * n + i];
+            return s;
+        };
+        const double s = total(part);
         const double v = b ? b[i] - s : s;
         y[i] = v;
         m_y = fabs(v);
         if (asum_part) {
-            double a = 0.0;
-            for (int k = 0; k < nsplit; ++k) a += asum_part[(size_t)k * n + i];
-            m_a = a;
+            m_a = total(asum_part);
         }
         if (xv) m_x = fabs(xv[i]);
     }
