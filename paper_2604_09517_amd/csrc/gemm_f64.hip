@@ -10,9 +10,9 @@
 //     accumulators of v_mfma_f64_16x16x4_f64 (64 doubles per lane).
 //   * The accumulators start from C and the MFMA consumes -A, so the tile is
 //     read once and written once: C - sum_k a_ik b_kj in one pass.
-//   * K is walked in chunks of 16; A and B chunks are staged in LDS, double
-//     buffered, with the next chunk's global loads in flight during the MFMAs
-//     of the current one (one workgroup barrier per chunk).
+//   * K is walked in steps of four k, operands loaded a few steps ahead;
+//     chunks of B of 16 k go through LDS in the general kernel, through a
+//     packed copy in the one for whole tiles.
 //   * Tile order: consecutive workgroup ids are dealt round-robin over the 8
 //     XCDs, so ids are remapped to give every XCD a contiguous run of tiles,
 //     and tiles are ordered in groups of 8 tile-rows so that tiles that share
@@ -23,6 +23,8 @@
 // register r holds D[q + 4r][i].
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "common.h"
 #include "kernels.h"
 
@@ -31,10 +33,15 @@ namespace {
 typedef double v4d __attribute__((ext_vector_type(4)));
 
 constexpr int BM = 128, BN = 128, BK = 16;
-constexpr int APAD = 4, BPAD = 4;   // LDS row padding (doubles)
-constexpr int AST = BM + APAD;      // LDS stride of one k-row of the A chunk
-constexpr int BST = BN + BPAD;
+constexpr int BST = BN + 4;   // LDS row of a k (padded: 16 k's of a column spread over the banks)
 constexpr int GROUP_M = 8;
+
+// Barrier that orders LDS only, so that global loads stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+    __builtin_amdgcn_s_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
 
 __device__ inline void tile_of(int g, int tiles_m, int tiles_n, int &tm, int &tn) {
     const int G = tiles_m * tiles_n;
@@ -53,114 +60,121 @@ __device__ inline void tile_of(int g, int tiles_m, int tiles_n, int &tm, int &tn
     tn = r / gsize;
 }
 
+// Any shape, alignment and leading dimension.  The product is formed
+// transposed (matrix rows: columns of C), so that the 16 lanes of a quarter
+// wave are 16 consecutive rows of A and of C: A goes straight into the operand
+// registers, three steps of four k ahead, by 8-byte loads that need no alignment,
+// and C moves as whole lines; the chunk of B, which all waves need, goes
+// through two LDS buffers (one barrier a chunk).  No load is under a
+// condition: rows and columns past the matrix read others' values and are not
+// stored, terms past K are made zeros in the last chunk.
+// 6100 x 7003, K = 300: 688 -> 590 us (43 TFLOP/s; a form that staged A too,
+// by loads under a condition each, had 37); 4700 x 4700, K = 256: 288 -> 235.
+// Bound by the matrix cores (330 us) and by C (683 MB, 157 us), which hardly
+// overlap, and by the last round of tiles.
 // TRANSB: B is given as its transpose (element (k, j) at B[j + k ldb]);
 // ZEROC: C starts from zero instead of being read.
-template <bool FULL, bool TRANSB, bool ZEROC>
+template <bool TRANSB, bool ZEROC>
 __global__ __launch_bounds__(256, 2) void gemm_f64_sub_kernel(
     int64_t M, int64_t N, int64_t K, const double *__restrict__ A, int64_t lda,
     const double *__restrict__ B, int64_t ldb, double *__restrict__ C, int64_t ldc,
     int tiles_m, int tiles_n) {
-    __shared__ double As[2][BK * AST];
-    __shared__ double Bs[2][BK * BST];
+    __shared__ double Bs[2][BK][BST];
 
     int tm, tn;
     tile_of(blockIdx.x, tiles_m, tiles_n, tm, tn);
-    const int64_t row0 = (int64_t)tm * BM;
-    const int64_t col0 = (int64_t)tn * BN;
-
     const int tid = threadIdx.x;
     const int wave = tid >> 6, lane = tid & 63;
-    const int wm = wave & 1, wn = wave >> 1;
     const int li = lane & 15, lq = lane >> 4;
+    const int64_t row0 = (int64_t)tm * BM + (wave & 1) * 64 + li;   // of the lane, tile 0
+    const int64_t col0 = (int64_t)tn * BN;
+    const int wn = (wave >> 1) * 64;
 
-    // ---- accumulators <- C -------------------------------------------------
-    v4d acc[4][4];
+    // the lane's rows of A; a step of four k at a time, three steps ahead
+    const double *Ar[4];
 #pragma unroll
-    for (int bi = 0; bi < 4; ++bi)
+    for (int i = 0; i < 4; ++i) Ar[i] = A + (row0 + 16 * i < M ? row0 + 16 * i : M - 1);
+    auto load_a = [&](int64_t k, double (&a)[4]) {
+        const size_t off = (size_t)(k + lq < K ? k + lq : K - 1) * (size_t)lda;
 #pragma unroll
-        for (int bj = 0; bj < 4; ++bj) {
-            const int64_t r = row0 + wm * 64 + bi * 16 + lq;
-            const int64_t c = col0 + wn * 64 + bj * 16 + li;
+        for (int i = 0; i < 4; ++i) a[i] = Ar[i][off];
+    };
+    // the thread's part of a chunk of B: columns bc + 16 q of one k, or
+    // (TRANSB) k's bk + 2 q of one column
+    const int bk = TRANSB ? tid >> 7 : tid & 15, bc = TRANSB ? tid & 127 : tid >> 4;
+    auto load_b = [&](int64_t k0, double (&b)[8]) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int64_t c = col0 + bc + (TRANSB ? 0 : 16 * q), cc = c < N ? c : N - 1;
+            const int64_t k = k0 + bk + (TRANSB ? 2 * q : 0), kc = k < K ? k : K - 1;
+            b[q] = TRANSB ? MXLU_AT(B, cc, kc, ldb) : MXLU_AT(B, kc, cc, ldb);
+        }
+    };
+    auto put_b = [&](int64_t k0, int buf, const double (&b)[8]) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int k = bk + (TRANSB ? 2 * q : 0);
+            Bs[buf][k][bc + (TRANSB ? 0 : 16 * q)] = k0 + k < K ? -b[q] : -0.0;
+        }
+    };
+
+    constexpr int D = BK / 4;   // steps of a chunk, sets of the ring
+    double a[D][4], b[8];
+    if (K > 0) {
+        load_b(0, b);
+#pragma unroll
+        for (int u = 0; u < D - 1; ++u) load_a(4 * u, a[u]);
+    }
+    v4d acc[4][4];   // [tile of columns][tile of rows]: columns lq + 4 e, row li
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                double v = 0.0;
-                if (!ZEROC && (FULL || (r + 4 * e < M && c < N))) v = MXLU_AT(C, r + 4 * e, c, ldc);
-                acc[bi][bj][e] = v;
+                const int64_t r = row0 + 16 * i, c = col0 + wn + 16 * j + lq + 4 * e;
+                acc[j][i][e] = ZEROC ? 0.0 : MXLU_AT(C, r < M ? r : M - 1, c < N ? c : N - 1, ldc);
             }
-        }
-
-    // ---- global -> register staging of one K chunk --------------------------
-    // A chunk (BM x BK): thread -> row i = tid % 128, k = (tid / 128) * 8 + q
-    // B chunk (BK x BN): thread -> col j = tid / 2,  k = (tid % 2) * 8 + q
-    const int a_i = tid & 127, a_k0 = (tid >> 7) * 8;
-    const int b_j = TRANSB ? (tid & 127) : (tid >> 1);
-    const int b_k0 = TRANSB ? (tid >> 7) * 8 : (tid & 1) * 8;
-    double ra[8], rb[8];
-
-    auto load_chunk = [&](int64_t k0) {
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int64_t k = k0 + a_k0 + q;
-            const int64_t r = row0 + a_i;
-            ra[q] = (FULL || (r < M && k < K)) ? MXLU_AT(A, r, k, lda) : 0.0;
-        }
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-            const int64_t k = k0 + b_k0 + q;
-            const int64_t c = col0 + b_j;
-            rb[q] = (FULL || (k < K && c < N))
-                        ? (TRANSB ? MXLU_AT(B, c, k, ldb) : MXLU_AT(B, k, c, ldb))
-                        : 0.0;
-        }
-    };
-    auto store_chunk = [&](int buf) {
-#pragma unroll
-        for (int q = 0; q < 8; ++q) As[buf][(a_k0 + q) * AST + a_i] = -ra[q];
-#pragma unroll
-        for (int q = 0; q < 8; ++q) Bs[buf][(b_k0 + q) * BST + b_j] = rb[q];
-    };
-
-    const int nk = (int)((K + BK - 1) / BK);
-    load_chunk(0);
-    store_chunk(0);
-    __syncthreads();
+    if (K > 0) put_b(0, 0, b);
     retire_vector_loads();
-
-    for (int kt = 0; kt < nk; ++kt) {
-        const int buf = kt & 1;
-        if (kt + 1 < nk) load_chunk((int64_t)(kt + 1) * BK);
-        const double *as = As[buf];
-        const double *bs = Bs[buf];
+    for (int64_t k0 = 0; k0 < K; k0 += BK) {
+        const int h = (int)(k0 / BK) & 1;
+        lds_barrier();   // this chunk of B is there, the one before is consumed
+        load_b(k0 + BK, b);   // past the end: the last values again, not used
 #pragma unroll
-        for (int kk = 0; kk < BK; kk += 4) {
-            double a[4], b[4];
+        for (int u = 0; u < D; ++u) {
+            load_a(k0 + 4 * (u + D - 1), a[(u + D - 1) % D]);
+            __builtin_amdgcn_sched_barrier(0);   // (left alone, the loads sink to their use)
+            double av[4], bv[4];
 #pragma unroll
-            for (int bi = 0; bi < 4; ++bi) a[bi] = as[(kk + lq) * AST + wm * 64 + bi * 16 + li];
+            for (int i = 0; i < 4; ++i) av[i] = a[u][i];
+            if (k0 + BK > K)
 #pragma unroll
-            for (int bj = 0; bj < 4; ++bj) b[bj] = bs[(kk + lq) * BST + wn * 64 + bj * 16 + li];
+                for (int i = 0; i < 4; ++i) av[i] = k0 + 4 * u + lq < K ? av[i] : 0.0;
 #pragma unroll
-            for (int bi = 0; bi < 4; ++bi)
+            for (int j = 0; j < 4; ++j) bv[j] = Bs[h][4 * u + lq][wn + 16 * j + li];
 #pragma unroll
-                for (int bj = 0; bj < 4; ++bj)
-                    acc[bi][bj] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[bi], b[bj], acc[bi][bj],
-                                                                       0, 0, 0);
+            for (int j = 0; j < 4; ++j)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    acc[j][i] = __builtin_amdgcn_mfma_f64_16x16x4f64(bv[j], av[i], acc[j][i], 0, 0, 0);
         }
-        if (kt + 1 < nk) store_chunk(buf ^ 1);
-        __syncthreads();
+        put_b(k0 + BK, h ^ 1, b);
     }
-
-    // ---- C <- accumulators -------------------------------------------------
+    const bool inside = (int64_t)(tm + 1) * BM <= M && col0 + BN <= N;   // uniform
+    auto store = [&](auto all) {
 #pragma unroll
-    for (int bi = 0; bi < 4; ++bi)
+        for (int j = 0; j < 4; ++j)
 #pragma unroll
-        for (int bj = 0; bj < 4; ++bj) {
-            const int64_t r = row0 + wm * 64 + bi * 16 + lq;
-            const int64_t c = col0 + wn * 64 + bj * 16 + li;
+            for (int i = 0; i < 4; ++i)
 #pragma unroll
-            for (int e = 0; e < 4; ++e)
-                if (FULL || (r + 4 * e < M && c < N))
-                    MXLU_AT(C, r + 4 * e, c, ldc) = acc[bi][bj][e];
-        }
+                for (int e = 0; e < 4; ++e) {
+                    const int64_t r = row0 + 16 * i, c = col0 + wn + 16 * j + lq + 4 * e;
+                    if (decltype(all)::value || (r < M && c < N)) MXLU_AT(C, r, c, ldc) = acc[j][i][e];
+                }
+    };
+    if (inside) store(std::true_type{});
+    else store(std::false_type{});
 }
 
 // Trailing update of the factorization, full tiles only: C -= A B with the
@@ -289,8 +303,7 @@ __global__ __launch_bounds__(256) void pack_neg_transpose_kernel(int64_t K, int6
 namespace mxlu {
 
 int gemm_f64_sub(int64_t M, int64_t N, int64_t K, const double *A, int64_t lda,
-                 const double *B, int64_t ldb, double *C, int64_t ldc, hipStream_t s,
-                 bool trailing) {
+                 const double *B, int64_t ldb, double *C, int64_t ldc, hipStream_t s) {
     if (M <= 0 || N <= 0 || K <= 0) return 0;
     const int64_t tiles_m = (M + BM - 1) / BM, tiles_n = (N + BN - 1) / BN;
     if (tiles_m * tiles_n > 0x7fffffff) {
@@ -303,16 +316,9 @@ int gemm_f64_sub(int64_t M, int64_t N, int64_t K, const double *A, int64_t lda,
     // TFLOP/s)
     if (N <= 128 || tiles_m * tiles_n < 256)
         return gemm_panel_sub<double>(M, N, K, A, lda, B, ldb, C, ldc, s);
-    // the bounds-check-free instance serves the trailing update only, so that
-    // its launches are exactly the DGEMM phase
-    const bool full = trailing && (M % BM == 0) && (N % BN == 0) && (K % BK == 0);
     const dim3 grid((unsigned)(tiles_m * tiles_n));
-    if (full)
-        hipLaunchKernelGGL((gemm_f64_sub_kernel<true, false, false>), grid, dim3(256), 0, s, M, N,
-                           K, A, lda, B, ldb, C, ldc, (int)tiles_m, (int)tiles_n);
-    else
-        hipLaunchKernelGGL((gemm_f64_sub_kernel<false, false, false>), grid, dim3(256), 0, s, M, N,
-                           K, A, lda, B, ldb, C, ldc, (int)tiles_m, (int)tiles_n);
+    hipLaunchKernelGGL((gemm_f64_sub_kernel<false, false>), grid, dim3(256), 0, s, M, N, K, A, lda, B,
+                       ldb, C, ldc, (int)tiles_m, (int)tiles_n);
     MXLU_LAUNCH_CHECK();
     return 0;
 }
@@ -366,10 +372,10 @@ int gemm_f64_nt_sub(int64_t M, int64_t N, int64_t K, const double *A, int64_t ld
     }
     const dim3 grid((unsigned)(tiles_m * tiles_n));
     if (accumulate)
-        hipLaunchKernelGGL((gemm_f64_sub_kernel<false, true, false>), grid, dim3(256), 0, s, M, N,
+        hipLaunchKernelGGL((gemm_f64_sub_kernel<true, false>), grid, dim3(256), 0, s, M, N,
                            K, A, lda, B, ldb, C, ldc, (int)tiles_m, (int)tiles_n);
     else
-        hipLaunchKernelGGL((gemm_f64_sub_kernel<false, true, true>), grid, dim3(256), 0, s, M, N,
+        hipLaunchKernelGGL((gemm_f64_sub_kernel<true, true>), grid, dim3(256), 0, s, M, N,
                            K, A, lda, B, ldb, C, ldc, (int)tiles_m, (int)tiles_n);
     MXLU_LAUNCH_CHECK();
     return 0;

@@ -11,11 +11,8 @@
 namespace mxlu {
 
 // C(M x N) -= A(M x K) * B(K x N), FP64, column-major.
-// `trailing` marks the DGEMM phase of the factorization (its own kernel
-// instance, so that profiles separate it from the updates inside the panel).
 int gemm_f64_sub(int64_t M, int64_t N, int64_t K, const double *A, int64_t lda,
-                 const double *B, int64_t ldb, double *C, int64_t ldc, hipStream_t s,
-                 bool trailing = false);
+                 const double *B, int64_t ldb, double *C, int64_t ldc, hipStream_t s);
 // C(M x N) = (accumulate ? C : 0) - A(M x K) * B(N x K)^T.
 // The trailing update A22 -= L21 U12 of the factorization with the
 // register-direct kernel: full 128 x 128 tiles, K % 16 == 0, lda even and A

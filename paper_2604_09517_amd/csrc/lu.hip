@@ -373,7 +373,7 @@ int factor_impl(int64_t n, int64_t nb, double *A, int64_t lda, int32_t *ipiv, hi
                                        lda, s));
             else
                 MXLU_TRY(gemm_f64_sub(nt, nt, kb, L21, lda, U12, lda, &MXLU_AT(A, c1, c1, lda),
-                                      lda, s, true));
+                                      lda, s));
             continue;
         }
         // Look-ahead: update the next panel's columns first, then factor that
@@ -642,7 +642,7 @@ extern "C" int mxlu_schur_update_f64(int64_t M, int64_t N, int64_t K, const doub
     if (M == 0 || N == 0 || K == 0) return 0;
     if (int rc = check_device()) return rc;
     clear_error();
-    return gemm_f64_sub(M, N, K, A, lda, B, ldb, C, ldc, (hipStream_t)stream, true);
+    return gemm_f64_sub(M, N, K, A, lda, B, ldb, C, ldc, (hipStream_t)stream);
 }
 
 extern "C" int mxlu_outer_update_f64(int64_t M, int64_t N, int64_t K, const double *A,

@@ -640,7 +640,7 @@ int mxp_impl(int64_t n, int64_t nrhs, const ASource &src, const double *B, int64
     // Splits of the columns in a residual product (a thread per row or two):
     // enough for about 1024 workgroups of 512 rows, 32 columns each at least,
     // 32 for the tallest.  One split per 2048 rows left n = 1000 on two
-    // workgroups (50 us a product, now 6) and n = 3001 on twelve (257 us,
+    // workgroups (50 us a product, now 4) and n = 3001 on twelve (257 us,
     // now 13).  The transposed product has a wave per column: splits only
     // where a column is long.
     c.nsplit = (int)std::max<int64_t>(
