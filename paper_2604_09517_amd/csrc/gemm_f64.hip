@@ -187,14 +187,19 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_sub_kernel(
 // negation and a fragment of 2 adjacent columns is one 16-byte load.
 //
 // A 16-byte load gives a lane two adjacent rows of A (or columns of Bn), so
-// the MFMA row index i' of fragment pair p, half h stands for tile row
-// 32 p + 2 i' + h of the wave's 64 (columns likewise): lane (li, lq) loads
-// A rows wm*64 + 32p + 2li + {0, 1} and Bn columns wn*64 + 32p + 2li + {0, 1}
-// at k = 4 kc + lq.  MFMA (a, b) with a = 2 pa + ha, b = 2 pb + hb leaves in
-// accumulator register r of lane (li, lq) the element at tile row
-// wm*64 + 32 pa + 2 (lq + 4 r) + ha and tile column wn*64 + 32 pb + 2 li + hb,
-// so C moves as 16-byte pairs of rows too.  Every element still takes its
-// k terms in ascending groups of 4, starting from C, as in the LDS kernel.
+// the index i' of fragment pair p, half h stands for tile row 32 p + 2 i' + h
+// of the wave's 64 (columns likewise): lane (li, lq) loads A rows wm*64 + 32p +
+// 2li + {0, 1} and Bn columns wn*64 + 32p + 2li + {0, 1} at k = 4 kc + lq.  The
+// product is formed transposed: MFMA (b, a) with a = 2 pa + ha, b = 2 pb + hb
+// leaves in accumulator register r of lane (li, lq) the element at tile row
+// wm*64 + 32 pa + 2 li + ha and tile column wn*64 + 32 pb + 2 (lq + 4 r) + hb,
+// so that C moves as 16-byte pairs of rows, 256 bytes of a column at a time.
+// Every element still takes its k terms in ascending groups of 4, starting
+// from C, as in the LDS kernel.
+// Bound by the matrix cores, and by C, whose loads and stores hardly overlap
+// with them (all tiles of a round start together): n = 32768, K = 256: 60.5
+// TFLOP/s with C by 64-byte pieces of a column, 64 by 256 bytes, 65.5 with C
+// also past the caches, which keep the panels (a large library product: 73).
 constexpr int kDirectSets = 4, kDirectK = 4 * kDirectSets;
 typedef double v2d __attribute__((ext_vector_type(2)));
 
@@ -209,19 +214,20 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_direct_kernel(
     const int lane = threadIdx.x & 63;
     const int li = lane & 15, lq = lane >> 4;
 
-    v4d acc[4][4];
+    // C columns 32 (b / 2) + 2 (lq + 4 r) + b % 2, rows 32 pa + 2 li + {0, 1}
+    double *Cb = &MXLU_AT(C, row0 + 2 * li, col0 + 2 * lq, ldc);
+    v4d acc[4][4];   // [b][a]
 #pragma unroll
-    for (int pa = 0; pa < 2; ++pa)
+    for (int b = 0; b < 4; ++b)
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const int64_t c = col0 + 32 * (b >> 1) + 2 * li + (b & 1);
+        for (int r = 0; r < 4; ++r)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const v2d v = *(const v2d *)&MXLU_AT(C, row0 + 32 * pa + 2 * (lq + 4 * r), c, ldc);
-                acc[2 * pa][b][r] = v.x;
-                acc[2 * pa + 1][b][r] = v.y;
+            for (int pa = 0; pa < 2; ++pa) {
+                const v2d v = __builtin_nontemporal_load(
+                    (const v2d *)&MXLU_AT(Cb, 32 * pa, 32 * (b >> 1) + 8 * r + (b & 1), ldc));
+                acc[b][2 * pa][r] = v.x;
+                acc[b][2 * pa + 1][r] = v.y;
             }
-        }
 
     const double *Ab = &MXLU_AT(A, row0 + 2 * li, lq, lda);
     const double *Bb = Bn + (size_t)lq * ldbn + col0 + 2 * li;
@@ -249,29 +255,27 @@ __global__ __launch_bounds__(256, 2) void gemm_f64_direct_kernel(
             load(kt0 + u + D - 1, fa[(u + D - 1) % D], fb[(u + D - 1) % D]);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int a = 0; a < 4; ++a)
+            for (int b = 0; b < 4; ++b)
 #pragma unroll
-                for (int b = 0; b < 4; ++b) {
+                for (int a = 0; a < 4; ++a) {
                     const double av = (a & 1) ? fa[u][a >> 1].y : fa[u][a >> 1].x;
                     const double bv = (b & 1) ? fb[u][b >> 1].y : fb[u][b >> 1].x;
-                    acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc[a][b], 0, 0, 0);
+                    acc[b][a] = __builtin_amdgcn_mfma_f64_16x16x4f64(bv, av, acc[b][a], 0, 0, 0);
                 }
         }
     }
 
 #pragma unroll
-    for (int pa = 0; pa < 2; ++pa)
+    for (int b = 0; b < 4; ++b)
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const int64_t c = col0 + 32 * (b >> 1) + 2 * li + (b & 1);
+        for (int r = 0; r < 4; ++r)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) {
+            for (int pa = 0; pa < 2; ++pa) {
                 v2d v;
-                v.x = acc[2 * pa][b][r];
-                v.y = acc[2 * pa + 1][b][r];
-                *(v2d *)&MXLU_AT(C, row0 + 32 * pa + 2 * (lq + 4 * r), c, ldc) = v;
+                v.x = acc[b][2 * pa][r];
+                v.y = acc[b][2 * pa + 1][r];
+                __builtin_nontemporal_store(v, (v2d *)&MXLU_AT(Cb, 32 * pa, 32 * (b >> 1) + 8 * r + (b & 1), ldc));
             }
-        }
 }
 
 // Bn[k][j] = -B[k][j] (B column-major K x N, Bn row-major with ldbn), through
