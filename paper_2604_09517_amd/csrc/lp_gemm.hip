@@ -74,10 +74,13 @@ __device__ __forceinline__ v4f mfma16(uint4 a, uint4 b, v4f c) {
 // stages with 16-byte direct global->LDS loads (no register staging): each
 // wave issues 4 + 2 loads of 1 KB per chunk, so up to kNs16 - 1 chunks are in
 // flight while the matrix cores work on the current one, and one workgroup
-// barrier per chunk orders the ring.  A is negated when read from LDS.  The
-// A rows of each pair of MFMA blocks are interleaved so that a lane's
-// accumulators cover 8 consecutive rows of a column: C is read and written
-// 16 bytes per lane.
+// barrier per chunk orders the ring.  U12 is negated when read from LDS.  The
+// product is formed transposed and the rows of eight MFMA blocks are
+// interleaved, so that a lane's accumulators cover 8 consecutive rows of a
+// column and 16 lanes 128: C, which hardly overlaps with the matrix cores'
+// work, moves 256 bytes of a column at a time.  N = 65536, NB = 512, all
+// updates: 333 ms with C by 64-byte pieces of 16 columns, 304 by 256 bytes, 276
+// with C also past the caches (681 TFLOP/s; C alone takes 168 ms at 4.3 TB/s).
 constexpr int BK16 = kLpKc;
 constexpr int kNs16 = 3;
 static_assert(TM == kLpTileM && TN == kLpTileN, "tile and packing must agree");
@@ -87,26 +90,26 @@ typedef __attribute__((address_space(3))) void lvoid_t;
 typedef int v4i __attribute__((ext_vector_type(4)));
 typedef unsigned v4u __attribute__((ext_vector_type(4)));
 
-// 16 bytes of the C tile, optionally as streaming (non-temporal) accesses:
-// each C element is touched once per update, and keeping it out of the caches
-// leaves them to the operand panels that every tile of a tile row or column
-// reads again.  Measured: the FP8 update gains with both (11.1 -> 9.5-9.9 ms
-// per launch at N = 131072, NB = 1024; loads or stores alone are slower than
-// neither), the 16-bit update loses with any (2.29 -> 2.34-2.43 ms at
-// N = 65536, NB = 512), so it keeps ordinary accesses.
-template <bool NT>
-__device__ __forceinline__ uint4 c_load(const uint16_t *p) {
-    if constexpr (!NT) return *reinterpret_cast<const uint4 *>(p);
+// 16 or 8 bytes of the C tile as streaming (non-temporal) accesses: each C
+// element is touched once per update, and keeping it out of the caches leaves
+// them to the operand panels that every tile of a tile row or column reads
+// again.  BF16 at N = 65536, NB = 512, all updates: 304 -> 276 ms; the FP8
+// update gains with both loads and stores (11.1 -> 9.5-9.9 ms per launch at N =
+// 131072, NB = 1024; either alone is slower than neither).
+typedef unsigned v2u __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint4 c_load(const uint16_t *p, uint4) {
     const v4u v = __builtin_nontemporal_load(reinterpret_cast<const v4u *>(p));
     return make_uint4(v.x, v.y, v.z, v.w);
 }
-template <bool NT>
+__device__ __forceinline__ uint2 c_load(const uint16_t *p, uint2) {
+    const v2u v = __builtin_nontemporal_load(reinterpret_cast<const v2u *>(p));
+    return make_uint2(v.x, v.y);
+}
 __device__ __forceinline__ void c_store(uint16_t *p, uint4 v) {
-    if constexpr (!NT) {
-        *reinterpret_cast<uint4 *>(p) = v;
-        return;
-    }
     __builtin_nontemporal_store(v4u{v.x, v.y, v.z, v.w}, reinterpret_cast<v4u *>(p));
+}
+__device__ __forceinline__ void c_store(uint16_t *p, uint2 v) {
+    __builtin_nontemporal_store(v2u{v.x, v.y}, reinterpret_cast<v2u *>(p));
 }
 
 // LDS byte address of a pointer into a __shared__ array
@@ -195,7 +198,7 @@ __device__ __forceinline__ uint4 neg16(uint4 v) {   // flip the sign bit of 8 16
     return v;
 }
 
-template <int FMT, bool NTL = false, bool NTS = false>
+template <int FMT>
 __global__ __launch_bounds__(256, 2) void lp_schur16_kernel(
     int64_t M, int64_t N, int K, const uint16_t *__restrict__ Lp, int64_t Mp,
     const uint16_t *__restrict__ Up, int64_t Np, uint16_t *__restrict__ C, int64_t ldc,
@@ -210,54 +213,49 @@ __global__ __launch_bounds__(256, 2) void lp_schur16_kernel(
     const int wm = wave & 1, wn = wave >> 1;
     const int li = lane & 15, lg = lane >> 4;
 
-    // Row mapping: the A operand of MFMA block bi = 2p + h supplies, in lane
-    // li, tile row 32p + 2 li + h, so accumulator register r of lane (li, lg)
-    // of blocks 2p and 2p + 1 holds the 8 consecutive rows 32p + 8 lg + 2r + h
-    // of column c: C moves 16 bytes per lane (rows row8 .. row8 + 7).
+    // Row mapping: the product is formed transposed, block bi of L21 supplying
+    // in lane li tile row 8 li + bi of the wave's 128, so accumulator register
+    // r of lane (li, lg) of the eight blocks holds the 8 consecutive rows 8 li
+    // .. 8 li + 7 of column 16 bj + 4 lg + r: C moves 16 bytes per lane, 256
+    // bytes of a column at a time.
     // Interior tiles with 16-byte aligned columns (uniform branch) issue all
     // their loads back to back without checks.
     const bool full = row0 + TM <= M && col0 + TN <= N && (ldc & 7) == 0 &&
                       ((uintptr_t)C & 15) == 0;
-    auto row_of = [&](int bi, int r) -> int64_t {
-        return row0 + wm * 128 + 32 * (bi >> 1) + 2 * (4 * lg + r) + (bi & 1);
-    };
+    const int64_t r8 = row0 + wm * 128 + 8 * li, cl = col0 + wn * 64 + 4 * lg;
     v4f acc[8][4];
     if (full) {
 #pragma unroll
-        for (int pr = 0; pr < 4; ++pr)
+        for (int bj = 0; bj < 4; ++bj)
 #pragma unroll
-            for (int bj = 0; bj < 4; ++bj) {
-                const int64_t r8 = row0 + wm * 128 + 32 * pr + 8 * lg;
-                const int64_t c = col0 + wn * 64 + bj * 16 + li;
-                const uint4 v = c_load<NTL>(&C[(size_t)r8 + (size_t)c * ldc]);
+            for (int r = 0; r < 4; ++r) {
+                const uint4 v = c_load(&C[(size_t)r8 + (size_t)(cl + 16 * bj + r) * ldc], uint4{});
                 const uint32_t w4[4] = {v.x, v.y, v.z, v.w};
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    acc[2 * pr][bj][r] = lp_to_f32<FMT>((uint16_t)w4[r]);
-                    acc[2 * pr + 1][bj][r] = lp_to_f32<FMT>((uint16_t)(w4[r] >> 16));
+                for (int h = 0; h < 4; ++h) {
+                    acc[2 * h][bj][r] = lp_to_f32<FMT>((uint16_t)w4[h]);
+                    acc[2 * h + 1][bj][r] = lp_to_f32<FMT>((uint16_t)(w4[h] >> 16));
                 }
             }
     } else {
 #pragma unroll
         for (int bi = 0; bi < 8; ++bi)
 #pragma unroll
-            for (int bj = 0; bj < 4; ++bj) {
-                const int64_t c = col0 + wn * 64 + bj * 16 + li;
+            for (int bj = 0; bj < 4; ++bj)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const int64_t row = row_of(bi, r);
+                    const int64_t row = r8 + bi, c = cl + 16 * bj + r;
                     acc[bi][bj][r] = (row < M && c < N)
                                          ? lp_to_f32<FMT>(C[(size_t)row + (size_t)c * ldc])
                                          : 0.0f;
                 }
-            }
     }
 
     // LDS layout of a stage: 64-byte lines (one row of L21 or column of U12
     // over the chunk's 32 k), four 16-byte segments.  The 16 lanes li of a
     // lane group read one segment of 16 lines at once (one pass of a 16-byte
-    // LDS read), so (1) the A rows 32p + 2 li + h of one MFMA block sit in the
-    // consecutive lines 32p + 16h + li, and (2) segment s of line x is stored
+    // LDS read), so (1) the rows 8 li + bi of one block sit in the
+    // consecutive lines 16 bi + li, and (2) segment s of line x is stored
     // in slot s ^ sw(x), sw(x) = ((x >> 1) & 3) ^ ((x >> 3) & 1): the 16 lanes
     // of a pass touch 16 distinct 16-byte bank groups of 256 bytes (8 in each
     // half).  Wave w copies lines [64 w, 64 w + 64) of L21 and [32 w, 32 w +
@@ -269,7 +267,7 @@ __global__ __launch_bounds__(256, 2) void lp_schur16_kernel(
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
         const int x = wave * 64 + 16 * q + t4;
-        const int r = 32 * (x >> 5) + 2 * (x & 15) + ((x >> 4) & 1);
+        const int r = (x & ~127) + 8 * (x & 15) + ((x >> 4) & 7);
         offA[q] = r * (BK16 * 2) + 16 * (s4 ^ sw(x));
     }
 #pragma unroll
@@ -317,40 +315,37 @@ __global__ __launch_bounds__(256, 2) void lp_schur16_kernel(
         lds_frags16(lds_addr(&as[(wm * 128 + li) * BK16 + so]),
                     lds_addr(&bs[(wn * 64 + li) * BK16 + so]), a, b);
 #pragma unroll
-        for (int bi = 0; bi < 8; ++bi) a[bi] = neg16(a[bi]);
+        for (int bj = 0; bj < 4; ++bj) b[bj] = neg16(b[bj]);
 #pragma unroll
         for (int bi = 0; bi < 8; ++bi)
 #pragma unroll
-            for (int bj = 0; bj < 4; ++bj) acc[bi][bj] = mfma16<FMT>(a[bi], b[bj], acc[bi][bj]);
+            for (int bj = 0; bj < 4; ++bj) acc[bi][bj] = mfma16<FMT>(b[bj], a[bi], acc[bi][bj]);
     }
 
     if (full) {
 #pragma unroll
-        for (int pr = 0; pr < 4; ++pr)
+        for (int bj = 0; bj < 4; ++bj)
 #pragma unroll
-            for (int bj = 0; bj < 4; ++bj) {
-                const int64_t r8 = row0 + wm * 128 + 32 * pr + 8 * lg;
-                const int64_t c = col0 + wn * 64 + bj * 16 + li;
+            for (int r = 0; r < 4; ++r) {
                 uint32_t w4[4];
 #pragma unroll
-                for (int r = 0; r < 4; ++r)
-                    w4[r] = (uint32_t)f32_to_lp<FMT>(acc[2 * pr][bj][r]) |
-                            ((uint32_t)f32_to_lp<FMT>(acc[2 * pr + 1][bj][r]) << 16);
-                c_store<NTS>(&C[(size_t)r8 + (size_t)c * ldc], make_uint4(w4[0], w4[1], w4[2], w4[3]));
+                for (int h = 0; h < 4; ++h)
+                    w4[h] = (uint32_t)f32_to_lp<FMT>(acc[2 * h][bj][r]) |
+                            ((uint32_t)f32_to_lp<FMT>(acc[2 * h + 1][bj][r]) << 16);
+                c_store(&C[(size_t)r8 + (size_t)(cl + 16 * bj + r) * ldc],
+                             make_uint4(w4[0], w4[1], w4[2], w4[3]));
             }
     } else {
 #pragma unroll
         for (int bi = 0; bi < 8; ++bi)
 #pragma unroll
-            for (int bj = 0; bj < 4; ++bj) {
-                const int64_t c = col0 + wn * 64 + bj * 16 + li;
+            for (int bj = 0; bj < 4; ++bj)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const int64_t row = row_of(bi, r);
+                    const int64_t row = r8 + bi, c = cl + 16 * bj + r;
                     if (row < M && c < N)
                         C[(size_t)row + (size_t)c * ldc] = f32_to_lp<FMT>(acc[bi][bj][r]);
                 }
-            }
     }
 }
 
@@ -361,8 +356,9 @@ __global__ __launch_bounds__(256, 2) void lp_schur16_kernel(
 // 16-byte direct global->LDS loads (8 loads of 1 KB per wave and chunk).
 // The accumulators start at zero and take +Lq Uq; the epilogue forms
 // C - acc sL sU (the scalings exact: powers of two), the order of the
-// definition; C is read and written 16 bytes (8 rows) per lane, the A rows of
-// each pair of MFMA blocks being interleaved as in the 16-bit form.
+// definition; C moves 8 bytes (4 rows) per lane, 128 of a column at a time, the
+// rows of the four MFMA blocks being interleaved as in the 16-bit form (N =
+// 98304, NB = 1024, all updates: 717 ms by 64-byte pieces, now 632).
 constexpr int kTm8 = 128, kTn8 = 128;
 constexpr int BK8 = kLp8Kc;
 static_assert(kTm8 == kLp8Tile && kTn8 == kLp8Tile, "tile and packing must agree");
@@ -381,7 +377,7 @@ __device__ __forceinline__ void wait_vmcnt() {
 // row (column), the operand bytes being placed so that the matrix cores' k
 // is the chunk's k (bytes 0-15 of a lane from k 16 lg, bytes 16-31 from
 // k 64 + 16 lg); the epilogue is then C - acc.
-template <int FMT, int NS, bool MX, bool NTL = true, bool NTS = true>
+template <int FMT, int NS, bool MX>
 __global__ __launch_bounds__(256, NS <= 2 ? 2 : 1) void lp_schur8_kernel(
     int64_t M, int64_t N, int K, const uint8_t *__restrict__ Lq, int64_t Mp,
     const float *__restrict__ sL, const uint8_t *__restrict__ Uq, int64_t Np,
@@ -407,31 +403,30 @@ __global__ __launch_bounds__(256, NS <= 2 ? 2 : 1) void lp_schur8_kernel(
     const int wm = wave & 1, wn = wave >> 1;
     const int li = lane & 15, lg = lane >> 4;
 
-    // Rows as in the 16-bit form: the A operand of MFMA block bi = 2p + h
-    // supplies tile row 32p + 2 li + h in lane li, so a lane's accumulators of
-    // blocks 2p, 2p + 1 cover 8 consecutive rows of one column (16 bytes of C;
-    // rows 0-3 and 4-7 each share a scale tile, tiles being multiples of 4).
+    // Transposed as in the 16-bit form: block bi of L21 supplies row 4 li + bi
+    // of the wave's 64 in lane li, so a lane's accumulators of the four blocks
+    // are 4 consecutive rows of column 16 bj + 4 lg + r: 8 bytes of C per
+    // lane, 128 of a column at a time.  The four rows share a scale tile, and
+    // so do the columns of the four r, tiles being multiples of 4.
     // The accumulators start at zero and the epilogue forms C - acc sL sU (the
     // scalings are exact: powers of two), so the C tile is needed only at the
     // end: interior tiles with 16-byte aligned columns (uniform branch) load it
     // just before the first operand chunks, and its latency overlaps theirs.
     const bool full = row0 + kTm8 <= M && col0 + kTn8 <= N && (ldc & 7) == 0 &&
                       ((uintptr_t)C & 15) == 0;
-    auto row_of = [&](int bi, int r) -> int64_t {
-        return row0 + wm * 64 + 32 * (bi >> 1) + 2 * (4 * lg + r) + (bi & 1);
-    };
+    const int64_t r4 = row0 + wm * 64 + 4 * li, cl = col0 + wn * 64 + 4 * lg;
     v4f acc[4][4];
 #pragma unroll
     for (int bi = 0; bi < 4; ++bi)
 #pragma unroll
         for (int bj = 0; bj < 4; ++bj) acc[bi][bj] = v4f{0.0f, 0.0f, 0.0f, 0.0f};
-    uint4 cv[2][4];
+    uint2 cv[4][4];   // [bj][r]
 
     // LDS layout of a stage: 128-byte lines (one row of L21 or column of U12
     // over the chunk's 128 k), 16-byte segments.  A row is read by the 16
     // lanes li of a lane group at once (one pass of a 16-byte LDS read), so
-    // (1) the A rows 32p + 2 li + h that one MFMA block takes sit in 16
-    // consecutive lines, line 32p + 16h + li, and (2) segment s of line x is
+    // (1) the rows 4 li + bi that one block takes sit in 16 consecutive
+    // lines, 16 bi + li, and (2) segment s of line x is
     // stored in slot s ^ sw(x), sw(x) = (x & 7) ^ ((x >> 3) & 1): the 16 lanes
     // of a pass then touch 16 distinct 16-byte bank groups of the 256 bytes
     // the LDS serves per cycle (and 8 distinct ones in each half).  The
@@ -444,7 +439,7 @@ __global__ __launch_bounds__(256, NS <= 2 ? 2 : 1) void lp_schur8_kernel(
 #pragma unroll
     for (int q = 0; q < NA; ++q) {
         const int x = wave * (SA / 4 / BK8) + 8 * q + t8;            // LDS line
-        const int r = 32 * (x >> 5) + 2 * (x & 15) + ((x >> 4) & 1);   // tile row
+        const int r = (x & ~63) + 4 * (x & 15) + ((x >> 4) & 3);     // tile row
         offA[q] = r * BK8 + 16 * (s8 ^ sw(x));
     }
 #pragma unroll
@@ -479,13 +474,10 @@ __global__ __launch_bounds__(256, NS <= 2 ? 2 : 1) void lp_schur8_kernel(
     // operand chunks issued after the one they wait for
     if (full) {
 #pragma unroll
-        for (int pr = 0; pr < 2; ++pr)
+        for (int bj = 0; bj < 4; ++bj)
 #pragma unroll
-            for (int bj = 0; bj < 4; ++bj) {
-                const int64_t r8 = row0 + wm * 64 + 32 * pr + 8 * lg;
-                const int64_t c = col0 + wn * 64 + bj * 16 + li;
-                cv[pr][bj] = c_load<NTL>(&C[(size_t)r8 + (size_t)c * ldc]);
-            }
+            for (int r = 0; r < 4; ++r)
+                cv[bj][r] = c_load(&C[(size_t)r4 + (size_t)(cl + 16 * bj + r) * ldc], uint2{});
     }
 #pragma unroll
     for (int c = 0; c < kNs8 - 1; ++c)
@@ -498,7 +490,7 @@ __global__ __launch_bounds__(256, NS <= 2 ? 2 : 1) void lp_schur8_kernel(
         const size_t blk = (size_t)(4 * kc + lg);
 #pragma unroll
         for (int bi = 0; bi < 4; ++bi)
-            a4[bi] = sLx[blk * Mp + (size_t)(row0 + wm * 64 + 32 * (bi >> 1) + 2 * li + (bi & 1))];
+            a4[bi] = sLx[blk * Mp + (size_t)(r4 + bi)];
 #pragma unroll
         for (int bj = 0; bj < 4; ++bj)
             b4[bj] = sUx[blk * Np + (size_t)(col0 + wn * 64 + bj * 16 + li)];
@@ -527,7 +519,7 @@ __global__ __launch_bounds__(256, NS <= 2 ? 2 : 1) void lp_schur8_kernel(
 #pragma unroll
             for (int bj = 0; bj < 4; ++bj)
                 acc[bi][bj] = __builtin_amdgcn_mfma_scale_f32_16x16x128_f8f6f4(
-                    a[bi], b[bj], acc[bi][bj], 0, 0, 0, sa[bi], 0, sb[bj]);
+                    b[bj], a[bi], acc[bi][bj], 0, 0, 0, sb[bj], 0, sa[bi]);
         if constexpr (MX)
             if (kt + 1 < nk)
 #pragma unroll
@@ -538,47 +530,38 @@ __global__ __launch_bounds__(256, NS <= 2 ? 2 : 1) void lp_schur8_kernel(
     }
 
     // C <- round(fp32(C) - acc sL sU)   (MX: C - acc)
-    if (full) {
 #pragma unroll
-        for (int pr = 0; pr < 2; ++pr)
+    for (int bj = 0; bj < 4; ++bj) {
+        if (full) {
+            float sc = 1.0f;
+            if constexpr (!MX) sc = sL[tix(r4)] * sU[tix(cl + 16 * bj)];
 #pragma unroll
-            for (int bj = 0; bj < 4; ++bj) {
-                const int64_t r8 = row0 + wm * 64 + 32 * pr + 8 * lg;
-                const int64_t c = col0 + wn * 64 + bj * 16 + li;
-                float sc_lo = 1.0f, sc_hi = 1.0f;
-                if constexpr (!MX) {
-                    const float su = sU[tix(c)];
-                    sc_lo = sL[tix(r8)] * su;
-                    sc_hi = sL[tix(r8 + 4)] * su;
-                }
-                const uint32_t c4[4] = {cv[pr][bj].x, cv[pr][bj].y, cv[pr][bj].z, cv[pr][bj].w};
-                uint32_t w4[4];
+            for (int r = 0; r < 4; ++r) {
+                const uint32_t c2[2] = {cv[bj][r].x, cv[bj][r].y};
+                uint32_t w2[2];
 #pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const float sc = r < 2 ? sc_lo : sc_hi;
-                    const float lo = lp_to_f32<FMT>((uint16_t)c4[r]) - acc[2 * pr][bj][r] * sc;
+                for (int h = 0; h < 2; ++h) {
+                    const float lo = lp_to_f32<FMT>((uint16_t)c2[h]) - acc[2 * h][bj][r] * sc;
                     const float hi =
-                        lp_to_f32<FMT>((uint16_t)(c4[r] >> 16)) - acc[2 * pr + 1][bj][r] * sc;
-                    w4[r] = (uint32_t)f32_to_lp<FMT>(lo) | ((uint32_t)f32_to_lp<FMT>(hi) << 16);
+                        lp_to_f32<FMT>((uint16_t)(c2[h] >> 16)) - acc[2 * h + 1][bj][r] * sc;
+                    w2[h] = (uint32_t)f32_to_lp<FMT>(lo) | ((uint32_t)f32_to_lp<FMT>(hi) << 16);
                 }
-                c_store<NTS>(&C[(size_t)r8 + (size_t)c * ldc], make_uint4(w4[0], w4[1], w4[2], w4[3]));
+                c_store(&C[(size_t)r4 + (size_t)(cl + 16 * bj + r) * ldc], make_uint2(w2[0], w2[1]));
             }
-    } else {
+        } else {
 #pragma unroll
-        for (int bi = 0; bi < 4; ++bi)
-#pragma unroll
-            for (int bj = 0; bj < 4; ++bj) {
-                const int64_t c = col0 + wn * 64 + bj * 16 + li;
+            for (int bi = 0; bi < 4; ++bi)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const int64_t row = row_of(bi, r);
+                    const int64_t row = r4 + bi, c = cl + 16 * bj + r;
                     if (row < M && c < N) {
-                        uint16_t *cp = &C[(size_t)row + (size_t)c * ldc];
-                        const float sc = MX ? 1.0f : sL[tix(row)] * sU[tix(c)];
-                        *cp = f32_to_lp<FMT>(lp_to_f32<FMT>(*cp) - acc[bi][bj][r] * sc);
+                        float sc = 1.0f;
+                        if constexpr (!MX) sc = sL[tix(row)] * sU[tix(c)];
+                        const size_t at = (size_t)row + (size_t)c * ldc;
+                        C[at] = f32_to_lp<FMT>(lp_to_f32<FMT>(C[at]) - acc[bi][bj][r] * sc);
                     }
                 }
-            }
+        }
     }
 }
 
