@@ -383,17 +383,25 @@ struct RefineCtx {
     // device scratch
     double *r, *z, *w, *V, *part, *apart, *dotp, *hdev;
     float *v32;
-    unsigned long long *stats;   // [0] |r|max [1] ||A|| [2] |x|max [3] precond s
+    // [0] |r|max [1] ||A|| [2] |x|max; [3], [4] in turn: the scale (max |r|) of
+    // the next preconditioner, left there by the kernel that forms its input;
+    // each preconditioner clears the other
+    unsigned long long *stats;
+    int turn = 0;
+    unsigned long long *scale() { return stats + 3 + turn; }
     TrsvChain ch{};
     int nsplit, nchunks;
     double anorm = -1.0;
 };
 
+// d = M r, max |r| being in c.scale()
 int precond(RefineCtx &c, const double *r, double *d) {
+    const unsigned long long *smax = c.scale();
+    c.turn ^= 1;
     if (c.F32)
-        return lp_precond_apply_f32(c.n, c.F32, c.ldf, c.perm, r, d, c.v32, c.stats + 3, c.s);
-    return lp_precond_apply(c.fmt, c.trans, c.n, c.F, c.ldf, c.perm, r, d, c.v32, c.stats + 3,
-                            c.ch, c.s);
+        return lp_precond_apply_f32(c.n, c.F32, c.ldf, c.perm, r, d, c.v32, smax, c.scale(), c.s);
+    return lp_precond_apply(c.fmt, c.trans, c.n, c.F, c.ldf, c.perm, r, d, c.v32, smax, c.scale(), c.ch,
+                            c.s);
 }
 
 // r = b - op(A) x; returns the scaled residual (host sync).
@@ -401,7 +409,7 @@ int residual(RefineCtx &c, const double *b, const double *x, double bnorm, doubl
     MXLU_HIP_TRY(hipMemsetAsync(c.stats, 0, 3 * sizeof(unsigned long long), c.s));
     const bool need_anorm = c.anorm < 0.0;
     MXLU_TRY(gemv_f64(c.trans, c.n, c.src, x, b, c.r, c.part, need_anorm ? c.apart : nullptr,
-                      c.nsplit, c.stats, c.s));
+                      c.nsplit, c.stats, c.scale(), c.s));
     unsigned long long h[3];
     MXLU_HIP_TRY(hipMemcpyAsync(h, c.stats, sizeof(h), hipMemcpyDeviceToHost, c.s));
     MXLU_HIP_TRY(hipStreamSynchronize(c.s));
@@ -423,35 +431,44 @@ int gmres_cycle(RefineCtx &c, double *x, int mmax, int *steps) {
     *steps = 0;
     // z = M r; beta = ||z||
     MXLU_TRY(precond(c, c.r, c.z));
-    MXLU_TRY(dots_f64(n, 1, c.z, ldv, c.z, c.dotp, c.nchunks, c.hdev, c.s));
+    const bool small = arnoldi_small_ok(n, c.nchunks, mmax);
+    if (small)   // also forms the first column
+        MXLU_TRY(arnoldi_small_f64(n, 0, c.V, ldv, c.z, nullptr, nullptr, c.hdev, c.V, c.s));
+    else
+        MXLU_TRY(dots_f64(n, 1, c.z, ldv, c.z, c.dotp, c.nchunks, c.hdev, c.s));
     double beta2 = 0.0;
     MXLU_HIP_TRY(hipMemcpyAsync(&beta2, c.hdev, sizeof(double), hipMemcpyDeviceToHost, c.s));
     MXLU_HIP_TRY(hipStreamSynchronize(c.s));
     const double beta = std::sqrt(beta2);
     if (!(beta > 0.0)) return 0;
-    MXLU_TRY(scale_copy_f64(n, c.z, 1.0 / beta, c.V, c.s));
+    if (!small) MXLU_TRY(scale_copy_f64(n, c.z, 1.0 / beta, c.V, c.s));
     g[0] = beta;
     int k = 0;
     for (int j = 0; j < mmax; ++j) {
         double *vj = c.V + (size_t)j * ldv;
         // w = op(A) v_j ; z = M w
         MXLU_TRY(gemv_f64(c.trans, n, c.src, vj, nullptr, c.w, c.part, nullptr, c.nsplit,
-                          nullptr, c.s));
+                          nullptr, c.scale(), c.s));
         MXLU_TRY(precond(c, c.w, c.z));
         // classical Gram-Schmidt, twice
         double *h1 = c.hdev, *h2 = c.hdev + (mmax + 1), *hn = c.hdev + 2 * (mmax + 1);
-        MXLU_TRY(dots_f64(n, j + 1, c.V, ldv, c.z, c.dotp, c.nchunks, h1, c.s));
-        MXLU_TRY(gemv_small_f64(n, j + 1, c.V, ldv, h1, -1.0, c.z, c.s));
-        MXLU_TRY(dots_f64(n, j + 1, c.V, ldv, c.z, c.dotp, c.nchunks, h2, c.s));
-        MXLU_TRY(gemv_small_f64(n, j + 1, c.V, ldv, h2, -1.0, c.z, c.s));
-        MXLU_TRY(dots_f64(n, 1, c.z, ldv, c.z, c.dotp, c.nchunks, hn, c.s));
+        if (small) {
+            MXLU_TRY(arnoldi_small_f64(n, j + 1, c.V, ldv, c.z, h1, h2, hn, c.V + (size_t)(j + 1) * ldv,
+                                       c.s));
+        } else {
+            MXLU_TRY(dots_f64(n, j + 1, c.V, ldv, c.z, c.dotp, c.nchunks, h1, c.s));
+            MXLU_TRY(gemv_small_f64(n, j + 1, c.V, ldv, h1, -1.0, c.z, c.s));
+            MXLU_TRY(dots_f64(n, j + 1, c.V, ldv, c.z, c.dotp, c.nchunks, h2, c.s));
+            MXLU_TRY(gemv_small_f64(n, j + 1, c.V, ldv, h2, -1.0, c.z, c.s));
+            MXLU_TRY(dots_f64(n, 1, c.z, ldv, c.z, c.dotp, c.nchunks, hn, c.s));
+        }
         MXLU_HIP_TRY(hipMemcpyAsync(hh.data(), c.hdev, sizeof(double) * (2 * (mmax + 1) + 1),
                                     hipMemcpyDeviceToHost, c.s));
         MXLU_HIP_TRY(hipStreamSynchronize(c.s));
         const double hnorm = std::sqrt(hh[2 * (mmax + 1)]);
         for (int i = 0; i <= j; ++i) H[(size_t)j * (mmax + 1) + i] = hh[i] + hh[(mmax + 1) + i];
         H[(size_t)j * (mmax + 1) + j + 1] = hnorm;
-        if (hnorm > 0.0)
+        if (hnorm > 0.0 && !small)
             MXLU_TRY(scale_copy_f64(n, c.z, 1.0 / hnorm, c.V + (size_t)(j + 1) * ldv, c.s));
         double *col = &H[(size_t)j * (mmax + 1)];
         for (int i = 0; i < j; ++i) {   // previous rotations
@@ -489,13 +506,14 @@ int refine_column(RefineCtx &c, const double *b, double *x, bool x_init, int *co
     const mxp_opts &o = *c.o;
     const int64_t n = c.n;
     unsigned long long hb;
-    MXLU_HIP_TRY(hipMemsetAsync(c.stats, 0, sizeof(unsigned long long), c.s));
-    MXLU_TRY(absmax_f64(n, b, c.stats, c.s));
-    MXLU_HIP_TRY(hipMemcpyAsync(&hb, c.stats, sizeof(hb), hipMemcpyDeviceToHost, c.s));
+    MXLU_HIP_TRY(hipMemsetAsync(c.stats, 0, 5 * sizeof(unsigned long long), c.s));
+    MXLU_TRY(absmax_f64(n, b, c.scale(), c.s));
+    MXLU_HIP_TRY(hipMemcpyAsync(&hb, c.scale(), sizeof(hb), hipMemcpyDeviceToHost, c.s));
     MXLU_HIP_TRY(hipStreamSynchronize(c.s));
     double bnorm;
     std::memcpy(&bnorm, &hb, sizeof(double));
     if (!x_init) MXLU_TRY(precond(c, b, x));
+    else MXLU_HIP_TRY(hipMemsetAsync(c.scale(), 0, sizeof(unsigned long long), c.s));
     std::vector<double> hist;
     int increases = 0, it = 0, inner_total = 0;
     *conv = 0;

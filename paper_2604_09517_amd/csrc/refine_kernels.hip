@@ -204,12 +204,14 @@ __global__ __launch_bounds__(256) void gemv_t_partial_kernel(int64_t n, ASource 
 }
 
 // y[i] = (b ? b[i] - sum_s part : sum_s part); maxima of |y| and of the
-// |A| row sums go to stats[0] and stats[1] (bit patterns), |x| to stats[2].
+// |A| row sums go to stats[0] and stats[1] (bit patterns), |x| to stats[2];
+// that of |y| to ymax as well.
 __global__ void gemv_finish_kernel(int64_t n, int nsplit, const double *__restrict__ part,
                                    const double *__restrict__ asum_part,
                                    const double *__restrict__ b, double *__restrict__ y,
                                    const double *__restrict__ xv,
-                                   unsigned long long *__restrict__ stats) {
+                                   unsigned long long *__restrict__ stats,
+                                   unsigned long long *__restrict__ ymax) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     double m_y = 0.0, m_a = 0.0, m_x = 0.0;
     if (i < n) {
@@ -236,16 +238,19 @@ __global__ void gemv_finish_kernel(int64_t n, int nsplit, const double *__restri
         }
         if (xv) m_x = fabs(xv[i]);
     }
-    if (stats) {
+    if (stats || ymax) {
         for (int off = 32; off > 0; off >>= 1) {
             m_y = fmax(m_y, __shfl_xor(m_y, off));
             m_a = fmax(m_a, __shfl_xor(m_a, off));
             m_x = fmax(m_x, __shfl_xor(m_x, off));
         }
         if ((threadIdx.x & 63) == 0) {
-            atomic_max_abs(&stats[0], m_y);
-            if (asum_part) atomic_max_abs(&stats[1], m_a);
-            if (xv) atomic_max_abs(&stats[2], m_x);
+            if (stats) {
+                atomic_max_abs(&stats[0], m_y);
+                if (asum_part) atomic_max_abs(&stats[1], m_a);
+                if (xv) atomic_max_abs(&stats[2], m_x);
+            }
+            if (ymax) atomic_max_abs(ymax, fmax(0.0, m_y));   // (a NaN alone counts as none)
         }
     }
 }
@@ -295,6 +300,68 @@ __global__ void gemv_small_kernel(int64_t n, int k, const double *__restrict__ V
     z[i] = acc;
 }
 
+// One step of the orthogonalization by a single workgroup, n < 2048 (one chunk
+// of the sums above): classical Gram-Schmidt twice against V's k columns, then
+// the norm and the next column: h1 = V^T z, z -= V h1, h2 = V^T z, z -= V h2,
+// *hn = z^T z, vnext = z / sqrt(*hn); with k = 0 only the last two.  The same
+// sums in the same order as dots_partial_kernel (256 strided partial sums and
+// its tree, four of them per lane) and gemv_small_kernel: eight launches in
+// one.  At n = 1000 those took 3 to 5 us each and about as much between them.
+constexpr int kArnoldiMaxN = 2048;
+
+__global__ __launch_bounds__(1024) void arnoldi_small_kernel(int n, int k, const double *__restrict__ V,
+                                                             int64_t ldv, const double *__restrict__ z,
+                                                             double *__restrict__ h1,
+                                                             double *__restrict__ h2,
+                                                             double *__restrict__ hn,
+                                                             double *__restrict__ vnext) {
+    __shared__ double zs[kArnoldiMaxN];
+    __shared__ double hs[256];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    for (int i = tid; i < n; i += 1024) zs[i] = z[i];
+    __syncthreads();
+    auto dot = [&](const double *x) {   // x^T z in lane 0; every lane of the wave takes part
+        double a[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll 2
+        for (int i0 = 0; i0 < n; i0 += 256)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int i = i0 + 64 * q + lane;
+                if (i < n) a[q] = fma(x[i], zs[i], a[q]);
+            }
+        double s = (a[0] + a[2]) + (a[1] + a[3]);
+        for (int off = 32; off > 0; off >>= 1) s += __shfl_down(s, off);
+        return s;
+    };
+    for (int pass = 0; pass < (k > 0 ? 2 : 0); ++pass) {
+        for (int c = wave; c < k; c += 16) {
+            const double s = dot(V + (size_t)c * ldv);
+            if (lane == 0) {
+                hs[c] = s;
+                (pass ? h2 : h1)[c] = s;
+            }
+        }
+        __syncthreads();
+        for (int i = tid; i < n; i += 1024) {
+            double acc = zs[i];
+#pragma unroll 8
+            for (int c = 0; c < k; ++c) acc = fma(-V[(size_t)i + (size_t)c * ldv], hs[c], acc);
+            zs[i] = acc;
+        }
+        __syncthreads();
+    }
+    if (wave == 0) {
+        const double s = dot(zs);
+        if (lane == 0) {
+            hs[0] = s;
+            *hn = s;
+        }
+    }
+    __syncthreads();
+    const double alpha = 1.0 / sqrt(hs[0]);   // (not finite: the caller stops here)
+    for (int i = tid; i < n; i += 1024) vnext[i] = zs[i] * alpha;
+}
+
 __global__ void scale_copy_kernel(int64_t n, const double *__restrict__ z, double alpha,
                                   double *__restrict__ v) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -317,28 +384,29 @@ __global__ void absmax_kernel(int64_t n, const double *__restrict__ v,
 }
 
 // ---------------------------------------------------------------- precond
+// (FP32 factors; those of 16 bits do both steps in their solves)
 // v32[i] = fp32( r[src(i)] / s ), s = *smax (bits) or 1 when zero;
 // src(i) = perm[i] when perm is given (apply P), else i.
 __global__ void precond_in_kernel(int64_t n, const double *__restrict__ r,
                                   const int32_t *__restrict__ perm,
                                   const unsigned long long *__restrict__ smax,
-                                  float *__restrict__ v32) {
+                                  unsigned long long *smax_next, float *__restrict__ v32) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    if (i == 0) *smax_next = 0;
     if (i >= n) return;
     const double s = bits_to_double(*smax);
     const double ri = r[perm ? perm[i] : i];
     v32[i] = s > 0.0 ? (float)(ri / s) : 0.0f;
 }
 
-// d[dst(i)] = s * fp64(v32[i]); dst(i) = perm[i] when given (apply P^T).
+// d[i] = s * fp64(v32[i])
 __global__ void precond_out_kernel(int64_t n, const float *__restrict__ v32,
-                                   const int32_t *__restrict__ perm,
                                    const unsigned long long *__restrict__ smax,
                                    double *__restrict__ d) {
     const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (i >= n) return;
     const double s = bits_to_double(*smax);
-    d[perm ? perm[i] : i] = s > 0.0 ? s * (double)v32[i] : 0.0;
+    d[i] = s > 0.0 ? s * (double)v32[i] : 0.0;
 }
 
 unsigned g1(int64_t n) { return (unsigned)((n + 255) / 256); }
@@ -416,7 +484,7 @@ namespace mxlu {
 
 int gemv_f64(int trans, int64_t n, const ASource &src, const double *x,
              const double *b, double *y, double *part, double *asum_part, int nsplit,
-             unsigned long long *stats, hipStream_t s) {
+             unsigned long long *stats, unsigned long long *ymax, hipStream_t s) {
     if (n <= 0) return 0;
     const int64_t cps = (n + nsplit - 1) / nsplit;
     const dim3 gn(g1(n), (unsigned)nsplit), gt((unsigned)((n + 3) / 4), (unsigned)nsplit);
@@ -437,7 +505,7 @@ int gemv_f64(int trans, int64_t n, const ASource &src, const double *x,
                            asum_part);
     MXLU_LAUNCH_CHECK();
     hipLaunchKernelGGL(gemv_finish_kernel, dim3(g1(n)), dim3(256), 0, s, n, nsplit, part,
-                       asum_part, b, y, x, stats);
+                       asum_part, b, y, x, stats, ymax);
     MXLU_LAUNCH_CHECK();
     return 0;
 }
@@ -467,6 +535,19 @@ int gemv_small_f64(int64_t n, int k, const double *V, int64_t ldv, const double 
     return 0;
 }
 
+bool arnoldi_small_ok(int64_t n, int nchunks, int k) {
+    return nchunks == 1 && n < kArnoldiMaxN && k <= 256;
+}
+
+int arnoldi_small_f64(int64_t n, int k, const double *V, int64_t ldv, const double *z, double *h1,
+                      double *h2, double *hn, double *vnext, hipStream_t s) {
+    if (n <= 0) return 0;
+    hipLaunchKernelGGL(arnoldi_small_kernel, dim3(1), dim3(1024), 0, s, (int)n, k, V, ldv, z, h1, h2,
+                       hn, vnext);
+    MXLU_LAUNCH_CHECK();
+    return 0;
+}
+
 int scale_copy_f64(int64_t n, const double *z, double alpha, double *v, hipStream_t s) {
     if (n <= 0) return 0;
     hipLaunchKernelGGL(scale_copy_kernel, dim3(g1(n)), dim3(256), 0, s, n, z, alpha, v);
@@ -490,12 +571,11 @@ int absmax_f64(int64_t n, const double *v, unsigned long long *out, hipStream_t 
 }
 
 int lp_precond_apply_f32(int64_t n, const float *F, int64_t ldf, const int32_t *perm,
-                         const double *r, double *d, float *v32, unsigned long long *smax,
-                         hipStream_t s) {
+                         const double *r, double *d, float *v32, const unsigned long long *smax,
+                         unsigned long long *smax_next, hipStream_t s) {
     if (n <= 0) return 0;
-    MXLU_HIP_TRY(hipMemsetAsync(smax, 0, sizeof(unsigned long long), s));
-    MXLU_TRY(absmax_f64(n, r, smax, s));
-    hipLaunchKernelGGL(precond_in_kernel, dim3(g1(n)), dim3(256), 0, s, n, r, perm, smax, v32);
+    hipLaunchKernelGGL(precond_in_kernel, dim3(g1(n)), dim3(256), 0, s, n, r, perm, smax, smax_next,
+                       v32);
     MXLU_LAUNCH_CHECK();
     for (int64_t b0 = 0; b0 < n; b0 += kTrsv32Bs) {   // L, forward
         const int rows = (int)std::min<int64_t>(kTrsv32Bs, n - b0);
@@ -520,26 +600,8 @@ int lp_precond_apply_f32(int64_t n, const float *F, int64_t ldf, const int32_t *
             MXLU_LAUNCH_CHECK();
         }
     }
-    hipLaunchKernelGGL(precond_out_kernel, dim3(g1(n)), dim3(256), 0, s, n, v32, nullptr, smax,
+    hipLaunchKernelGGL(precond_out_kernel, dim3(g1(n)), dim3(256), 0, s, n, v32, smax,
                        d);
-    MXLU_LAUNCH_CHECK();
-    return 0;
-}
-
-int lp_precond_apply(int fmt, int trans, int64_t n, const uint16_t *F, int64_t ldf,
-                     const int32_t *perm, const double *r, double *d, float *v32,
-                     unsigned long long *smax, TrsvChain &ch, hipStream_t s) {
-    if (n <= 0) return 0;
-    MXLU_HIP_TRY(hipMemsetAsync(smax, 0, sizeof(unsigned long long), s));
-    MXLU_TRY(absmax_f64(n, r, smax, s));
-    // forward: v = P r / s; L; U.   transposed: v = r / s; U^T; L^T; P^T v.
-    hipLaunchKernelGGL(precond_in_kernel, dim3(g1(n)), dim3(256), 0, s, n, r,
-                       trans ? nullptr : perm, smax, v32);
-    MXLU_LAUNCH_CHECK();
-    MXLU_TRY(trsv_lp(fmt, trans ? 2 : 0, n, F, ldf, v32, ch, s));
-    MXLU_TRY(trsv_lp(fmt, trans ? 3 : 1, n, F, ldf, v32, ch, s));
-    hipLaunchKernelGGL(precond_out_kernel, dim3(g1(n)), dim3(256), 0, s, n, v32,
-                       trans ? perm : nullptr, smax, d);
     MXLU_LAUNCH_CHECK();
     return 0;
 }

@@ -89,12 +89,14 @@ __device__ __forceinline__ int swz(int r) { return ((r >> 1) & 7) ^ ((r >> 4) & 
 using Unit = uint32_t __attribute__((ext_vector_type(4)));   // eight 16-bit values
 
 template <int FMT, int KIND>
-__global__ __launch_bounds__(256) void trsv_chain_kernel(int64_t n, const uint16_t *__restrict__ F,
-                                                         int64_t ldf, float *__restrict__ v,
-                                                         uint64_t *xs, uint32_t tag, int nstrips,
-                                                         int *expired) {
+__global__ __launch_bounds__(256) void trsv_chain_kernel(
+    int64_t n, const uint16_t *__restrict__ F, int64_t ldf, const int32_t *__restrict__ perm,
+    const double *__restrict__ r, float *__restrict__ v, double *__restrict__ d,
+    const unsigned long long *__restrict__ smax, unsigned long long *smax_next, uint64_t *xs,
+    uint32_t tag, int nstrips, int *expired) {
     constexpr bool FWD = KIND == 0 || KIND == 2, UNIT = KIND == 0 || KIND == 3;
     constexpr bool COLS = KIND == 0 || KIND == 1;   // the factor's rows run along its columns
+    constexpr bool FIRST = FWD;   // of the two solves
     // a chunk in staging per wave, then the chunks of the own block (those of
     // wave s at s (s + 1) / 2)
     __shared__ Unit stage[kStrips][kStrip][8];
@@ -174,7 +176,18 @@ __global__ __launch_bounds__(256) void trsv_chain_kernel(int64_t n, const uint16
         if (FMT == kFmtBf16) return __uint_as_float((k & 1) ? u & 0xffff0000u : u << 16);
         return lp_to_f32<FMT>((uint16_t)((k & 1) ? u >> 16 : u));
     };
-    float acc = mine ? v[row] : 0.0f;
+    // the right-hand side: r / s in FP32 (P r / s for L), or the first solution
+    const double scale = __longlong_as_double((long long)*smax);
+    float acc = 0.0f;
+    if (FIRST) {
+        if (blockIdx.x == 0 && threadIdx.x == 0) *smax_next = 0;
+        if (mine) {
+            const double ri = r[KIND == 0 && perm ? perm[row] : row];
+            acc = scale > 0.0 ? (float)(ri / scale) : 0.0f;
+        }
+    } else if (mine) {
+        acc = v[row];
+    }
     // terms of 16 columns (group gq of the chunk in solve order), x: lane = column
     auto terms = [&](const uint32_t (&rr)[32], float x, auto gq) {
         constexpr int g = decltype(gq)::value;
@@ -223,8 +236,9 @@ __global__ __launch_bounds__(256) void trsv_chain_kernel(int64_t n, const uint16
 #pragma unroll
             for (int m = 0; m < 4; ++m) {
                 const int k = 8 * j + 2 * m;
-                u[m] = rr[4 * j + m] & ((FWD ? k < lane : k > lane) && mine ? 0xffffu : 0u) |
-                       rr[4 * j + m] & ((FWD ? k + 1 < lane : k + 1 > lane) && mine ? 0xffff0000u : 0u);
+                const uint32_t keep = ((FWD ? k < lane : k > lane) ? 0xffffu : 0u) |
+                                      ((FWD ? k + 1 < lane : k + 1 > lane) ? 0xffff0000u : 0u);
+                u[m] = mine ? rr[4 * j + m] & keep : 0u;
             }
             diag[lane][j ^ swz(lane)] = u;
         }
@@ -391,7 +405,11 @@ __global__ __launch_bounds__(256) void trsv_chain_kernel(int64_t n, const uint16
             group(G1{});
             group(G2{});
             group(G3{});
-            if (mine) v[row] = sol;
+            if (FIRST) {
+                if (mine) v[row] = sol;
+            } else if (mine) {   // d = s x (P^T of it for L^T)
+                d[KIND == 3 && perm ? perm[row] : row] = scale > 0.0 ? scale * (double)sol : 0.0;
+            }
         } else {
             for (int g = 0; g < 4; ++g) lds_barrier();
         }
@@ -399,7 +417,9 @@ __global__ __launch_bounds__(256) void trsv_chain_kernel(int64_t n, const uint16
 }
 
 template <int FMT, int KIND>
-int trsv_run(int64_t n, const uint16_t *F, int64_t ldf, float *v, TrsvChain &ch, hipStream_t s) {
+int trsv_run(int64_t n, const uint16_t *F, int64_t ldf, const int32_t *perm, const double *r, double *d,
+             float *v, const unsigned long long *smax, unsigned long long *smax_next, TrsvChain &ch,
+             hipStream_t s) {
     const int64_t nstrips = (n + kStrip - 1) / kStrip;
     if (nstrips > 0x7ffffff0) {
         set_error_msg("trsv: too many blocks");
@@ -411,27 +431,37 @@ int trsv_run(int64_t n, const uint16_t *F, int64_t ldf, float *v, TrsvChain &ch,
     }
     const uint32_t tag = ++ch.tag;
     hipLaunchKernelGGL((trsv_chain_kernel<FMT, KIND>), dim3((unsigned)((nstrips + kStrips - 1) / kStrips)),
-                       dim3(256), 0, s, n, F, ldf, v, ch.xs, tag, (int)nstrips, ch.expired);
+                       dim3(256), 0, s, n, F, ldf, perm, r, v, d, smax, smax_next, ch.xs, tag,
+                       (int)nstrips, ch.expired);
     MXLU_LAUNCH_CHECK();
     return 0;
+}
+
+template <int FMT>
+int apply(int trans, int64_t n, const uint16_t *F, int64_t ldf, const int32_t *perm, const double *r,
+          double *d, float *v, const unsigned long long *smax, unsigned long long *smax_next,
+          TrsvChain &ch, hipStream_t s) {
+    if (trans) {   // v = r / s; U^T; L^T; P^T
+        MXLU_TRY((trsv_run<FMT, 2>(n, F, ldf, perm, r, d, v, smax, smax_next, ch, s)));
+        return trsv_run<FMT, 3>(n, F, ldf, perm, r, d, v, smax, smax_next, ch, s);
+    }
+    // v = P r / s; L; U
+    MXLU_TRY((trsv_run<FMT, 0>(n, F, ldf, perm, r, d, v, smax, smax_next, ch, s)));
+    return trsv_run<FMT, 1>(n, F, ldf, perm, r, d, v, smax, smax_next, ch, s);
 }
 
 }  // namespace
 
 namespace mxlu {
 
-int trsv_lp(int fmt, int kind, int64_t n, const uint16_t *F, int64_t ldf, float *v, TrsvChain &ch,
-            hipStream_t s) {
+int lp_precond_apply(int fmt, int trans, int64_t n, const uint16_t *F, int64_t ldf,
+                     const int32_t *perm, const double *r, double *d, float *v32,
+                     const unsigned long long *smax, unsigned long long *smax_next, TrsvChain &ch,
+                     hipStream_t s) {
     if (n <= 0) return 0;
-    if (fmt == kFmtBf16)
-        return kind == 0   ? trsv_run<kFmtBf16, 0>(n, F, ldf, v, ch, s)
-               : kind == 1 ? trsv_run<kFmtBf16, 1>(n, F, ldf, v, ch, s)
-               : kind == 2 ? trsv_run<kFmtBf16, 2>(n, F, ldf, v, ch, s)
-                           : trsv_run<kFmtBf16, 3>(n, F, ldf, v, ch, s);
-    return kind == 0   ? trsv_run<kFmtFp16, 0>(n, F, ldf, v, ch, s)
-           : kind == 1 ? trsv_run<kFmtFp16, 1>(n, F, ldf, v, ch, s)
-           : kind == 2 ? trsv_run<kFmtFp16, 2>(n, F, ldf, v, ch, s)
-                       : trsv_run<kFmtFp16, 3>(n, F, ldf, v, ch, s);
+    return fmt == kFmtBf16
+               ? apply<kFmtBf16>(trans, n, F, ldf, perm, r, d, v32, smax, smax_next, ch, s)
+               : apply<kFmtFp16>(trans, n, F, ldf, perm, r, d, v32, smax, smax_next, ch, s);
 }
 
 }  // namespace mxlu

@@ -368,6 +368,33 @@ def test_mxp_solve_matches_oracle(api, prec, method, n, nb):
     assert fe < 4 * 16 * n * EPS * kappa
 
 
+@pytest.mark.parametrize("n", [2, 65, 255, 257, 1025, 2047])
+def test_gmres_single_workgroup_orthogonalization(api, n):
+    """Orthogonalization steps of one workgroup (n < 2048): sizes around its 256
+    partial sums and its 1024 threads, two right-hand sides (the second one's
+    preconditioner scale must not see the first one's last residual); bounds
+    and iteration counts as in the test above."""
+    note(f"gmres single workgroup n={n}")
+    seed = inputs.config_seed(2) + 7 * n
+    A = inputs.diag_dominant_matrix(seed, 0, n)
+    B = inputs.uniform_matrix(seed, 1, n, 2)
+    B[:, 1] *= 2.0 ** -40
+    dA, dB = to_dev(A), to_dev(B)
+    X, rep, _, _ = api.mxp_solve(dA, dB, prec="bf16", nb=64, refine="gmres")
+    torch.cuda.synchronize()
+    X = X.cpu().numpy()
+    assert rep["status"] == 0 and rep["converged"] == 1
+    F_ref, _, _ = oracle.lp_getrf(A, min(64, n), PREC_ID["bf16"], pivot=False)
+    outer = inner = 0
+    for c in range(2):
+        out = refine.refine(A, B[:, c], F_ref, None, method="gmres")
+        outer += out["outer_iters"]
+        inner += out["inner_iters"]
+        assert checks.scaled_residual(A, X[:, c], B[:, c]) < 16
+    assert abs(rep["outer_iters"] - outer) <= 2
+    assert abs(rep["inner_iters"] - inner) <= outer + 2
+
+
 @pytest.mark.parametrize("prec,n,nb,tile", [("fp8", 896, 128, 12), ("bf16", 1000, 256, 128)])
 def test_mxp_solve_tile_scaled_matrix(api, prec, n, nb, tile):
     """A harder system for the refinement: the tile-scaled matrix has
