@@ -10,16 +10,17 @@
 //     row has in the interchanged leaf, an interchange exchanges two
 //     positions, and rows are stored to their positions (after every
 //     workgroup has loaded that part of its rows).
-//   * four waves with up to four rows per thread, one wave per SIMD: a wave
-//     issues an instruction every four cycles, so two waves on a SIMD double
-//     the reductions and bookkeeping of every column.  Four rows of 32 FP64
+//   * up to four rows per thread: the reductions and bookkeeping of a column
+//     are issued once per wave, an instruction every four cycles, so few waves
+//     with several rows each do them faster than many.  Four rows of 32 FP64
 //     columns do not fit a thread's vector registers, so the leaf is taken in
 //     two halves of 16 columns: the second is loaded when the first is done,
 //     takes the first's columns (its 16 pivot rows' triangular solve, then one
 //     product per thread and row) and is factored like the first.
 //     The first half's columns are left to the caller's interchanges for
 //     those of the second half (panel_leaf_swap).
-//   * up to 1024 rows: one workgroup, no exchange through memory.  Two LDS
+//   * up to 2048 rows: one workgroup (four waves up to 1024 rows, else eight,
+//     two a SIMD), no exchange through memory.  Two LDS
 //     barriers per column: the waves' candidates (value, position) meet in
 //     LDS, every wave picks the winner and divides while the winner's wave
 //     writes its row.
@@ -36,13 +37,14 @@
 // The wave reduction takes the maximum of the upper words by DPP and finds
 // its lane by ballot; only ties in the upper word take the full comparison.
 //
-// A leaf of 32 FP64 columns with 64 / 256 / 512 / 1024 / 2048 / 4096 / 16384 /
-// 32768 rows takes 34 / 36 / 54 / 58 / 124 / 130 / 132 / 149 us.  On up to 64
-// workgroups of one 1024-row sweep without the halves (512 threads, two rows
-// each) it was 44 / 44 / 59 / 59 / 113 / 123 / 136 / 150 us; as 32 workgroups
-// or more with two exchange rounds per column 123 us up to 4096 rows, 145 and
-// 160 us.  The interchanges that follow take 5.8 us in one launch; composing
-// and applying them in two took 12 to 16 us, which outweighs the 2048-row loss.
+// A leaf of 32 FP64 columns with 64 / 256 / 512 / 1024 / 1500 / 2048 / 4096 /
+// 16384 / 32768 rows takes 35 / 36 / 51 / 56 / 65 / 73 / 117 / 125 / 150 us.
+// With an exchange from 1025 rows on, 1500 and 2048 rows took 124 us.  Without
+// the halves (512 threads, two rows each, an exchange from 1025 rows on) it was
+// 44 / 44 / 59 / 59 / 113 / 113 / 123 / 136 / 150 us; as 32 workgroups or more
+// with two exchange rounds per column 123 us up to 4096 rows, 145 and 160 us.
+// The interchanges that follow take 5.8 us in one launch; composing and
+// applying them in two took 12 to 16 us.
 #pragma once
 
 #include "common.h"
@@ -238,11 +240,13 @@ struct WideLeaf {
         // the group's candidate: every wave picks it
         int from;
         {
-            static_assert(NW == 4, "one quad of waves");
+            static_assert(NW == 4 || NW == 8, "a quad of waves or two");
             const WideKey k = sh.cand[lane & (NW - 1)];
             int mx = k.key;
             mx = max(mx, __builtin_amdgcn_update_dpp(0, mx, 0xB1, 0xF, 0xF, false));
             mx = max(mx, __builtin_amdgcn_update_dpp(0, mx, 0x4E, 0xF, 0xF, false));
+            if (NW == 8)
+                mx = max(mx, __builtin_amdgcn_update_dpp(0, mx, 0x141, 0xF, 0xF, false));   // row_half_mirror
             top = __builtin_amdgcn_readfirstlane(mx);
             uint64_t mask = __builtin_amdgcn_ballot_w64(k.key == top) & (uint64_t)((1 << NW) - 1);
             from = __builtin_ctzll(mask);
@@ -258,9 +262,9 @@ struct WideLeaf {
             piv = lane_value((T)k.v, from);
             idx = __builtin_amdgcn_readlane(k.idx, from);
         }
-        if (!EXCH || G == 1) {
+        if constexpr (!EXCH) {
             if (wave == from) put_row(idx, jb, sh.row);
-        } else if constexpr (EXCH) {
+        } else {
             uint64_t *gs = slots + (size_t)par * mxlu::kMaxGroups * kSlotWords;
             if (wave == from) {   // the wave that holds the row
                 put_row(idx, jb, sh.stage);
@@ -406,7 +410,7 @@ struct WideLeaf {
     // other row's products, one fused multiply-add per term in ascending order
     // as everywhere in the panel.
     __device__ __forceinline__ void second_half(WideShared<T, NT, CW> &sh, const T *P, int64_t lda) {
-        if (!EXCH || G == 1) {
+        if constexpr (!EXCH) {
 #pragma unroll
             for (int q = 0; q < RPT; ++q)
                 if (pos[q] >= 0 && pos[q] < CW) {
@@ -416,7 +420,7 @@ struct WideLeaf {
                         sh.u12[pos[q]][c] = x[q][c];
                     }
                 }
-        } else if constexpr (EXCH) {
+        } else {
             // the pivot rows lie in several groups: they go through memory,
             // in slots no group uses
             uint64_t *area = slots + (size_t)mxlu::kWideMaxGroups * kSlotWords;
@@ -627,8 +631,18 @@ int panel_leaf_wide(int64_t m, int w, T *P, int64_t ldp, int64_t r0, int32_t *ip
         hipLaunchKernelGGL((panel_leaf_wide_kernel<T, 256, 1, 32, false>), dim3(1), dim3(256), 0, s,
                            (int)m, w, P, ldp, 1, r0, ipiv + r0, ex.slots, ex.flags);
     } else {
-        hipLaunchKernelGGL((panel_leaf_wide_kernel<T, 256, 4, 16, true>), dim3((unsigned)G), dim3(256),
-                           0, s, (int)m, w, P, ldp, G, r0, ipiv + r0, ex.slots, ex.flags);
+        // an exchange through memory costs about 2 us a column, a second wave
+        // on every SIMD 0.5 us: 2048 rows in one workgroup 73 us, in two 124
+        if (m <= 1024)
+            hipLaunchKernelGGL((panel_leaf_wide_kernel<T, 256, 4, 16, false>), dim3(1), dim3(256), 0, s,
+                               (int)m, w, P, ldp, 1, r0, ipiv + r0, ex.slots, ex.flags);
+        else if (m <= 2048)
+            hipLaunchKernelGGL((panel_leaf_wide_kernel<T, 512, 4, 16, false>), dim3(1), dim3(512), 0, s,
+                               (int)m, w, P, ldp, 1, r0, ipiv + r0, ex.slots, ex.flags);
+        else
+            hipLaunchKernelGGL((panel_leaf_wide_kernel<T, 256, 4, 16, true>), dim3((unsigned)G),
+                               dim3(256), 0, s, (int)m, w, P, ldp, G, r0, ipiv + r0, ex.slots,
+                               ex.flags);
         if (w > 16) *split = 16;
     }
     MXLU_LAUNCH_CHECK();
