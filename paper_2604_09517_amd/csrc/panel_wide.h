@@ -10,17 +10,18 @@
 //     row has in the interchanged leaf, an interchange exchanges two
 //     positions, and rows are stored to their positions (after every
 //     workgroup has loaded that part of its rows).
-//   * up to four rows per thread: the reductions and bookkeeping of a column
-//     are issued once per wave, an instruction every four cycles, so few waves
-//     with several rows each do them faster than many.  Four rows of 32 FP64
-//     columns do not fit a thread's vector registers, so the leaf is taken in
-//     two halves of 16 columns: the second is loaded when the first is done,
-//     takes the first's columns (its 16 pivot rows' triangular solve, then one
-//     product per thread and row) and is factored like the first.
-//     The first half's columns are left to the caller's interchanges for
-//     those of the second half (panel_leaf_swap).
-//   * up to 2048 rows: one workgroup (four waves up to 1024 rows, else eight,
-//     two a SIMD), no exchange through memory.  Two LDS
+//   * one row per thread where one workgroup holds them so, up to four else:
+//     the reductions and bookkeeping of a column are issued once per wave, an
+//     instruction every four cycles, whatever the rows of a lane.  Four rows
+//     of 32 FP64 columns do not fit a thread's vector registers, so that such
+//     a leaf is taken in two halves of 16 columns: the second is loaded when
+//     the first is done, takes the first's columns (its 16 pivot rows'
+//     triangular solve, then one product per thread and row) and is factored
+//     like the first.  The first half's columns are left to the caller's
+//     interchanges for those of the second half (panel_leaf_swap).
+//   * branches are dearer than multiply-adds: a row's update is one masked
+//     region, no load is under a condition.
+//   * up to 2048 rows: one workgroup, no exchange through memory.  Two LDS
 //     barriers per column: the waves' candidates (value, position) meet in
 //     LDS, every wave picks the winner and divides while the winner's wave
 //     writes its row.
@@ -38,13 +39,13 @@
 // its lane by ballot; only ties in the upper word take the full comparison.
 //
 // A leaf of 32 FP64 columns with 64 / 256 / 512 / 1024 / 1500 / 2048 / 4096 /
-// 16384 / 32768 rows takes 35 / 36 / 51 / 56 / 65 / 73 / 117 / 125 / 150 us.
-// With an exchange from 1025 rows on, 1500 and 2048 rows took 124 us.  Without
-// the halves (512 threads, two rows each, an exchange from 1025 rows on) it was
-// 44 / 44 / 59 / 59 / 113 / 113 / 123 / 136 / 150 us; as 32 workgroups or more
-// with two exchange rounds per column 123 us up to 4096 rows, 145 and 160 us.
-// The interchanges that follow take 5.8 us in one launch; composing and
-// applying them in two took 12 to 16 us.
+// 8192 / 16384 / 32768 rows takes 22 / 30 / 36 / 51 / 67 / 72 / 103 / 112 / 130
+// / 150 us.  All in halves above 256 rows, with an exchange from 1025 rows on
+// and a masked region for every four columns of a row it was 35 / 36 / 54 / 58 /
+// 124 / 124 / 130 / 132 / 132 / 149; as 32 workgroups or more with two exchange
+// rounds per column 123 us up to 4096 rows, 145 and 160 us.  The interchanges
+// that follow take 5.8 us in one launch; composing and applying them in two
+// took 12 to 16 us.
 #pragma once
 
 #include "common.h"
@@ -146,17 +147,16 @@ struct WideLeaf {
     }
 
     // the thread whose row is at position idx writes its columns from CB jb on
-    // to d0 (in column order)
-    __device__ __forceinline__ void put_row(int idx, int jb, T *d0) {
+    // to d, in the order of its registers (column CB (jb + k) + c at CB k + c)
+    __device__ __forceinline__ void put_row(int idx, int jb, T *d) {
 #pragma unroll
         for (int q = 0; q < RPT; ++q)
             if (pos[q] == idx) {
 #pragma unroll
                 for (int k = 0; k < NB; ++k) {
                     if (k >= NB - jb) break;   // uniform
-                    T *d = d0 + CB * (jb + k);
 #pragma unroll
-                    for (int c = 0; c < CB; ++c) d[c] = x[q][CB * k + c];
+                    for (int c = 0; c < CB; ++c) d[CB * k + c] = x[q][CB * k + c];
                 }
             }
     }
@@ -234,19 +234,23 @@ struct WideLeaf {
             }
             piv = lane_value(val, l);
             idx = none ? INT_MAX : __builtin_amdgcn_readlane(at, l);
-            if (lane == 0) sh.cand[wave] = WideKey{(double)piv, idx, top};
+            if (NW > 1 && lane == 0) sh.cand[wave] = WideKey{(double)piv, idx, top};
         }
-        lds_barrier();
         // the group's candidate: every wave picks it
-        int from;
-        {
-            static_assert(NW == 4 || NW == 8, "a quad of waves or two");
+        int from = 0;
+        if constexpr (NW > 1) {
+            lds_barrier();
+            static_assert(NW == 4 || NW == 8 || NW == 16, "reduced below");
             const WideKey k = sh.cand[lane & (NW - 1)];
             int mx = k.key;
             mx = max(mx, __builtin_amdgcn_update_dpp(0, mx, 0xB1, 0xF, 0xF, false));
             mx = max(mx, __builtin_amdgcn_update_dpp(0, mx, 0x4E, 0xF, 0xF, false));
             if (NW == 8)
                 mx = max(mx, __builtin_amdgcn_update_dpp(0, mx, 0x141, 0xF, 0xF, false));   // row_half_mirror
+            if (NW == 16) {
+                mx = max(mx, __builtin_amdgcn_update_dpp(0, mx, 0x124, 0xF, 0xF, false));   // row_ror:4
+                mx = max(mx, __builtin_amdgcn_update_dpp(0, mx, 0x128, 0xF, 0xF, false));   // row_ror:8
+            }
             top = __builtin_amdgcn_readfirstlane(mx);
             uint64_t mask = __builtin_amdgcn_ballot_w64(k.key == top) & (uint64_t)((1 << NW) - 1);
             from = __builtin_ctzll(mask);
@@ -271,7 +275,7 @@ struct WideLeaf {
                 wave_sync_lds();
                 const uint32_t *words = reinterpret_cast<const uint32_t *>(sh.stage);
                 uint64_t *own = gs + (size_t)g * kSlotWords;
-                if (lane >= VW * CB * jb && lane < RW) ll_store(&own[4 + lane], seq, words[lane]);
+                if (lane < VW * (CW - CB * jb)) ll_store(&own[4 + lane], seq, words[lane]);
                 if (lane == 0) ll_store(&own[2], seq, (uint32_t)idx);
             }
             // one batch: the candidates (lane: group) and every NW-th load of
@@ -283,13 +287,13 @@ struct WideLeaf {
             const uint64_t *pr = gs + (size_t)rg * kSlotWords + 4 + lane % RW;
             uint64_t hv0 = none, hv1 = none, hi = none, xw[KR];
             if (head) {
-                hv0 = ll_load(ph + 4 + VW * JH);
-                if (VW == 2) hv1 = ll_load(ph + 4 + VW * JH + VW - 1);
+                hv0 = ll_load(ph + 4 + VW * JL);
+                if (VW == 2) hv1 = ll_load(ph + 4 + VW * JL + VW - 1);
                 hi = ll_load(ph + 2);
             }
 #pragma unroll
             for (int k = 0; k < KR; ++k)
-                xw[k] = rg + GPL * NW * k < G && lane % RW >= VW * CB * jb
+                xw[k] = rg + GPL * NW * k < G && lane % RW < VW * (CW - CB * jb)
                             ? ll_load(pr + k * (GPL * NW * kSlotWords))
                             : none;
             for (long rounds = 0;; ++rounds) {
@@ -298,8 +302,8 @@ struct WideLeaf {
                 for (int k = 0; k < KR; ++k) late = late || stale(xw[k], seq);
                 if (__builtin_amdgcn_ballot_w64(late) == 0) break;
                 if (expired(rounds)) break;
-                if (stale(hv0, seq)) hv0 = ll_load(ph + 4 + VW * JH);
-                if (VW == 2 && stale(hv1, seq)) hv1 = ll_load(ph + 4 + VW * JH + VW - 1);
+                if (stale(hv0, seq)) hv0 = ll_load(ph + 4 + VW * JL);
+                if (VW == 2 && stale(hv1, seq)) hv1 = ll_load(ph + 4 + VW * JL + VW - 1);
                 if (stale(hi, seq)) hi = ll_load(ph + 2);
 #pragma unroll
                 for (int k = 0; k < KR; ++k)
@@ -352,33 +356,52 @@ struct WideLeaf {
             asm("" : "+v"(l[q]));   // here, while the row is on its way
         }
         lds_barrier();   // the row is there
-        // One value of the pivot row per lane; each goes to the multiply-adds
-        // through a scalar register (LDS broadcasts of the whole row to every
-        // wave took longer than the arithmetic).
-        const T ul = sh.row[lane & (CW - 1)];
-        // rows up to position J are final: not even a multiple by zero, which
-        // an infinity in the pivot row would turn into NaN
-        bool below[RPT];
-#pragma unroll
-        for (int q = 0; q < RPT; ++q) {
-            below[q] = pos[q] > J;
-            x[q][JL] = below[q] ? l[q] : x[q][JL];
-        }
-#pragma unroll
-        for (int k = 0; k < NB; ++k) {
-            if (k >= NB - jb) break;   // finished columns (uniform)
-            T u[CB];
-#pragma unroll
-            for (int c = 0; c < CB; ++c)
-                if (CB * k + c > JL) u[c] = lane_value(ul, CB * (jb + k) + c);
+        // One value of the pivot row per lane, in the order of the registers;
+        // each goes to the multiply-adds through a scalar register (LDS
+        // broadcasts of the whole row to every wave took longer than the
+        // arithmetic).
+        T ul = sh.row[lane & (CW - 1)];
+        asm volatile("" : "+v"(ul));   // read by every lane, not by those of a masked region below
+        // Rows up to position J are final: not even a multiple by zero, which
+        // an infinity in the pivot row would turn into NaN.
+        if constexpr (RPT <= 2) {
+            // one masked region per row with the columns inside (a region per
+            // four columns spent more on its branches than on the arithmetic)
 #pragma unroll
             for (int q = 0; q < RPT; ++q)
-                if (below[q]) {
+                if (pos[q] > J) {
+                    x[q][JL] = l[q];
 #pragma unroll
-                    for (int c = 0; c < CB; ++c)
-                        if (CB * k + c > JL)
-                            x[q][CB * k + c] = fma(-l[q], u[c], x[q][CB * k + c]);
+                    for (int k = 0; k < NB; ++k) {
+                        if (k >= NB - jb) break;   // finished columns (uniform)
+#pragma unroll
+                        for (int c = CB * k; c < CB * k + CB; ++c)
+                            if (c > JL) x[q][c] = fma(-l[q], lane_value(ul, c), x[q][c]);
+                    }
                 }
+        } else {
+            bool below[RPT];
+#pragma unroll
+            for (int q = 0; q < RPT; ++q) {
+                below[q] = pos[q] > J;
+                x[q][JL] = below[q] ? l[q] : x[q][JL];
+            }
+#pragma unroll
+            for (int k = 0; k < NB; ++k) {
+                if (k >= NB - jb) break;   // finished columns (uniform)
+                T u[CB];
+#pragma unroll
+                for (int c = 0; c < CB; ++c)
+                    if (CB * k + c > JL) u[c] = lane_value(ul, CB * k + c);
+#pragma unroll
+                for (int q = 0; q < RPT; ++q)
+                    if (below[q]) {
+#pragma unroll
+                        for (int c = 0; c < CB; ++c)
+                            if (CB * k + c > JL)
+                                x[q][CB * k + c] = fma(-l[q], u[c], x[q][CB * k + c]);
+                    }
+            }
         }
     }
 
@@ -524,13 +547,15 @@ __global__ __launch_bounds__(NT) void panel_leaf_wide_kernel(int m, int w, T *P,
     s.r0 = r0;
     s.slots = slots;
     s.flags = flags;
+    // rows and columns past the leaf: others' values, never looked at (no load
+    // is under a condition, so that all are in flight together)
     auto load = [&](int c0) {
 #pragma unroll
         for (int q = 0; q < RPT; ++q) {
             const int r = s.g * Leaf::R + s.tid + NT * q;
+            const T *src = P + (r < m ? r : m - 1);
 #pragma unroll
-            for (int c = 0; c < CW; ++c)
-                s.x[q][c] = (r < m && c0 + c < w) ? P[(size_t)r + (size_t)(c0 + c) * lda] : (T)0;
+            for (int c = 0; c < CW; ++c) s.x[q][c] = src[(size_t)min(c0 + c, w - 1) * lda];
         }
     };
     // a row may go to another group's position: every group has loaded these
@@ -627,23 +652,26 @@ int panel_leaf_wide(int64_t m, int w, T *P, int64_t ldp, int64_t r0, int32_t *ip
         return MXLU_E_NOMEM;
     }
     *split = 0;
-    if (m <= 256) {   // a row per thread: all 32 columns fit
-        hipLaunchKernelGGL((panel_leaf_wide_kernel<T, 256, 1, 32, false>), dim3(1), dim3(256), 0, s,
-                           (int)m, w, P, ldp, 1, r0, ipiv + r0, ex.slots, ex.flags);
-    } else {
-        // an exchange through memory costs about 2 us a column, a second wave
-        // on every SIMD 0.5 us: 2048 rows in one workgroup 73 us, in two 124
-        if (m <= 1024)
-            hipLaunchKernelGGL((panel_leaf_wide_kernel<T, 256, 4, 16, false>), dim3(1), dim3(256), 0, s,
-                               (int)m, w, P, ldp, 1, r0, ipiv + r0, ex.slots, ex.flags);
-        else if (m <= 2048)
-            hipLaunchKernelGGL((panel_leaf_wide_kernel<T, 512, 4, 16, false>), dim3(1), dim3(512), 0, s,
-                               (int)m, w, P, ldp, 1, r0, ipiv + r0, ex.slots, ex.flags);
-        else
-            hipLaunchKernelGGL((panel_leaf_wide_kernel<T, 256, 4, 16, true>), dim3((unsigned)G),
-                               dim3(256), 0, s, (int)m, w, P, ldp, G, r0, ipiv + r0, ex.slots,
-                               ex.flags);
-        if (w > 16) *split = 16;
+    auto launch = [&](auto kernel, int threads, int groups) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)groups), dim3((unsigned)threads), 0, s, (int)m, w, P, ldp,
+                           groups, r0, ipiv + r0, ex.slots, ex.flags);
+    };
+    // A row per thread as long as one workgroup holds the rows so, then four
+    // rows per thread: an exchange through memory costs about 2 us a column, a
+    // second wave on every SIMD a quarter, the halves another (2048 rows in
+    // one workgroup 72 us, in two 124).  Beyond, two rows per thread with all
+    // columns at once (4096 / 8192 / 16384 / 32768 rows 103 / 112 / 132 / 172
+    // us) as long as the groups whose rows every wave polls are few, else four
+    // rows in halves, whose rows are half as long (115 / 120 / 130 / 150).
+    if (m <= 64) launch(panel_leaf_wide_kernel<T, 64, 1, 32, false>, 64, 1);
+    else if (m <= 256) launch(panel_leaf_wide_kernel<T, 256, 1, 32, false>, 256, 1);
+    else if (m <= 512) launch(panel_leaf_wide_kernel<T, 512, 1, 32, false>, 512, 1);
+    else if (m <= 1024) launch(panel_leaf_wide_kernel<T, 1024, 1, 32, false>, 1024, 1);
+    else if (m > 2048 && m <= 8192) launch(panel_leaf_wide_kernel<T, 512, 2, 32, true>, 512, G);
+    else {
+        if (m <= 2048) launch(panel_leaf_wide_kernel<T, 512, 4, 16, false>, 512, 1);
+        else launch(panel_leaf_wide_kernel<T, 256, 4, 16, true>, 256, G);
+        if (w > 16) *split = 16;   // (the halves)
     }
     MXLU_LAUNCH_CHECK();
     return 0;

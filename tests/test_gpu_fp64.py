@@ -532,13 +532,15 @@ def test_results_independent_of_scratch_contents(api, lookahead):
 
 
 # ----------------------------------------------- leaf on few workgroups
-@pytest.mark.parametrize("m,nb", [(1, 1), (33, 33), (64, 32), (255, 7), (256, 40), (257, 32),
+@pytest.mark.parametrize("m,nb", [(1, 1), (33, 33), (64, 32), (65, 40), (255, 7), (256, 40), (257, 32),
+                                  (512, 70), (513, 33),
                                   (300, 16), (700, 49), (1023, 33), (1024, 64), (1025, 31),
-                                  (1500, 17), (2048, 40), (2049, 72), (5000, 43), (9000, 32), (65536, 32)])
+                                  (1500, 17), (2048, 40), (2049, 72), (5000, 43), (8192, 33),
+                                  (8193, 64), (65536, 32)])
 def test_panel_leaf_geometries_match_oracle(api, m, nb):
-    """The leaf at the edges of its geometries: one workgroup of 256 threads
-    (up to 256 rows), one with four rows per thread in halves of 16 columns (up
-    to 1024, with 512 threads up to 2048), several with an exchange (up to 65536), leaves narrower than
+    """The leaf at the edges of its geometries: one workgroup with a row per
+    thread (up to 64, 256, 512, 1024 rows), one with four in halves of 16 columns
+    (up to 2048), several with an exchange (two rows to 8192, four to 65536), leaves narrower than
     32 columns or a half, and the interchanges of the columns around.  Pivots
     identical to the oracle's; values within the 1e-12 of the other panel
     test (the in-panel products differ from the oracle's in rounding only)."""
