@@ -8,6 +8,7 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "quarter.h"
 
 namespace {
 
@@ -45,14 +46,15 @@ __device__ __forceinline__ void wave_sync_lds() {
 // rows than smaller ones and still leave n / 128 compute units streaming the
 // factor.  Before, every 256 rows took two launches (a diagonal block on one
 // workgroup with a barrier per row, and a row-per-thread update):
-// n = 8192, 16 right-hand sides: 18.0 -> 1.45 ms; n = 32768, one: 12.4 -> 6.
+// n = 8192, 16 right-hand sides: 18.0 -> 1.12 ms; n = 32768, one: 12.4 -> 4.4
 // (measured with the factors of a matrix of the benchmark recipe).
-// A block takes about 9 us (L) and 10 us (U): eight strips of 2200 to 2600
-// cycles (about 1400 or 1900 of them the substitution's instructions, at four
-// cycles each, the rest the way to the next strip through LDS) and 2 us for
-// the way to the next workgroup.  A substitution with a lane per right-hand
-// side (16 values in registers, factor entries broadcast from LDS) waited for
-// an LDS read every other multiply-add and took 2.5 times as long.
+// A block takes 7.6 us (L) and 8.2 us (U): eight strips of about 0.7 us and 2
+// us for the way to the next workgroup.  With the accumulators' rows spread over
+// the quarter waves the other way, each step exchanged its four rows among all
+// quarters first, and a block took 8.6 and 9.3 us; a substitution with a lane
+// per right-hand side (16 values in registers, factor entries broadcast from
+// LDS) waited for an LDS read every other multiply-add and took 2.5 times as
+// long.
 //
 // A solution value goes to `out` as one 64-bit word, written and read with
 // agent-scope relaxed atomics; the words start as kTriEmpty, a signalling NaN
@@ -79,26 +81,6 @@ __device__ __forceinline__ uint64_t tri_load(const double *p) {
                              __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// y[q] <- the value that lane (lane % 16) + 16 q of the wave holds
-__device__ __forceinline__ void quarters(double v, double (&y)[4]) {
-    const uint64_t b = (uint64_t)__double_as_longlong(v);
-    uint32_t o[2][4];
-#pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        const uint32_t d = (uint32_t)(b >> (32 * h));
-        const auto eo = __builtin_amdgcn_permlane16_swap(d, d, false, false);   // rows 0 0 2 2, 1 1 3 3
-        const auto e = __builtin_amdgcn_permlane32_swap(eo[0], eo[0], false, false);
-        const auto f = __builtin_amdgcn_permlane32_swap(eo[1], eo[1], false, false);
-        o[h][0] = e[0];
-        o[h][2] = e[1];
-        o[h][1] = f[0];
-        o[h][3] = f[1];
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q)
-        y[q] = __longlong_as_double((long long)(((uint64_t)o[1][q] << 32) | o[0][q]));
-}
-
 template <int KIND>
 __global__ __launch_bounds__(512) void tri_chain_f64_kernel(
     int64_t n, int nr, const double *__restrict__ T, int64_t ldt, const double *in, int64_t ldin,
@@ -117,7 +99,10 @@ __global__ __launch_bounds__(512) void tri_chain_f64_kernel(
     const int li = lane & 15, lq = lane >> 4;
     const int w = blockIdx.x;
     const int64_t r0 = (int64_t)(FWD ? w : nblk - 1 - w) * BS;
-    const int64_t row = r0 + 16 * v + li;     // this lane's factor row
+    // this lane's factor row: matrix row i stands for row 4 (i % 4) + i / 4 of
+    // the strip, so that a quarter wave's accumulators are four rows in turn
+    const int ri = 4 * (li & 3) + (li >> 2);
+    const int64_t row = r0 + 16 * v + ri;
     const int64_t rowc = row < n ? row : n - 1;
     auto block_row = [&](int t) { return (int64_t)(FWD ? t : nblk - 1 - t) * BS; };
     auto tile = [&](int vv, int s) {   // of strip vv's rows and strip s's columns, s solved before vv
@@ -198,7 +183,7 @@ __global__ __launch_bounds__(512) void tri_chain_f64_kernel(
         const int64_t k = r0 + 16 * v + 4 * kk + lq, kc = k < n ? k : n - 1;
         const double f = TR ? T[(size_t)kc + (size_t)rowc * (size_t)ldt]
                             : T[(size_t)rowc + (size_t)kc * (size_t)ldt];
-        Dg[v][4 * kk + lq][li] = row < n && k < n ? f : (row == k ? 1.0 : 0.0);
+        Dg[v][4 * kk + lq][ri] = row < n && k < n ? f : (row == k ? 1.0 : 0.0);
     }
     if (!UNIT) {
         wave_sync_lds();
@@ -208,10 +193,10 @@ __global__ __launch_bounds__(512) void tri_chain_f64_kernel(
         const uint64_t all = __builtin_amdgcn_ballot_w64(in_range);
         if (lane == 0) s_range[v] = all == ~0ull;
     }
-    v4d acc;                   // lane (li, lq), register r: row lq + 4 r, right-hand side li
+    v4d acc;                   // lane (li, lq), register r: row 4 lq + r, right-hand side li
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-        const int64_t g = r0 + 16 * v + lq + 4 * r;
+        const int64_t g = r0 + 16 * v + 4 * lq + r;
         acc[r] = (g < n && li < nr) ? in[(size_t)(inperm ? inperm[g] : g) + (size_t)li * (size_t)ldin]
                                     : 0.0;
     }
@@ -255,7 +240,7 @@ __global__ __launch_bounds__(512) void tri_chain_f64_kernel(
             }
         }
         const int g = FWD ? b : 3 - b;   // rows and columns 4 g .. 4 g + 3
-        ta[b] = (FWD ? li > 4 * g + 3 : li < 4 * g) ? -Dg[v][4 * g + lq][li] : 0.0;
+        ta[b] = (FWD ? ri > 4 * g + 3 : ri < 4 * g) ? -Dg[v][4 * g + lq][ri] : 0.0;
     }
     if (w > 0) {
         // the last earlier block is on the chain's critical path: its strips
@@ -293,11 +278,11 @@ __global__ __launch_bounds__(512) void tri_chain_f64_kernel(
     // own block, 16 rows at a time
     double(*X)[kTriLd] = Xs[w & 1];
     lds_barrier();   // Ot is complete; Xs[w & 1] was last read two blocks ago
-    // Substitution with the wave's tile, four rows a step: the accumulator
-    // keeps rows 4 g .. 4 g + 3 in its register g, one per quarter wave; the
-    // quarters exchange them (lane permutes), every lane solves the four, and
-    // one matrix instruction takes them to the rows still to come.  x: the
-    // solution in accumulator layout.
+    // Substitution with the wave's tile, four rows a step: quarter wave g holds
+    // rows 4 g .. 4 g + 3 of its lanes' right-hand sides, which each lane solves
+    // by itself; three lane permutes of a word turn them into a matrix operand
+    // (lane (li, lq): row 4 g + lq), and one matrix instruction takes them to
+    // the rows still to come.  x[g]: that operand, the solution.
     // U: the quotient x / d through r = RN(1 / d), formed ahead of the chain:
     // q0 = RN(x r), q = RN(q0 + (x - q0 d) r), the correctly rounded quotient
     // while everything stays in the normal range (Markstein's theorem); DIV
@@ -306,19 +291,11 @@ __global__ __launch_bounds__(512) void tri_chain_f64_kernel(
         constexpr bool DIV = decltype(div)::value;
         v4d c = acc;
         uint32_t top = 0;
+        auto step = [&](auto bq) {
+            constexpr int b = decltype(bq)::value, g = FWD ? b : 3 - b;
+            double y[4];   // in solve order
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const int g = FWD ? b : 3 - b;
-            double y[4];
-            quarters(c[g], y);
-            if (!FWD) {   // solve order within the step
-                double t = y[0];
-                y[0] = y[3];
-                y[3] = t;
-                t = y[1];
-                y[1] = y[2];
-                y[2] = t;
-            }
+            for (int i = 0; i < 4; ++i) y[i] = c[FWD ? i : 3 - i];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 if (!UNIT) {
@@ -327,18 +304,22 @@ __global__ __launch_bounds__(512) void tri_chain_f64_kernel(
                     } else {
                         const double q0 = y[i] * rv[b][i];
                         y[i] = fma(fma(-q0, dv[b][i], y[i]), rv[b][i], q0);
-                        top = max(top, (uint32_t)((uint64_t)__double_as_longlong(y[i]) >> 32) &
-                                           0x7fffffffu);
                     }
                 }
 #pragma unroll
                 for (int k = i + 1; k < 4; ++k)
                     y[k] = fma(-tri[b][k * (k - 1) / 2 + i], y[i], y[k]);
             }
-            const int q = FWD ? lq : 3 - lq;
-            x[g] = q == 0 ? y[0] : q == 1 ? y[1] : q == 2 ? y[2] : y[3];
+            const double z[4] = {y[FWD ? 0 : 3], y[FWD ? 1 : 2], y[FWD ? 2 : 1], y[FWD ? 3 : 0]};
+            x[g] = spread<g>(z);
+            if (!UNIT && !DIV)
+                top = max(top, (uint32_t)((uint64_t)__double_as_longlong(x[g]) >> 32) & 0x7fffffffu);
             if (b < 3) c = __builtin_amdgcn_mfma_f64_16x16x4f64(ta[b], x[g], c, 0, 0, 0);
-        }
+        };
+        step(std::integral_constant<int, 0>{});
+        step(std::integral_constant<int, 1>{});
+        step(std::integral_constant<int, 2>{});
+        step(std::integral_constant<int, 3>{});
         return top;
     };
     for (int j = 0; j < NS; ++j) {
