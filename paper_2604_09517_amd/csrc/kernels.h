@@ -57,8 +57,8 @@ int leaf_plan(int64_t m, const LeafDevice &d, int64_t *R, int64_t *G);
 // The current device's facts for the FP64 leaf with group cap `cap`.
 int leaf_device_f64(int cap, LeafDevice *d);
 
-// The leaf's wide form (panel_wide.h) on G = ceil(m / 1024) workgroups.  *split:
-// as of panel_leaf.
+// The leaf's wide form (panel_wide.h): up to 2048 rows on one workgroup, more
+// on G = ceil(m / 1024).  *split: as of panel_leaf.
 constexpr int kWideMaxGroups = 64;
 template <typename T>
 int panel_leaf_wide(int64_t m, int w, T *P, int64_t ldp, int64_t r0, int32_t *ipiv, int G,

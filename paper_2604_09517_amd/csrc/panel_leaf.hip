@@ -636,7 +636,7 @@ static int reg_leaf_occupancy() {
 }
 
 // Wide form: fits with at most kWideMaxGroups groups of 1024 rows, one per
-// CU the leaf may use.  0: does not fit.
+// CU the leaf may use (up to 2048 rows it takes one of them).  0: does not fit.
 static int64_t wide_leaf_groups(int64_t m, const LeafDevice &d) {
     const int64_t cus = d.cap > 0 ? std::min<int64_t>(d.cap, d.cus) : d.cus;
     const int64_t G = (m + 1023) / 1024;

@@ -1,8 +1,8 @@
 // PFACT leaf, wide form (FP64 and FP32, leaves of any width up to 32 columns,
 // up to kWideMaxGroups workgroups): the column steps, pivot choice and
 // arithmetic of the forms in panel_leaf.hip, bit for bit, on the fewest
-// workgroups that hold the rows in registers: NT threads with RPT rows each
-// (1024 rows, which fill a CU's registers in FP64).
+// workgroups that hold the rows in registers: NT threads with RPT rows each, of
+// which CW columns are held at a time.
 //
 // What bounds a leaf is the chain of dependent latencies of each column, so
 // everything is chosen to shorten that chain:
