@@ -300,12 +300,16 @@ bool lookahead_fits(int64_t n, int64_t nb, const double *A, int64_t lda,
 
 // Columns of the remaining update given to the update stream while the next
 // panel is factored: about 1.5x what its CUs finish in the panel's expected
-// time (the leaves take ~7 us per column, the update kernel ~0.24 TFLOP/s per
-// CU).  The rest runs on all CUs once the panel is done, alongside the tail
-// of this part, so erring high costs little and erring low leaves the update
-// CUs idle until the panel ends.
+// time (the leaves take 3.2 us per column at 4096 rows and 4.7 at 32768, the
+// update kernel ~0.24 TFLOP/s per CU).  The rest runs on all CUs once the
+// panel is done, alongside the tail of this part: erring high puts work on the
+// update's CUs that all could share, erring low leaves them idle until the
+// panel ends.  The factorization of n = 32768, nb = 256 with 2.8 / 3.8 / 4.5 /
+// 5.0 / 5.6 / 7.0 / 9.5 us per column takes 559 / 534 / 500 / 497 / 500 / 505 /
+// 511 ms; n = 49152 with 4.5 / 5.0 / 5.6 / 7.0 us 1534 / 1502 / 1495 / 1519;
+// n = 24576, nb = 128 287 / 288 / 291 / 294; n = 8192 and 16384 within 1 %.
 int64_t lookahead_split(int64_t nt, int64_t kb, int64_t kb1, const OverlapStreams *ov) {
-    constexpr double kPanelSecPerCol = 7.0e-6, kUpdateFlopsPerCu = 2.4e11;
+    constexpr double kPanelSecPerCol = 5.0e-6, kUpdateFlopsPerCu = 2.4e11;
     const double flops = 1.5 * kPanelSecPerCol * (double)kb1 * kUpdateFlopsPerCu * ov->update_cus;
     const int64_t rest = nt - kb1;
     int64_t n1 = (int64_t)(flops / (2.0 * (double)nt * (double)kb));
