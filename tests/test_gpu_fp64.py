@@ -651,3 +651,23 @@ def test_solve_permutation_replays_interchanges(api, n):
     api.lu_solve(LU, torch.from_numpy(piv).cuda(), db)
     torch.cuda.synchronize()
     assert np.array_equal(db.cpu().numpy(), b[perm])
+
+
+@pytest.mark.parametrize("trans", [0, 1])
+@pytest.mark.parametrize("scale", [-390, -500, -960, -1000, -1020])
+def test_lu_solve_small_quotients_correctly_rounded(api, trans, scale):
+    """Right-hand sides so small that the remainder of a quotient leaves the
+    normal range (and quotients that are subnormal): with U diagonal every
+    component is one division, which must be the correctly rounded one.  One
+    component in five is zero, one right-hand side all zeros."""
+    n, nrhs = 140, 6
+    rng = np.random.default_rng(-scale)
+    d = rng.uniform(1, 2, n) * 2.0 ** rng.integers(-30, 31, n) * rng.choice([-1.0, 1.0], n)
+    B_h = rng.uniform(1, 2, (n, nrhs)) * 2.0 ** scale
+    B_h[rng.random((n, nrhs)) < 0.2] = 0.0
+    B_h[:, 2] = 0.0
+    dB = to_dev(B_h)
+    ipiv = torch.arange(n, dtype=torch.int32, device="cuda")
+    api.lu_solve(to_dev(np.diag(d)), ipiv, dB, trans=bool(trans))
+    torch.cuda.synchronize()
+    assert np.array_equal(dB.cpu().numpy(), B_h / d[:, None])
