@@ -129,11 +129,11 @@ __global__ __launch_bounds__(256) void trsv_chain_kernel(
             for (int e = 0; e < 8; ++e) {
                 const int64_t je = j + (COLS ? e : 8 * e);
                 g[e] = *reinterpret_cast<const Unit *>(src + (size_t)(je < n ? je : n - 1) * ldf);
+                // columns past n meet a solution of zero, which an infinity
+                // would turn into NaN (forward ones never get here)
+                if (KIND == 1 && je >= n) g[e] = Unit{0, 0, 0, 0};
             }
-            if (KIND == 3) {
-                // columns past n meet a solution of zero; their storage may
-                // hold anything (KIND 1 has taken column n - 1 instead, which
-                // those rows meet anyway; forward ones never get here)
+            if (KIND == 3) {   // the same (their storage may hold anything)
                 Unit keep;
 #pragma unroll
                 for (int q = 0; q < 4; ++q)

@@ -313,6 +313,27 @@ def test_preconditioner_strip_edges(api, prec, n):
             assert np.all(far <= 1e-5 * np.abs(ref).max())
 
 
+@pytest.mark.parametrize("trans", [0, 1])
+@pytest.mark.parametrize("n", [2, 63, 65, 100, 300, 449])
+def test_preconditioner_infinite_factor_entry(api, n, trans):
+    """An FP16 factor entry that overflowed, in the first row's last column of
+    U (transposed: the last row's first column of L, which meets it the same
+    way): that component of the solution is infinite, not NaN, and the others
+    are the oracle's, bit for bit (every product is exact)."""
+    note(f"preconditioner infinity n={n} trans={trans}")
+    F = np.eye(n)
+    F[(n - 1, 0) if trans else (0, n - 1)] = np.inf
+    b = inputs.uniform_matrix(900 + n, 1, n, 1)[:, 0]
+    opts = api.mxp_options(prec="fp16", nb=64, max_outer=0, reuse_factors=True, trans=bool(trans))
+    work = torch.full((api.mxp_workspace_bytes(n, opts, n),), 255, dtype=torch.uint8, device="cuda")
+    api.mxp_factors(work, n, "fp16").copy_(torch.from_numpy(F).to(torch.float16))
+    X, rep, _, _ = api.mxp_solve(to_dev(np.eye(n)), to_dev(b), work=work, opts=opts, allow_notconv=True)
+    torch.cuda.synchronize()
+    x, ref = X.cpu().numpy(), oracle.lp_precond(F, None, b, trans=bool(trans))
+    assert np.isinf(ref[0])
+    assert np.array_equal(x, ref)
+
+
 def test_preconditioner_bitwise_outside_the_reciprocal_range(api):
     """The U solve's diagonal steps divide through a reciprocal only while
     every value is in the normal range; with some diagonal entries of U scaled
