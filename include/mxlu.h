@@ -107,7 +107,8 @@ int mxlu_release(void);
  * mxlu_debug_expire_waits -- test hook, process-wide (0 = off, the default):
  * when on, every panel factorization starts as if one of its bounded waits
  * had already expired, so each wait gives up at its first check and every
- * kernel runs to completion; the call then returns MXLU_E_TIMEOUT.  Lets
+ * kernel runs to completion; the call then returns MXLU_E_TIMEOUT.  The waits
+ * of lu_solve and lu_solve_noalloc give up at their first check as well.  Lets
  * tests exercise that path without delaying any kernel.  Returns 0, or -1
  * for a value other than 0 or 1.
  */
@@ -128,7 +129,13 @@ int mxlu_debug_poison_scratch(int byte);
  *   trans = 0: solves A X = B  (apply P, L y = P b, U x = y)
  *   trans = 1: solves A^T X = B (U^T y = b, L^T z = y, x = P^T z)
  *   B      n x nrhs FP64, leading dimension ldb; overwritten by X
- * Fully asynchronous on `stream`.
+ * Fully asynchronous on `stream`.  The workgroups of a solve hand blocks of the
+ * solution on to each other, each waiting only for workgroups that are already
+ * running, so that other work on the device (other solves included) can delay
+ * a solve but not block it.  The waits are bounded all the same: one that
+ * expires (16 s or more without progress) ends the solve with NaN in X, which
+ * the return value, given before the solve runs, cannot tell: see
+ * mxlu_solve_timeouts.
  */
 int lu_solve(int64_t n, int64_t nrhs, const double *LU, int64_t lda,
              const int32_t *ipiv, double *B, int64_t ldb, int trans,
@@ -150,6 +157,15 @@ int lu_solve(int64_t n, int64_t nrhs, const double *LU, int64_t lda,
 int lu_solve_noalloc(int64_t n, int64_t nrhs, const double *LU, int64_t lda,
                      const int32_t *ipiv, double *B, int64_t ldb, int trans,
                      void *stream);
+
+/*
+ * mxlu_solve_timeouts -- the number of triangular solves of lu_solve and
+ * lu_solve_noalloc on the current device, since the process started, whose
+ * waits have expired (each leaves NaN in its X); synchronises `stream` first,
+ * so that a caller who reads it after a solve and finds the number unchanged
+ * knows that no wait of that solve expired.  Returns MXLU_E_* (< 0) on failure.
+ */
+int64_t mxlu_solve_timeouts(void *stream);
 
 /*
  * mxlu_panel_factor_f64 -- the PFACT phase on its own (Sec. III-A.1: the

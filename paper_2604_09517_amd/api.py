@@ -102,7 +102,8 @@ def release():
 
 
 def debug_expire_waits(on):
-    """Test hook: panel factorizations start with their waits expired."""
+    """Test hook: panel factorizations start with their waits expired, and
+    those of lu_solve give up at their first check."""
     check("mxlu_debug_expire_waits", lib().mxlu_debug_expire_waits(1 if on else 0))
 
 
@@ -122,6 +123,15 @@ def lu_solve(LU, ipiv, B, trans=False):
     rc = lib().lu_solve(n, nrhs, pl, lda, pp, pb, ldb, 1 if trans else 0, _stream())
     check("lu_solve", rc)
     return B
+
+
+def solve_timeouts():
+    """Solves of lu_solve and lu_solve_noalloc on this device whose waits have
+    expired so far (each left NaN in its result); waits for the current stream."""
+    n = int(lib().mxlu_solve_timeouts(_stream()))
+    if n < 0:
+        check("mxlu_solve_timeouts", n)
+    return n
 
 
 def schur_update(C, A, B):

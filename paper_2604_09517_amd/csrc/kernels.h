@@ -118,11 +118,18 @@ int panel_factor(T *P, int64_t ldp, int64_t m, int64_t kb, int64_t ibase, int32_
 
 // perm[i] = original row at position i after the interchanges ipiv[0..n).
 int perm_from_ipiv(int64_t n, const int32_t *ipiv, int32_t *perm, hipStream_t s);
+// State of a chained solve on the device, cleared by each launch for itself:
+// blocks handed out, and whether a wait has expired.
+struct TriSync {
+    unsigned ticket, expired;
+};
 // A X = B (trans: A^T X = B) in place for nr <= 16 right-hand sides from the
-// factors LU and the gather map perm of their interchanges; E: n x nr doubles
-// of scratch (leading dimension lde).
+// factors LU and the gather map perm of their interchanges; scratch: E, n x nr
+// doubles (leading dimension lde), and *sync.
 int tri_solve_f64(int64_t n, int nr, const double *LU, int64_t lda, const int32_t *perm, double *B,
-                  int64_t ldb, int trans, double *E, int64_t lde, hipStream_t s);
+                  int64_t ldb, int trans, double *E, int64_t lde, TriSync *sync, hipStream_t s);
+// Solves of this kind on the current device whose waits have expired so far.
+int tri_timeouts(int64_t *count);
 
 // Streams of the mixed-precision factorization's look-ahead: `panel` factors
 // the next panel while the rest of the trailing update runs on the caller's

@@ -556,23 +556,26 @@ int solve_args(int64_t n, int64_t nrhs, const double *LU, int64_t lda, const int
     return 0;
 }
 
-// The solves of lu_solve with caller-provided device scratch: perm (n int32)
-// and Y (n x min(16, nrhs) doubles, leading dimension n).
+// The solves of lu_solve with caller-provided device scratch: perm (n int32),
+// Y (n x min(16, nrhs) doubles, leading dimension n) and *sync.
 int solve_impl(int64_t n, int64_t nrhs, const double *LU, int64_t lda, const int32_t *ipiv,
-               double *B, int64_t ldb, int trans, hipStream_t s, int32_t *perm, double *Y) {
+               double *B, int64_t ldb, int trans, hipStream_t s, int32_t *perm, double *Y,
+               TriSync *sync) {
     PhaseScope ph(kPhaseSolve, s, 8.0 * (double)n * (double)n);
     MXLU_TRY(perm_from_ipiv(n, ipiv, perm, s));
     for (int64_t r0 = 0; r0 < nrhs; r0 += 16)   // strips of at most 16 right-hand sides
         MXLU_TRY(tri_solve_f64(n, (int)std::min<int64_t>(16, nrhs - r0), LU, lda, perm,
-                               B + (size_t)r0 * (size_t)ldb, ldb, trans, Y, n, s));
+                               B + (size_t)r0 * (size_t)ldb, ldb, trans, Y, n, sync, s));
     return 0;
 }
 
-// Scratch of lu_solve_noalloc: Y (kNoAllocMaxN x 16 doubles) then perm
-// (kNoAllocMaxN int32), one copy per device, held until the process ends.
+// Scratch of lu_solve_noalloc: Y (kNoAllocMaxN x 16 doubles), perm
+// (kNoAllocMaxN int32) and the solves' state, one copy per device, held until
+// the process ends.
 constexpr int64_t kNoAllocMaxN = 65536;
 constexpr size_t kNoAllocYBytes = (size_t)kNoAllocMaxN * 16 * sizeof(double);
-constexpr size_t kNoAllocBytes = kNoAllocYBytes + (size_t)kNoAllocMaxN * sizeof(int32_t);
+constexpr size_t kNoAllocSync = kNoAllocYBytes + (size_t)kNoAllocMaxN * sizeof(int32_t);
+constexpr size_t kNoAllocBytes = kNoAllocSync + sizeof(TriSync);
 static __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
 
 std::mutex g_noalloc_mu;
@@ -607,10 +610,12 @@ extern "C" int lu_solve(int64_t n, int64_t nrhs, const double *LU, int64_t lda,
     clear_error();
     hipStream_t s = (hipStream_t)stream;
     Scratch scratch(s);
+    static_assert(sizeof(TriSync) == sizeof(double), "one allocation with Y");
     int32_t *perm = scratch.alloc_n<int32_t>((size_t)n);
-    double *Y = scratch.alloc_n<double>((size_t)n * (size_t)std::min<int64_t>(16, nrhs));
+    double *Y = scratch.alloc_n<double>((size_t)n * (size_t)std::min<int64_t>(16, nrhs) + 1);
     if (!perm || !Y) return MXLU_E_NOMEM;
-    return solve_impl(n, nrhs, LU, lda, ipiv, B, ldb, trans, s, perm, Y);
+    return solve_impl(n, nrhs, LU, lda, ipiv, B, ldb, trans, s, perm, Y + 1,
+                      reinterpret_cast<TriSync *>(Y));
 }
 
 extern "C" int lu_solve_noalloc(int64_t n, int64_t nrhs, const double *LU, int64_t lda,
@@ -628,7 +633,17 @@ extern "C" int lu_solve_noalloc(int64_t n, int64_t nrhs, const double *LU, int64
     MXLU_TRY(noalloc_scratch(&base));
     double *Y = static_cast<double *>(base);
     int32_t *perm = reinterpret_cast<int32_t *>(static_cast<unsigned char *>(base) + kNoAllocYBytes);
-    return solve_impl(n, nrhs, LU, lda, ipiv, B, ldb, trans, (hipStream_t)stream, perm, Y);
+    TriSync *sync = reinterpret_cast<TriSync *>(static_cast<unsigned char *>(base) + kNoAllocSync);
+    return solve_impl(n, nrhs, LU, lda, ipiv, B, ldb, trans, (hipStream_t)stream, perm, Y, sync);
+}
+
+extern "C" int64_t mxlu_solve_timeouts(void *stream) {
+    if (int rc = check_device()) return rc;
+    clear_error();
+    MXLU_HIP_TRY(hipStreamSynchronize((hipStream_t)stream));
+    int64_t count = 0;
+    MXLU_TRY(tri_timeouts(&count));
+    return count;
 }
 
 extern "C" int mxlu_schur_update_f64(int64_t M, int64_t N, int64_t K, const double *A,

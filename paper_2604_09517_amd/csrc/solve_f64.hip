@@ -59,18 +59,25 @@ __device__ __forceinline__ void wave_sync_lds() {
 // A solution value goes to `out` as one 64-bit word, written and read with
 // agent-scope relaxed atomics; the words start as kTriEmpty, a signalling NaN
 // that no arithmetic produces, and a reader polls a word until it holds
-// anything else, so no flags and fences are needed.  Workgroups wait only for
-// smaller ids, which are dispatched first, so the chain advances even when not
-// all are resident.  The polling is bounded: a wait that expires goes on with
-// NaN.
+// anything else, so no flags and fences are needed.  A workgroup takes its
+// block by an atomic ticket when it starts (about 1 us a launch), so that it
+// waits only for workgroups that have started and the chain advances however
+// many are resident: a workgroup fills a CU, and going by their ids two solves
+// on two streams could each fill an XCD and wait for a block of the other's.
+// The polling is bounded: a wait that expires goes on with NaN, sets *expired,
+// which ends the launch's other waits, and is counted (mxlu_solve_timeouts).
 // ---------------------------------------------------------------------------
 constexpr int kTriRows = 128;
 constexpr int kTriLd = 17;   // LDS row of 16 right-hand sides (odd: columns spread over the banks)
-constexpr uint64_t kTriEmpty = 0x7FF000005EED0001ull;
+constexpr uint64_t kTriEmpty = 0x7FF000005EED0001ull, kTriNaN = 0x7FF8000000000000ull;
+
+// launches whose waits have expired since the process started
+__device__ unsigned g_tri_timeouts;
 
 __global__ __launch_bounds__(256) void tri_clear_kernel(int64_t n, int nr, double *__restrict__ X,
-                                                        int64_t ldx) {
+                                                        int64_t ldx, mxlu::TriSync *__restrict__ sync) {
     const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i == 0) sync->ticket = sync->expired = 0;
     if (i >= n) return;
     for (int c = 0; c < nr; ++c)
         X[(size_t)i + (size_t)c * (size_t)ldx] = __longlong_as_double((long long)kTriEmpty);
@@ -85,7 +92,7 @@ template <int KIND>
 __global__ __launch_bounds__(512) void tri_chain_f64_kernel(
     int64_t n, int nr, const double *__restrict__ T, int64_t ldt, const double *in, int64_t ldin,
     const int32_t *__restrict__ inperm, double *out, int64_t ldo,
-    const int32_t *__restrict__ outperm, int nblk) {
+    const int32_t *__restrict__ outperm, int nblk, mxlu::TriSync *sync, int max_spins) {
     constexpr bool TR = KIND >= 2, FWD = KIND == 0 || KIND == 2, UNIT = KIND == 0 || KIND == 3;
     constexpr int BS = kTriRows, NS = BS / 16;
     __shared__ double Xs[2][BS][kTriLd];
@@ -94,10 +101,16 @@ __global__ __launch_bounds__(512) void tri_chain_f64_kernel(
     __shared__ __attribute__((aligned(16))) double Dg[NS][16][16];   // Dg[s][k][i] = F[16s+i][16s+k]
     __shared__ double Rd[BS];           // reciprocals of the diagonal
     __shared__ int s_range[NS];         // the strip's diagonal is in the normal range
+    __shared__ unsigned s_ticket;
     const int tid = threadIdx.x, lane = tid & 63;
     const int v = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 15, lq = lane >> 4;
-    const int w = blockIdx.x;
+    int w = 0;
+    if (nblk > 1) {
+        if (tid == 0) s_ticket = atomicAdd(&sync->ticket, 1u);
+        __syncthreads();
+        w = __builtin_amdgcn_readfirstlane((int)s_ticket);
+    }
     const int64_t r0 = (int64_t)(FWD ? w : nblk - 1 - w) * BS;
     // this lane's factor row: matrix row i stands for row 4 (i % 4) + i / 4 of
     // the strip, so that a quarter wave's accumulators are four rows in turn
@@ -142,6 +155,16 @@ __global__ __launch_bounds__(512) void tri_chain_f64_kernel(
         for (int e = 0; e < 4; ++e)
             xw[e] = (p0 + xr < n && xc + 4 * e < nr) ? tri_load(word(p0 + xr, xc + 4 * e)) : 0ull;
     };
+    // a wait gives up after max_spins looks (2^24: 16 s or more), or when another
+    // one has
+    auto give_up = [&](int spins) {
+        if (spins >= max_spins) {
+            if (atomicExch(&sync->expired, 1u) == 0) atomicAdd(&g_tri_timeouts, 1u);
+            return true;
+        }
+        return (spins & 1023) == 1023 && __hip_atomic_load(&sync->expired, __ATOMIC_RELAXED,
+                                                           __HIP_MEMORY_SCOPE_AGENT) != 0;
+    };
     // wait for them: one lane of the workgroup watches the word that appears
     // last, with long pauses, so that the many workgroups further down the
     // chain do not crowd the producer's stores; then every thread reads its
@@ -150,7 +173,7 @@ __global__ __launch_bounds__(512) void tri_chain_f64_kernel(
         if (tid == 0) {
             const int64_t last = FWD ? (p0 + BS < n ? p0 + BS - 1 : n - 1) : p0;
             const double *p = word(last, nr - 1);
-            for (int k = 0; k < (1 << 24) && tri_load(p) == kTriEmpty; ++k)   // about 16 s
+            for (int k = 0; tri_load(p) == kTriEmpty && !give_up(k); ++k)
                 __builtin_amdgcn_s_sleep(16);
         }
         __syncthreads();
@@ -163,8 +186,7 @@ __global__ __launch_bounds__(512) void tri_chain_f64_kernel(
 #pragma unroll
             for (int e = 0; e < 4; ++e)
                 if (xw[e] == kTriEmpty)
-                    xw[e] = rounds > 4096 ? 0x7FF8000000000000ull
-                                          : tri_load(word(p0 + xr, xc + 4 * e));
+                    xw[e] = give_up(rounds) ? kTriNaN : tri_load(word(p0 + xr, xc + 4 * e));
         }
     };
 
@@ -261,8 +283,7 @@ __global__ __launch_bounds__(512) void tri_chain_f64_kernel(
                     x = tri_load(p);
                     for (int spins = 0; x == kTriEmpty; ++spins) {
                         __builtin_amdgcn_s_sleep(1);
-                        x = tri_load(p);
-                        if (spins > (1 << 24)) x = 0x7FF8000000000000ull;   // about 16 s
+                        x = give_up(spins) ? kTriNaN : tri_load(p);
                     }
                 }
                 X[16 * s + sr][sc] = __longlong_as_double((long long)x);
@@ -368,13 +389,14 @@ __global__ __launch_bounds__(512) void tri_chain_f64_kernel(
 template <int KIND>
 int tri_chain(int64_t n, int nr, const double *T, int64_t ldt, const double *in, int64_t ldin,
               const int32_t *inperm, double *out, int64_t ldo, const int32_t *outperm,
-              hipStream_t s) {
+              mxlu::TriSync *sync, hipStream_t s) {
     const int64_t nblk = (n + kTriRows - 1) / kTriRows;
     hipLaunchKernelGGL(tri_clear_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, n, nr,
-                       out, ldo);
+                       out, ldo, sync);
     MXLU_LAUNCH_CHECK();
     hipLaunchKernelGGL(tri_chain_f64_kernel<KIND>, dim3((unsigned)nblk), dim3(512), 0, s, n, nr, T,
-                       ldt, in, ldin, inperm, out, ldo, outperm, (int)nblk);
+                       ldt, in, ldin, inperm, out, ldo, outperm, (int)nblk, sync,
+                       mxlu::g_expire_waits.load() ? 0 : 1 << 24);
     MXLU_LAUNCH_CHECK();
     return 0;
 }
@@ -384,19 +406,26 @@ int tri_chain(int64_t n, int nr, const double *T, int64_t ldt, const double *in,
 namespace mxlu {
 
 int tri_solve_f64(int64_t n, int nr, const double *LU, int64_t lda, const int32_t *perm, double *B,
-                  int64_t ldb, int trans, double *E, int64_t lde, hipStream_t s) {
+                  int64_t ldb, int trans, double *E, int64_t lde, TriSync *sync, hipStream_t s) {
     if (n <= 0 || nr <= 0) return 0;
     if (nr > 16) {
         set_error_msg("tri_solve_f64: more than 16 right-hand sides");
         return MXLU_E_NOMEM;
     }
     if (trans == 0) {   // L y = P b, U x = y
-        MXLU_TRY(tri_chain<0>(n, nr, LU, lda, B, ldb, perm, E, lde, nullptr, s));
-        return tri_chain<1>(n, nr, LU, lda, E, lde, nullptr, B, ldb, nullptr, s);
+        MXLU_TRY(tri_chain<0>(n, nr, LU, lda, B, ldb, perm, E, lde, nullptr, sync, s));
+        return tri_chain<1>(n, nr, LU, lda, E, lde, nullptr, B, ldb, nullptr, sync, s);
     }
     // U^T y = b, L^T z = y, x = P^T z
-    MXLU_TRY(tri_chain<2>(n, nr, LU, lda, B, ldb, nullptr, E, lde, nullptr, s));
-    return tri_chain<3>(n, nr, LU, lda, E, lde, nullptr, B, ldb, perm, s);
+    MXLU_TRY(tri_chain<2>(n, nr, LU, lda, B, ldb, nullptr, E, lde, nullptr, sync, s));
+    return tri_chain<3>(n, nr, LU, lda, E, lde, nullptr, B, ldb, perm, sync, s);
+}
+
+int tri_timeouts(int64_t *count) {
+    unsigned c = 0;
+    MXLU_HIP_TRY(hipMemcpyFromSymbol(&c, HIP_SYMBOL(g_tri_timeouts), sizeof(c)));
+    *count = c;
+    return 0;
 }
 
 }  // namespace mxlu

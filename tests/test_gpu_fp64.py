@@ -671,3 +671,86 @@ def test_lu_solve_small_quotients_correctly_rounded(api, trans, scale):
     api.lu_solve(to_dev(np.diag(d)), ipiv, dB, trans=bool(trans))
     torch.cuda.synchronize()
     assert np.array_equal(dB.cpu().numpy(), B_h / d[:, None])
+
+
+@pytest.mark.parametrize("noalloc", [False, True])
+@pytest.mark.parametrize("n,nrhs,trans", [(1024, 1, 0), (1000, 16, 1), (4100, 3, 0)])
+def test_expired_solve_waits_are_reported(api, n, nrhs, trans, noalloc):
+    """Forced from the host: every wait of the solve gives up at its first
+    check.  The solve runs to completion inside its arrays, leaves NaN and is
+    counted; the next solve is normal and not counted."""
+    note(f"expired solve waits n={n} nrhs={nrhs} trans={trans} noalloc={noalloc}")
+    LU = api.fortran_empty(n, n, ld=n + 2)
+    api.fill_uniform(LU, 3, inputs.STREAM_A)
+    LU.mul_(1.0 / n)
+    LU.diagonal().add_(1.0)
+    ipiv = torch.arange(n, dtype=torch.int32, device="cuda")
+    solve = api.lu_solve_noalloc if noalloc else api.lu_solve
+    pad = 512
+    buf = torch.full((pad + n * nrhs + pad,), 777.0, dtype=torch.float64, device="cuda")
+    B = buf[pad:pad + n * nrhs].view(nrhs, n).t()
+    B0 = api.fortran_empty(n, nrhs)
+    api.fill_uniform(B0, 3, inputs.STREAM_B)
+    ref = solve(LU, ipiv, B0.clone(), trans=bool(trans))
+    before = api.solve_timeouts()
+    B.copy_(B0)
+    api.debug_expire_waits(True)
+    try:
+        solve(LU, ipiv, B, trans=bool(trans))
+        torch.cuda.synchronize()
+    finally:
+        api.debug_expire_waits(False)
+    after = api.solve_timeouts()
+    assert after > before
+    assert torch.isnan(B).any()
+    assert torch.all(buf[:pad] == 777.0) and torch.all(buf[pad + n * nrhs:] == 777.0)
+    B.copy_(B0)
+    solve(LU, ipiv, B, trans=bool(trans))
+    assert api.solve_timeouts() == after
+    assert torch.equal(B, ref)
+
+
+def test_concurrent_solves(api):
+    """Solves on four streams from four threads at once, together more
+    workgroups than the device holds (each fills a CU): bit for bit the results
+    of the same solves one after the other, and no wait expires."""
+    import threading
+    n = 20000
+    note(f"concurrent solves n={n}")
+    LU = api.fortran_empty(n, n)
+    api.fill_uniform(LU, 5, inputs.STREAM_A)
+    LU.mul_(1.0 / n)
+    LU.diagonal().add_(1.0)
+    ipiv = torch.arange(n, dtype=torch.int32, device="cuda")
+    kinds = [(1, False), (16, True), (3, False), (5, True)]
+    rhs, ref = [], []
+    for k, (nrhs, trans) in enumerate(kinds):
+        b = api.fortran_empty(n, nrhs)
+        api.fill_uniform(b, 50 + k, inputs.STREAM_B)
+        rhs.append(b)
+        ref.append(api.lu_solve(LU, ipiv, b.clone(), trans=trans))
+    before = api.solve_timeouts()
+    out = [[b.clone() for _ in range(3)] for b in rhs]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in kinds]
+    errors = []
+
+    def work(k):
+        try:
+            with torch.cuda.stream(streams[k]):
+                for x in out[k]:
+                    api.lu_solve(LU, ipiv, x, trans=kinds[k][1])
+        except Exception as e:   # reported below, in the test's own thread
+            errors.append(e)
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(len(kinds))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert not errors
+    assert api.solve_timeouts() == before
+    for k in range(len(kinds)):
+        for x in out[k]:
+            assert torch.equal(x, ref[k])
