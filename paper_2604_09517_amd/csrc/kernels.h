@@ -118,6 +118,10 @@ int panel_factor(T *P, int64_t ldp, int64_t m, int64_t kb, int64_t ibase, int32_
 
 // perm[i] = original row at position i after the interchanges ipiv[0..n).
 int perm_from_ipiv(int64_t n, const int32_t *ipiv, int32_t *perm, hipStream_t s);
+// A chained solve with more workgroups than this, one for each XCD, hands its
+// blocks out by tickets (see tri_chain_f64_kernel).
+constexpr int kIdGroups = 8;
+
 // State of a chained solve on the device, cleared by each launch for itself:
 // blocks handed out, and whether a wait has expired.
 struct TriSync {

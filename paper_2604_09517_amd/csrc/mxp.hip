@@ -677,12 +677,13 @@ int mxp_impl(int64_t n, int64_t nrhs, const ASource &src, const double *B, int64
     c.v32 = scratch.alloc_n<float>((size_t)n);
     c.stats = scratch.alloc_n<unsigned long long>(8);
     c.ch.xs = scratch.alloc_n<uint64_t>((size_t)n);
-    c.ch.expired = scratch.alloc_n<int>(1);
+    c.ch.expired = scratch.alloc_n<int>(2);
+    c.ch.ticket = reinterpret_cast<unsigned *>(c.ch.expired + 1);
     if (!c.r || !c.z || !c.w || !c.V || !c.part || !c.apart || !c.dotp || !c.hdev || !c.v32 ||
         !c.stats || !c.ch.xs || !c.ch.expired)
         return MXLU_E_NOMEM;
     MXLU_HIP_TRY(hipMemsetAsync(c.ch.xs, 0, sizeof(uint64_t) * (size_t)n, s));
-    MXLU_HIP_TRY(hipMemsetAsync(c.ch.expired, 0, sizeof(int), s));
+    MXLU_HIP_TRY(hipMemsetAsync(c.ch.expired, 0, 2 * sizeof(int), s));
 
     Timer tr(s);
     tr.start();

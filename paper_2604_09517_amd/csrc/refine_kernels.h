@@ -35,11 +35,15 @@ int axpy_f64(int64_t n, const double *z, double *x, hipStream_t s);
 int absmax_f64(int64_t n, const double *v, unsigned long long *out, hipStream_t s);
 // State of the single-launch blocked triangular solves: xs holds n tagged
 // words (zeroed once at allocation), tag the last tag used (each solve takes
-// the next one), expired one device int set when a wait expires.
+// the next one), expired one device int set when a wait expires; *ticket
+// (zeroed once) counts the workgroups that have taken their place, tickets
+// those of the solves launched so far.
 struct TrsvChain {
     uint64_t *xs;
     int *expired;
     uint32_t tag;
+    unsigned *ticket;
+    unsigned tickets;
 };
 
 // d = M r (trans 0) or M^T r (trans 1) with M = U^-1 L^-1 P from the stored

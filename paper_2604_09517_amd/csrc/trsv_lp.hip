@@ -3,6 +3,7 @@
 #include <hip/hip_runtime.h>
 
 #include "common.h"
+#include "kernels.h"
 #include "lp_common.h"
 #include "refine_kernels.h"
 
@@ -54,10 +55,16 @@ using namespace mxlu;
 // float's bits and, in the upper half, the launch's tag; writers and readers
 // use agent-scope relaxed atomics and a reader polls each word until it
 // carries the tag, so no fences are needed.  Tags are unique per launch, so
-// words of earlier solves never match.  A workgroup waits only for workgroups
-// with smaller ids, which are dispatched first, so the chain always progresses
-// even when not all workgroups are resident.  The polling is bounded: on
-// expiry *expired is set and the solve completes with invalid values.
+// words of earlier solves never match.  A workgroup takes its place by an
+// atomic ticket when it starts (the counter runs on from launch to launch), so
+// that it waits only for workgroups that have started and the chain progresses
+// even when not all are resident (by their ids it need not: a workgroup fills a
+// CU, and each XCD starts its share of a launch on its own).  The ticket takes
+// 2 to 3 us; launches of at most kIdGroups, one on each XCD, go by ids, as it
+// would take more of them at once than the device has queues to fill an XCD (the
+// gradient of two GMRES solves of n = 1000 takes 3 % longer by tickets).  The
+// polling is bounded: on expiry *expired is set and the solve completes with
+// invalid values.
 constexpr int kStrip = 64;
 constexpr int kStrips = kTrsvBs / kStrip;   // strips (waves) of a workgroup
 static_assert(kStrips == 4, "one wave per SIMD");
@@ -93,7 +100,7 @@ __global__ __launch_bounds__(256) void trsv_chain_kernel(
     int64_t n, const uint16_t *__restrict__ F, int64_t ldf, const int32_t *__restrict__ perm,
     const double *__restrict__ r, float *__restrict__ v, double *__restrict__ d,
     const unsigned long long *__restrict__ smax, unsigned long long *smax_next, uint64_t *xs,
-    uint32_t tag, int nstrips, int *expired) {
+    uint32_t tag, int nstrips, int *expired, unsigned *ticket, unsigned first_ticket) {
     constexpr bool FWD = KIND == 0 || KIND == 2, UNIT = KIND == 0 || KIND == 3;
     constexpr bool COLS = KIND == 0 || KIND == 1;   // the factor's rows run along its columns
     constexpr bool FIRST = FWD;   // of the two solves
@@ -104,7 +111,13 @@ __global__ __launch_bounds__(256) void trsv_chain_kernel(
     __shared__ float xl[kStrips][kStrip];   // solutions of the own block
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int w = (int)blockIdx.x;
+    int w = (int)blockIdx.x;
+    if (gridDim.x > kIdGroups) {
+        __shared__ unsigned s_ticket;
+        if (threadIdx.x == 0) s_ticket = atomicAdd(ticket, 1u) - first_ticket;
+        __syncthreads();
+        w = __builtin_amdgcn_readfirstlane((int)s_ticket);
+    }
     const int S = kStrips * w + wave;
     const bool active = S < nstrips;
     auto base_of = [&](int s) { return (int64_t)kStrip * (FWD ? s : nstrips - 1 - s); };
@@ -430,10 +443,12 @@ int trsv_run(int64_t n, const uint16_t *F, int64_t ldf, const int32_t *perm, con
         return MXLU_E_NOMEM;
     }
     const uint32_t tag = ++ch.tag;
-    hipLaunchKernelGGL((trsv_chain_kernel<FMT, KIND>), dim3((unsigned)((nstrips + kStrips - 1) / kStrips)),
-                       dim3(256), 0, s, n, F, ldf, perm, r, v, d, smax, smax_next, ch.xs, tag,
-                       (int)nstrips, ch.expired);
+    const unsigned groups = (unsigned)((nstrips + kStrips - 1) / kStrips);
+    hipLaunchKernelGGL((trsv_chain_kernel<FMT, KIND>), dim3(groups), dim3(256), 0, s, n, F, ldf, perm, r,
+                       v, d, smax, smax_next, ch.xs, tag, (int)nstrips, ch.expired, ch.ticket,
+                       ch.tickets);
     MXLU_LAUNCH_CHECK();
+    if (groups > kIdGroups) ch.tickets += groups;   // (modulo 2^32, as the counter)
     return 0;
 }
 

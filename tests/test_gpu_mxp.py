@@ -812,3 +812,48 @@ def test_mxp_results_independent_of_workspace_contents(api, prec, pivot):
     if pivot:
         assert torch.equal(res[0][2], res[1][2])
     assert res[0][3:] == res[1][3:]
+
+
+def test_concurrent_mixed_precision_solves(api):
+    """Solves on three streams from three threads at once, forward and
+    transposed, whose preconditioners together have more workgroups than the
+    device holds (each fills a CU): bit for bit the results of the same solves
+    one after the other, and no wait expires (that would be an error)."""
+    import threading
+    n = 24576
+    note(f"concurrent mixed-precision solves n={n}")
+    A = api.fortran_empty(n, n)
+    api.fill_uniform(A, 9, inputs.STREAM_A)
+    api.make_diag_dominant(A)
+    b = api.fortran_empty(n, 1)[:, 0]
+    api.fill_uniform(b, 9, inputs.STREAM_B)
+    kinds = [dict(prec="bf16"), dict(prec="fp16", refine="classical"), dict(prec="bf16", trans=True)]
+    works, ref = [], []
+    for kw in kinds:
+        X, rep, work, _ = api.mxp_solve(A, b, nb=512, **kw)
+        works.append(work)
+        ref.append(api.mxp_solve(A, b, work=work, nb=512, reuse_factors=True, **kw)[0])
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in kinds]
+    out, errors = [[] for _ in kinds], []
+
+    def run(k):
+        try:
+            with torch.cuda.stream(streams[k]):
+                for _ in range(3):
+                    out[k].append(api.mxp_solve(A, b, work=works[k], nb=512, reuse_factors=True,
+                                                **kinds[k])[0])
+        except Exception as e:   # reported below, in the test's own thread
+            errors.append(e)
+
+    threads = [threading.Thread(target=run, args=(k,)) for k in range(len(kinds))]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    torch.cuda.synchronize()
+    assert not errors
+    for k in range(len(kinds)):
+        assert len(out[k]) == 3
+        for x in out[k]:
+            assert torch.equal(x, ref[k])
