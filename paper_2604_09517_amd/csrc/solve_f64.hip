@@ -60,10 +60,13 @@ __device__ __forceinline__ void wave_sync_lds() {
 // agent-scope relaxed atomics; the words start as kTriEmpty, a signalling NaN
 // that no arithmetic produces, and a reader polls a word until it holds
 // anything else, so no flags and fences are needed.  A workgroup takes its
-// block by an atomic ticket when it starts (about 1 us a launch), so that it
-// waits only for workgroups that have started and the chain advances however
-// many are resident: a workgroup fills a CU, and going by their ids two solves
-// on two streams could each fill an XCD and wait for a block of the other's.
+// block by an atomic ticket when it starts, so that it waits only for
+// workgroups that have started and the chain advances however many are
+// resident: a workgroup fills a CU, each XCD starts its share of a launch on its
+// own, and going by their ids two solves on two streams could each fill an XCD
+// and wait for a block of the other's.  The ticket takes 2 to 3 us of a launch;
+// launches of at most kIdGroups workgroups, one on each XCD, go by their ids: to
+// fill an XCD takes more of them at once than the device has queues.
 // The polling is bounded: a wait that expires goes on with NaN, sets *expired,
 // which ends the launch's other waits, and is counted (mxlu_solve_timeouts).
 // ---------------------------------------------------------------------------
@@ -105,8 +108,8 @@ __global__ __launch_bounds__(512) void tri_chain_f64_kernel(
     const int tid = threadIdx.x, lane = tid & 63;
     const int v = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int li = lane & 15, lq = lane >> 4;
-    int w = 0;
-    if (nblk > 1) {
+    int w = blockIdx.x;
+    if (nblk > mxlu::kIdGroups) {
         if (tid == 0) s_ticket = atomicAdd(&sync->ticket, 1u);
         __syncthreads();
         w = __builtin_amdgcn_readfirstlane((int)s_ticket);
