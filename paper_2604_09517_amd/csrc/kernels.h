@@ -35,7 +35,9 @@ struct PanelExchange {
     uint64_t *rowj;   // [2][kLeafW * 2] the current pivot row's old contents
     int *flags;       // [0]: first zero pivot (1-based), [1]: wait expired
     int group_cap;    // CUs a leaf may occupy (0: all); the LDS form puts one workgroup on each
+    int spin_limit;   // looks after which a wait gives up (kSpinLimit; 0 by the test hook)
 };
+constexpr int kSpinLimit = 1 << 22;
 constexpr int kLeafW = 32;        // columns factored by one leaf kernel
 constexpr int kMaxGroups = 256;   // workgroups of one leaf kernel (<= CUs)
 

@@ -108,7 +108,8 @@ template int panel_factor<double>(double *, int64_t, int64_t, int64_t, int64_t, 
 template int panel_factor<float>(float *, int64_t, int64_t, int64_t, int64_t, int32_t *,
                                  const PanelExchange &, hipStream_t);
 
-// Test hook (mxlu_debug_expire_waits): panel exchanges start expired.
+// Test hook (mxlu_debug_expire_waits): panel exchanges start expired and give up
+// at the first look.
 std::atomic<int> g_expire_waits{0};
 
 int alloc_panel_exchange(Scratch &scratch, int64_t n, PanelExchange *ex, hipStream_t s) {
@@ -118,13 +119,14 @@ int alloc_panel_exchange(Scratch &scratch, int64_t n, PanelExchange *ex, hipStre
     ex->rowj = scratch.alloc_n<uint64_t>(rowj_words);
     ex->flags = scratch.alloc_n<int>(4);
     ex->group_cap = 0;
+    ex->spin_limit = g_expire_waits.load() ? 0 : kSpinLimit;
     (void)n;
     if (!ex->slots || !ex->rowj || !ex->flags) return MXLU_E_NOMEM;
     // sequence number 0 is never current: zeroed words never match
     MXLU_HIP_TRY(hipMemsetAsync(ex->slots, 0, sizeof(uint64_t) * slot_words, s));
     MXLU_HIP_TRY(hipMemsetAsync(ex->rowj, 0, sizeof(uint64_t) * rowj_words, s));
     MXLU_HIP_TRY(hipMemsetAsync(ex->flags, 0, sizeof(int) * 4, s));
-    if (g_expire_waits.load())   // as if a wait had already expired
+    if (ex->spin_limit == 0)   // as if a wait had already expired
         MXLU_HIP_TRY(hipMemsetD32Async(reinterpret_cast<hipDeviceptr_t>(ex->flags + 1), 1, 1, s));
     return 0;
 }

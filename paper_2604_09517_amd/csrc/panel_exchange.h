@@ -49,21 +49,23 @@ __device__ __forceinline__ uint64_t ll_load(const uint64_t *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Bounded waiting, after `spins` looks: true when the caller has to give up.  Once
+// any wait has expired the results are invalid: later waits give up at their
+// first check (every `period` looks) instead of spinning.
+__device__ __forceinline__ bool ll_give_up(int spins, int limit, int period, int *flags) {
+    if (spins >= limit) {
+        atomicExch(&flags[1], 1);
+        return true;
+    }
+    return (spins & (period - 1)) == period - 1 &&
+           __hip_atomic_load(&flags[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+}
+
 // Payload of *p once it carries `seq`; x is a load of *p already issued.
-__device__ __forceinline__ uint32_t ll_wait(const uint64_t *p, uint64_t x, uint32_t seq,
+__device__ __forceinline__ uint32_t ll_wait(const uint64_t *p, uint64_t x, uint32_t seq, int limit,
                                            int *flags) {
-    long spins = 0;
-    while ((uint32_t)(x >> 32) != seq) {
-        if ((spins & 1023) == 1023) {
-            // once any wait has expired the results are invalid: later waits
-            // give up at their first check instead of spinning
-            if (__hip_atomic_load(&flags[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
-            if (spins > (1L << 22)) {
-                atomicExch(&flags[1], 1);
-                break;
-            }
-        }
-        ++spins;
+    for (int spins = 0; (uint32_t)(x >> 32) != seq; ++spins) {
+        if (ll_give_up(spins, limit, 1024, flags)) break;
         __builtin_amdgcn_s_sleep(1);
         x = ll_load(p);
     }
@@ -76,22 +78,14 @@ __device__ __forceinline__ uint32_t ll_wait(const uint64_t *p, uint64_t x, uint3
 // latency however many words are late; the loop is wave-uniform.
 template <int K, class Addr>
 __device__ __forceinline__ void ll_gather(uint64_t (&x)[K], uint32_t valid, Addr addr, uint32_t seq,
-                                          int *flags) {
-    long rounds = 0;
-    while (true) {
+                                          int limit, int *flags) {
+    for (int rounds = 0;; ++rounds) {
         uint32_t stale = 0;
 #pragma unroll
         for (int k = 0; k < K; ++k)
             if (((valid >> k) & 1u) && (uint32_t)(x[k] >> 32) != seq) stale |= 1u << k;
         if (__builtin_amdgcn_ballot_w64(stale != 0) == 0) break;
-        if ((rounds & 63) == 63) {
-            if (__hip_atomic_load(&flags[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) break;
-            if (rounds > (1L << 22)) {
-                atomicExch(&flags[1], 1);
-                break;
-            }
-        }
-        ++rounds;
+        if (ll_give_up(rounds, limit, 64, flags)) break;
         __builtin_amdgcn_s_sleep(1);
 #pragma unroll
         for (int k = 0; k < K; ++k)

@@ -57,7 +57,7 @@ constexpr int kWordsLds = (kOnePhaseGroups * kSlotWords > mxlu::kMaxGroups * 3)
 template <typename T>
 __global__ __launch_bounds__(256) void panel_leaf_kernel(
     int m, int w, T *__restrict__ P, int64_t lda, int R, int G, int64_t r0,
-    int32_t *__restrict__ ipiv, uint64_t *slots, uint64_t *rowj, int *flags) {
+    int32_t *__restrict__ ipiv, uint64_t *slots, uint64_t *rowj, int *flags, int limit) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     T *sp = reinterpret_cast<T *>(lds_raw);     // [w][R]
     // one-batch form: slot words of every group (slot layout); two-phase
@@ -154,7 +154,7 @@ __global__ __launch_bounds__(256) void panel_leaf_kernel(
                 }
                 valid |= (uint32_t)(lane < 2 * w) << kOneBatch;
                 x[kOneBatch] = (lane < 2 * w) ? ll_load(addr(kOneBatch)) : 0ull;
-                ll_gather(x, valid, addr, seq, flags);
+                ll_gather(x, valid, addr, seq, limit, flags);
 #pragma unroll
                 for (int k = 0; k < kOneBatch; ++k)
                     if ((valid >> k) & 1u) s_words[lane + 64 * k] = (uint32_t)x[k];
@@ -184,7 +184,7 @@ __global__ __launch_bounds__(256) void panel_leaf_kernel(
                     valid |= (uint32_t)use << k;
                     x[k] = use ? ll_load(addr(k)) : 0ull;
                 }
-                ll_gather(x, valid, addr, seq, flags);
+                ll_gather(x, valid, addr, seq, limit, flags);
 #pragma unroll
                 for (int k = 0; k < kCandPerLane; ++k)
                     if ((valid >> k) & 1u) s_words[lane + 64 * k] = (uint32_t)x[k];
@@ -197,10 +197,10 @@ __global__ __launch_bounds__(256) void panel_leaf_kernel(
             swap = (gv != 0.0) && gi != j;
             if (tid < 2 * w) {
                 const uint64_t *src = gs + (size_t)(gi / R) * kSlotWords + 4 + tid;
-                s_prow[tid] = ll_wait(src, ll_load(src), seq, flags);
+                s_prow[tid] = ll_wait(src, ll_load(src), seq, limit, flags);
             } else if (swap && tid >= 64 && tid < 64 + 2 * w) {
                 const uint64_t *src = &grj[tid - 64];
-                s_rowj[tid - 64] = ll_wait(src, ll_load(src), seq, flags);
+                s_rowj[tid - 64] = ll_wait(src, ll_load(src), seq, limit, flags);
             }
             __syncthreads();
             prow = s_prow;
@@ -283,7 +283,7 @@ struct RegLeafArgs {
     int64_t r0;
     int32_t *ipiv;
     uint64_t *slots, *rowj;
-    int *flags;
+    int *flags, limit;
 };
 
 template <int RPT>
@@ -417,7 +417,7 @@ __device__ __forceinline__ const uint32_t *reg_leaf_column(RegLeafState<RPT> &st
                 valid |= (uint32_t)use << k;
                 x[k] = use ? ll_load(addr(k)) : 0ull;
             }
-            ll_gather(x, valid, addr, seq, a.flags);
+            ll_gather(x, valid, addr, seq, a.limit, a.flags);
 #pragma unroll
             for (int k = 0; k < kOneBatch; ++k)
                 if ((valid >> k) & 1u) sh.words[lane + 64 * k] = (uint32_t)x[k];
@@ -432,7 +432,7 @@ __device__ __forceinline__ const uint32_t *reg_leaf_column(RegLeafState<RPT> &st
         swap = (gv != 0.0) && gi != J;
         if (swap && gi >= a.rb && gi < a.rb + a.rows && tid >= 64 && tid < 64 + 2 * w) {
             const uint64_t *src = &grj[tid - 64];
-            sh.rowj[tid - 64] = ll_wait(src, ll_load(src), seq, a.flags);
+            sh.rowj[tid - 64] = ll_wait(src, ll_load(src), seq, a.limit, a.flags);
         }
         __syncthreads();
     } else {
@@ -452,7 +452,7 @@ __device__ __forceinline__ const uint32_t *reg_leaf_column(RegLeafState<RPT> &st
                 valid |= (uint32_t)use << k;
                 x[k] = use ? ll_load(addr(k)) : 0ull;
             }
-            ll_gather(x, valid, addr, seq, a.flags);
+            ll_gather(x, valid, addr, seq, a.limit, a.flags);
 #pragma unroll
             for (int k = 0; k < kCandPerLane; ++k)
                 if ((valid >> k) & 1u) sh.words[lane + 64 * k] = (uint32_t)x[k];
@@ -465,10 +465,10 @@ __device__ __forceinline__ const uint32_t *reg_leaf_column(RegLeafState<RPT> &st
         swap = (gv != 0.0) && gi != J;
         if (tid < 2 * w) {
             const uint64_t *src = gs + (size_t)(gi / R) * kSlotWords + 4 + tid;
-            sh.prow[tid] = ll_wait(src, ll_load(src), seq, a.flags);
+            sh.prow[tid] = ll_wait(src, ll_load(src), seq, a.limit, a.flags);
         } else if (swap && gi >= a.rb && gi < a.rb + a.rows && tid >= 64 && tid < 64 + 2 * w) {
             const uint64_t *src = &grj[tid - 64];
-            sh.rowj[tid - 64] = ll_wait(src, ll_load(src), seq, a.flags);
+            sh.rowj[tid - 64] = ll_wait(src, ll_load(src), seq, a.limit, a.flags);
         }
         __syncthreads();
         prow = sh.prow;
@@ -537,7 +537,7 @@ __global__ __launch_bounds__(256) void panel_leaf_reg_kernel(int m, int w, doubl
                                                              int64_t lda, int G, int64_t r0,
                                                              int32_t *__restrict__ ipiv,
                                                              uint64_t *slots, uint64_t *rowj,
-                                                             int *flags) {
+                                                             int *flags, int limit) {
     constexpr int R = 256 * RPT;
     __shared__ RegLeafShared sh;
     RegLeafArgs a;
@@ -555,6 +555,7 @@ __global__ __launch_bounds__(256) void panel_leaf_reg_kernel(int m, int w, doubl
     a.slots = slots;
     a.rowj = rowj;
     a.flags = flags;
+    a.limit = limit;
     RegLeafState<RPT> st;
 #pragma unroll
     for (int q = 0; q < RPT; ++q)
@@ -731,7 +732,7 @@ int panel_leaf(int64_t m, int w, T *P, int64_t ldp, int64_t r0, int32_t *ipiv,
     if (form == kLeafReg2) {
         double *Pd = reinterpret_cast<double *>(P);
         hipLaunchKernelGGL(panel_leaf_reg_kernel<2>, dim3((unsigned)G), dim3(256), 0, s, (int)m, w,
-                           Pd, ldp, (int)G, r0, ipiv + r0, ex.slots, ex.rowj, ex.flags);
+                           Pd, ldp, (int)G, r0, ipiv + r0, ex.slots, ex.rowj, ex.flags, ex.spin_limit);
         MXLU_LAUNCH_CHECK();
         return 0;
     }
@@ -744,7 +745,7 @@ int panel_leaf(int64_t m, int w, T *P, int64_t ldp, int64_t r0, int32_t *ipiv,
         attr_set = true;
     }
     hipLaunchKernelGGL(panel_leaf_kernel<T>, dim3((unsigned)G), dim3(256), lds, s, (int)m, w, P,
-                       ldp, (int)R, (int)G, r0, ipiv + r0, ex.slots, ex.rowj, ex.flags);
+                       ldp, (int)R, (int)G, r0, ipiv + r0, ex.slots, ex.rowj, ex.flags, ex.spin_limit);
     MXLU_LAUNCH_CHECK();
     return 0;
 }

@@ -122,7 +122,7 @@ struct WideLeaf {
     static constexpr int KR = (mxlu::kWideMaxGroups + NW * GPL - 1) / (NW * GPL);
     T x[RPT][CW];    // register c: column (CB jb + c) % CW of the half in block jb
     int pos[RPT];    // the row's position in the interchanged leaf (-1: no row)
-    int m, w, G, g, tid, lane, wave;
+    int m, w, G, g, tid, lane, wave, limit;
     int64_t r0;
     uint64_t *slots;
     int *flags;
@@ -132,16 +132,8 @@ struct WideLeaf {
     __device__ __forceinline__ static bool stale(uint64_t t, uint32_t seq) {
         return (uint32_t)(t >> 32) != seq;
     }
-    // bounded waiting: true when the caller has to give up.  Once any wait has
-    // expired the results are invalid: later waits give up at their first check
-    __device__ __forceinline__ bool expired(long rounds) {
-        if ((rounds & 63) == 63) {
-            if (__hip_atomic_load(&flags[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return true;
-            if (rounds > (1L << 22)) {
-                atomicExch(&flags[1], 1);
-                return true;
-            }
-        }
+    __device__ __forceinline__ bool expired(int rounds) {
+        if (ll_give_up(rounds, limit, 64, flags)) return true;
         __builtin_amdgcn_s_sleep(1);
         return false;
     }
@@ -296,7 +288,7 @@ struct WideLeaf {
                 xw[k] = rg + GPL * NW * k < G && lane % RW < VW * (CW - CB * jb)
                             ? ll_load(pr + k * (GPL * NW * kSlotWords))
                             : none;
-            for (long rounds = 0;; ++rounds) {
+            for (int rounds = 0;; ++rounds) {
                 bool late = stale(hv0, seq) || stale(hv1, seq) || stale(hi, seq);
 #pragma unroll
                 for (int k = 0; k < KR; ++k) late = late || stale(xw[k], seq);
@@ -475,7 +467,7 @@ struct WideLeaf {
 #pragma unroll
             for (int e = 0; e < kPer; ++e) {
                 const int t = tid + NT * e;
-                for (long rounds = 0; stale(word[e], seq); ++rounds) {
+                for (int rounds = 0; stale(word[e], seq); ++rounds) {
                     if (expired(rounds)) break;
                     word[e] = ll_load(&area[t]);
                 }
@@ -533,7 +525,7 @@ struct WideLeaf {
 template <typename T, int NT, int RPT, int CW, bool EXCH>
 __global__ __launch_bounds__(NT) void panel_leaf_wide_kernel(int m, int w, T *P, int64_t lda, int G,
                                                              int64_t r0, int32_t *__restrict__ ipiv,
-                                                             uint64_t *slots, int *flags) {
+                                                             uint64_t *slots, int *flags, int limit) {
     __shared__ WideShared<T, NT, CW> sh;
     using Leaf = WideLeaf<T, NT, RPT, CW, EXCH>;
     Leaf s;
@@ -547,6 +539,7 @@ __global__ __launch_bounds__(NT) void panel_leaf_wide_kernel(int m, int w, T *P,
     s.r0 = r0;
     s.slots = slots;
     s.flags = flags;
+    s.limit = limit;
     // rows and columns past the leaf: others' values, never looked at (no load
     // is under a condition, so that all are in flight together)
     auto load = [&](int c0) {
@@ -654,7 +647,7 @@ int panel_leaf_wide(int64_t m, int w, T *P, int64_t ldp, int64_t r0, int32_t *ip
     *split = 0;
     auto launch = [&](auto kernel, int threads, int groups) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)groups), dim3((unsigned)threads), 0, s, (int)m, w, P, ldp,
-                           groups, r0, ipiv + r0, ex.slots, ex.flags);
+                           groups, r0, ipiv + r0, ex.slots, ex.flags, ex.spin_limit);
     };
     // A row per thread as long as one workgroup holds the rows so, then four
     // rows per thread: an exchange through memory costs about 2 us a column, a

@@ -754,3 +754,63 @@ def test_concurrent_solves(api):
     for k in range(len(kinds)):
         for x in out[k]:
             assert torch.equal(x, ref[k])
+
+
+# ------------------------------------------- leaf forms: stale words, special values
+def stale_case(api, m, cols, run):
+    """run(A, ipiv) with every wait giving up at its first look, in arrays with
+    guards around them; then again with normal waits.  Returns the pivots of
+    both and the status of the first."""
+    pad = 4096
+    buf = torch.full((pad + m * cols + pad,), 12345.0, dtype=torch.float64, device="cuda")
+    A = buf[pad:pad + m * cols].view(cols, m).t()
+    ibuf = torch.full((cols + 128,), -7, dtype=torch.int32, device="cuda")
+    ipiv = ibuf[64:64 + cols]
+    api.fill_uniform(A, 7, inputs.STREAM_A)
+    api.debug_expire_waits(True)
+    try:
+        rc = run(A, ipiv)
+        torch.cuda.synchronize()
+    finally:
+        api.debug_expire_waits(False)
+    stale = ipiv.cpu().numpy().copy()
+    assert torch.all(buf[:pad] == 12345.0) and torch.all(buf[pad + m * cols:] == 12345.0)
+    assert torch.all(ibuf[:64] == -7) and torch.all(ibuf[64 + cols:] == -7)
+    assert np.all(stale >= np.arange(cols)) and np.all(stale < m)
+    api.fill_uniform(A, 7, inputs.STREAM_A)
+    assert run(A, ipiv) == 0
+    return stale, ipiv.cpu().numpy(), rc
+
+
+@pytest.mark.parametrize("depth", [0, 1])
+def test_stale_exchange_words_factorization(api, depth):
+    """The leaves between workgroups (more than 2048 rows) on stale exchange
+    words, within a whole factorization: MXLU_E_TIMEOUT, every interchange a row
+    of the matrix, nothing outside the arrays; the pivots show that the
+    exchange did run on them (they are not the normal ones)."""
+    n, nb = 2304, 128
+    note(f"stale exchange words, factorization depth={depth}")
+    api.set_lookahead(depth)
+    try:
+        stale, piv, rc = stale_case(api, n, n, lambda A, ipiv: api.lib().lu_factor(
+            n, nb, A.data_ptr(), n, ipiv.data_ptr(), torch.cuda.current_stream().cuda_stream))
+    finally:
+        api.set_lookahead(1)
+    assert rc == -1005
+    assert not np.array_equal(stale, piv)
+    _, piv_ref, _ = oracle.getrf(inputs.uniform_matrix(7, inputs.STREAM_A, n, n), nb)
+    assert np.array_equal(piv, piv_ref)
+
+
+@pytest.mark.parametrize("m,nb", [(2100, 33), (4096, 32), (9000, 64), (20000, 49), (66000, 36)])
+def test_stale_exchange_words_panel(api, m, nb):
+    """The same for every form that exchanges: two rows per thread, four in
+    halves (whose second half polls the first one's pivot rows as well), and
+    above 65536 rows the two-row form and the rows in LDS (the four columns)."""
+    note(f"stale exchange words, panel m={m} nb={nb}")
+    stale, piv, rc = stale_case(api, m, nb, lambda P, ipiv: api.lib().mxlu_panel_factor_f64(
+        m, nb, P.data_ptr(), m, ipiv.data_ptr(), torch.cuda.current_stream().cuda_stream))
+    assert rc == -1005
+    assert not np.array_equal(stale, piv)
+    _, piv_ref, _ = oracle.panel_getrf(inputs.uniform_matrix(7, inputs.STREAM_A, m, nb))
+    assert np.array_equal(piv, piv_ref)
