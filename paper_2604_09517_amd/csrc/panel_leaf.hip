@@ -108,6 +108,8 @@ __global__ __launch_bounds__(256) void panel_leaf_kernel(
         idx = s_wi[0];
 #pragma unroll
         for (int k = 1; k < 4; ++k) argmax_merge(v, idx, s_wv[k], s_wi[k]);
+        // NaN alone: row j stands in, should no other group have a candidate
+        if (idx == INT_MAX && j >= rb && j < rb + rows) idx = j;
 
         // 2. publish
         uint64_t *mine = gs + (size_t)g * kSlotWords;
@@ -320,6 +322,8 @@ __device__ __forceinline__ void reg_leaf_candidate(RegLeafState<RPT> &st, const 
     idx = sh.wi[0];
 #pragma unroll
     for (int k = 1; k < 4; ++k) argmax_merge(v, idx, sh.wv[k], sh.wi[k]);
+    // NaN alone: row J stands in, should no other group have a candidate
+    if (idx == INT_MAX && J >= a.rb && J < a.rb + a.rows) idx = J;
     st.idx = idx;
     if (a.tid == 0) {
         const uint32_t seq = (uint32_t)(a.r0 + J + 1);

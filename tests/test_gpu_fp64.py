@@ -814,3 +814,42 @@ def test_stale_exchange_words_panel(api, m, nb):
     assert not np.array_equal(stale, piv)
     _, piv_ref, _ = oracle.panel_getrf(inputs.uniform_matrix(7, inputs.STREAM_A, m, nb))
     assert np.array_equal(piv, piv_ref)
+
+
+@pytest.mark.parametrize("kind", ["nan rows", "infinities", "nan column"])
+@pytest.mark.parametrize("m,nb", [(60, 32), (200, 32), (400, 32), (900, 32), (1500, 32), (3000, 32),
+                                  (9000, 32), (66000, 36)])
+def test_panel_leaf_special_values(api, m, nb, kind):
+    """A NaN is no candidate (the rows that hold some stay below the pivots
+    here, where the oracle agrees), an infinity is the largest, and a column of
+    NaN alone takes position j: pivots, NaNs and infinities of the oracle, the
+    other values within the 1e-12 of the tests above."""
+    note(f"panel leaf special values m={m} {kind}")
+    rng = np.random.default_rng(m)
+    P = rng.uniform(-1, 1, (m, nb))
+    rows = 40 + rng.permutation(m - 40)[:12]
+    if kind == "nan rows":
+        P[rows[:4], 3] = np.nan
+        P[rows[4:8], 19] = np.nan
+        P[rows[8], 0] = np.nan
+        P[rows[9], nb - 1] = np.nan
+    elif kind == "infinities":
+        P[rows[0], 4] = -np.inf
+        P[rows[1], 21] = np.inf
+        P[rows[2], 21] = -np.inf
+        P[rows[3], nb - 2] = np.inf
+    else:
+        P[:, 17] = np.nan
+    dP = to_dev(P)
+    _, ipiv, info = api.panel_factor(dP)
+    torch.cuda.synchronize()
+    with np.errstate(all="ignore"):
+        Pref, piv_ref, info_ref = oracle.panel_getrf(P)
+    got = dP.cpu().numpy()
+    assert info == info_ref
+    assert np.array_equal(ipiv.cpu().numpy(), piv_ref)
+    finite = np.isfinite(Pref)
+    assert np.array_equal(np.isnan(got), np.isnan(Pref))
+    assert np.array_equal(got[~finite], Pref[~finite], equal_nan=True)
+    d = np.abs(np.where(finite, got, 0.0) - np.where(finite, Pref, 0.0))
+    assert d.max() <= 1e-12 * max(1.0, np.abs(Pref[finite]).max())
