@@ -853,3 +853,36 @@ def test_panel_leaf_special_values(api, m, nb, kind):
     assert np.array_equal(got[~finite], Pref[~finite], equal_nan=True)
     d = np.abs(np.where(finite, got, 0.0) - np.where(finite, Pref, 0.0))
     assert d.max() <= 1e-12 * max(1.0, np.abs(Pref[finite]).max())
+
+
+@pytest.mark.parametrize("m,nb", [(1500, 32), (2048, 32), (9000, 32), (20000, 32), (66000, 36)])
+def test_panel_leaf_ties_and_zero_columns_tall(api, m, nb):
+    """Ties and exactly zero columns (5 repeats 2, 20 repeats 18) in the forms
+    with four rows per thread, in both halves, and in those above 65536 rows."""
+    rng = np.random.default_rng(m)
+    P = rng.integers(-1, 2, (m, nb)).astype(np.float64)
+    P[:, 5] = P[:, 2]
+    P[:, 20] = P[:, 18]
+    dP = to_dev(P)
+    _, ipiv, info = api.panel_factor(dP)
+    torch.cuda.synchronize()
+    Pref, piv_ref, info_ref = oracle.panel_getrf(P)
+    note(f"panel leaf ties m={m} info {info_ref}")
+    assert info == info_ref
+    assert np.array_equal(ipiv.cpu().numpy(), piv_ref)
+    assert np.abs(dP.cpu().numpy() - Pref).max() <= 1e-12 * max(1.0, np.abs(Pref).max())
+
+
+@pytest.mark.parametrize("m,nb", [(66000, 36), (70000, 7)])
+def test_panel_leaf_rows_in_lds_matches_oracle(api, m, nb):
+    """Leaves narrower than 32 columns above 65536 rows keep their rows in LDS:
+    pivots identical to the oracle's, values within 1e-12."""
+    note(f"panel leaf in LDS m={m} nb={nb}")
+    P = inputs.uniform_matrix(300 + nb, 0, m, nb)
+    dP = to_dev(P)
+    _, ipiv, info = api.panel_factor(dP)
+    torch.cuda.synchronize()
+    Pref, piv_ref, info_ref = oracle.panel_getrf(P)
+    assert info == info_ref == 0
+    assert np.array_equal(ipiv.cpu().numpy(), piv_ref)
+    assert np.abs(dP.cpu().numpy() - Pref).max() <= 1e-12 * max(1.0, np.abs(Pref).max())

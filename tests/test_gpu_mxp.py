@@ -857,3 +857,47 @@ def test_concurrent_mixed_precision_solves(api):
         assert len(out[k]) == 3
         for x in out[k]:
             assert torch.equal(x, ref[k])
+
+
+@pytest.mark.parametrize("n,nb", [(1100, 64), (2000, 32), (2500, 64), (9000, 64)])
+def test_fp32_pivoted_panel_forms_bitwise(api, n, nb):
+    """The first panel step of a pivoted FP32 factorization at sizes that take
+    the leaf's forms with four rows per thread in one workgroup (up to 2048
+    rows), two and four rows per thread with an exchange: pivots and the whole
+    partial factorization bit for bit the oracle's."""
+    note(f"fp32 pivoted panel n={n} nb={nb}")
+    A = inputs.uniform_matrix(517 + n, 0, n, n)
+    b = inputs.uniform_matrix(517 + n, 1, n, 1)[:, 0]
+    X, rep, work, ipiv = api.mxp_solve(to_dev(A), to_dev(b), prec="fp32", nb=nb, pivot=True,
+                                       max_outer=0, factor_steps=1, allow_notconv=True)
+    torch.cuda.synchronize()
+    F_ref, ipiv_ref, info = oracle.lp_getrf(A, nb, 4, pivot=True, max_steps=1)
+    assert rep["info"] == info == 0
+    assert np.array_equal(ipiv.cpu().numpy()[:nb], ipiv_ref[:nb])
+    assert np.array_equal(factors_to_host(api, work, n, "fp32"), F_ref)
+
+
+def test_fp32_pivoted_panel_rows_in_lds(api):
+    """Pivoted FP32 panels above 65536 rows keep their rows in LDS: the pivots
+    of the first panel of a generated matrix against elimination in FP32, and
+    its values within 64 units of 2^-24 (32 terms, each rounded twice)."""
+    n, nb, seed = 66000, 32, 77
+    note(f"fp32 pivoted panel in LDS n={n}")
+    b = api.fortran_empty(n, 1)[:, 0]
+    api.fill_uniform(b, seed, inputs.STREAM_B)
+    X, rep, work, ipiv = api.mxp_solve_seeded(n, seed, inputs.STREAM_A, b, dominant=False,
+                                              prec="fp32", nb=nb, pivot=True, max_outer=0,
+                                              factor_steps=1, allow_notconv=True)
+    torch.cuda.synchronize()
+    assert rep["info"] == 0
+    P = inputs.uniform_matrix(seed, inputs.STREAM_A, n, nb).astype(np.float32)
+    piv = np.empty(nb, dtype=np.int64)
+    for j in range(nb):
+        p = j + int(np.argmax(np.abs(P[j:, j])))
+        piv[j] = p
+        P[[j, p]] = P[[p, j]]
+        P[j + 1:, j] /= P[j, j]
+        P[j + 1:, j + 1:] -= np.outer(P[j + 1:, j], P[j, j + 1:])
+    got = api.mxp_factors(work, n, "fp32")[:, :nb].cpu().numpy()
+    assert np.array_equal(ipiv.cpu().numpy()[:nb], piv)
+    assert np.abs(got - P).max() <= 64 * 2.0 ** -24 * np.abs(P).max()
