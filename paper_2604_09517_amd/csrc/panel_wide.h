@@ -19,16 +19,16 @@
 //     triangular solve, then one product per thread and row) and is factored
 //     like the first.  The first half's columns are left to the caller's
 //     interchanges for those of the second half (panel_leaf_swap).
-//   * branches are dearer than multiply-adds: a row's update is one masked
-//     region, no load is under a condition.
+//   * no load is under a condition, and rows are updated four columns a masked
+//     region.
 //   * up to 2048 rows: one workgroup, no exchange through memory.  Two LDS
 //     barriers per column: the waves' candidates (value, position) meet in
 //     LDS, every wave picks the winner and divides while the winner's wave
 //     writes its row.
 //   * more rows: one exchange round trip per column.  The group's candidate
 //     row goes out with its position; every wave reads all groups' candidates
-//     (a lane per group) and picks the winner itself, and in the same batch a
-//     quarter of the rows, so that no second, dependent read of the winner's
+//     (a lane per group) and picks the winner itself, and in the same batch
+//     its share of the rows, so that no second, dependent read of the winner's
 //     row follows.
 //   * the columns are unrolled four at a time: after each four the row's
 //     registers are renamed by a rotation, which keeps every register index a
@@ -39,13 +39,12 @@
 // its lane by ballot; only ties in the upper word take the full comparison.
 //
 // A leaf of 32 FP64 columns with 64 / 256 / 512 / 1024 / 1500 / 2048 / 4096 /
-// 8192 / 16384 / 32768 rows takes 22 / 30 / 36 / 51 / 67 / 72 / 103 / 112 / 130
-// / 150 us.  All in halves above 256 rows, with an exchange from 1025 rows on
-// and a masked region for every four columns of a row it was 35 / 36 / 54 / 58 /
-// 124 / 124 / 130 / 132 / 132 / 149; as 32 workgroups or more with two exchange
-// rounds per column 123 us up to 4096 rows, 145 and 160 us.  The interchanges
-// that follow take 5.8 us in one launch; composing and applying them in two
-// took 12 to 16 us.
+// 8192 / 16384 / 32768 rows takes 22 / 31 / 37 / 53 / 67 / 72 / 91 / 98 / 120 /
+// 145 us.  All in halves above 256 rows and with an exchange from 1025 rows on it
+// was 35 / 36 / 54 / 58 / 124 / 124 / 130 / 132 / 132 / 149; as 32 workgroups or
+// more with two exchange rounds per column 123 us up to 4096 rows, 145 and 160
+// us.  The interchanges that follow take 5.8 us in one launch; composing and
+// applying them in two took 12 to 16 us.
 #pragma once
 
 #include "common.h"
@@ -356,44 +355,36 @@ struct WideLeaf {
         asm volatile("" : "+v"(ul));   // read by every lane, not by those of a masked region below
         // Rows up to position J are final: not even a multiple by zero, which
         // an infinity in the pivot row would turn into NaN.
-        if constexpr (RPT <= 2) {
-            // one masked region per row with the columns inside (a region per
-            // four columns spent more on its branches than on the arithmetic)
+        // The row's values are read by all lanes, outside the masked regions (a
+        // region per row and four columns): inside one, what the masked lanes
+        // hold would be the register allocator's to choose.  A region per row
+        // over all columns with the reads inside took 21 / 30 / 35 / 51 us at 64
+        // / 256 / 512 / 1024 rows, now 22 / 31 / 37 / 53, and 102 / 111 at 4096 /
+        // 8192, now 91 / 98; with all columns read ahead of it 25 / 32 / 37 / 53
+        // and 94 / 102 (scalar registers spill).
+        bool below[RPT], some = false;
+#pragma unroll
+        for (int q = 0; q < RPT; ++q) {
+            below[q] = pos[q] > J;
+            some = some || below[q];
+            x[q][JL] = below[q] ? l[q] : x[q][JL];
+        }
+        if (__builtin_amdgcn_ballot_w64(some) == 0) return;   // uniform: no row of the wave's
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            if (k >= NB - jb) break;   // finished columns (uniform)
+            T u[CB];
+#pragma unroll
+            for (int c = 0; c < CB; ++c)
+                if (CB * k + c > JL) u[c] = lane_value(ul, CB * k + c);
 #pragma unroll
             for (int q = 0; q < RPT; ++q)
-                if (pos[q] > J) {
-                    x[q][JL] = l[q];
+                if (below[q]) {
 #pragma unroll
-                    for (int k = 0; k < NB; ++k) {
-                        if (k >= NB - jb) break;   // finished columns (uniform)
-#pragma unroll
-                        for (int c = CB * k; c < CB * k + CB; ++c)
-                            if (c > JL) x[q][c] = fma(-l[q], lane_value(ul, c), x[q][c]);
-                    }
+                    for (int c = 0; c < CB; ++c)
+                        if (CB * k + c > JL)
+                            x[q][CB * k + c] = fma(-l[q], u[c], x[q][CB * k + c]);
                 }
-        } else {
-            bool below[RPT];
-#pragma unroll
-            for (int q = 0; q < RPT; ++q) {
-                below[q] = pos[q] > J;
-                x[q][JL] = below[q] ? l[q] : x[q][JL];
-            }
-#pragma unroll
-            for (int k = 0; k < NB; ++k) {
-                if (k >= NB - jb) break;   // finished columns (uniform)
-                T u[CB];
-#pragma unroll
-                for (int c = 0; c < CB; ++c)
-                    if (CB * k + c > JL) u[c] = lane_value(ul, CB * k + c);
-#pragma unroll
-                for (int q = 0; q < RPT; ++q)
-                    if (below[q]) {
-#pragma unroll
-                        for (int c = 0; c < CB; ++c)
-                            if (CB * k + c > JL)
-                                x[q][CB * k + c] = fma(-l[q], u[c], x[q][CB * k + c]);
-                    }
-            }
         }
     }
 
@@ -653,9 +644,9 @@ int panel_leaf_wide(int64_t m, int w, T *P, int64_t ldp, int64_t r0, int32_t *ip
     // rows per thread: an exchange through memory costs about 2 us a column, a
     // second wave on every SIMD a quarter, the halves another (2048 rows in
     // one workgroup 72 us, in two 124).  Beyond, two rows per thread with all
-    // columns at once (4096 / 8192 / 16384 / 32768 rows 103 / 112 / 132 / 172
+    // columns at once (4096 / 8192 / 16384 / 32768 rows 90 / 97 / 116 / 159
     // us) as long as the groups whose rows every wave polls are few, else four
-    // rows in halves, whose rows are half as long (115 / 120 / 130 / 150).
+    // rows in halves, whose rows are half as long (106 / 105 / 118 / 145).
     if (m <= 64) launch(panel_leaf_wide_kernel<T, 64, 1, 32, false>, 64, 1);
     else if (m <= 256) launch(panel_leaf_wide_kernel<T, 256, 1, 32, false>, 256, 1);
     else if (m <= 512) launch(panel_leaf_wide_kernel<T, 512, 1, 32, false>, 512, 1);
