@@ -314,11 +314,14 @@ int gemm_f64_sub(int64_t M, int64_t N, int64_t K, const double *A, int64_t lda,
         set_error_msg("gemm_f64_sub: grid too large");
         return MXLU_E_NOMEM;
     }
-    // fewer columns than a tile, or fewer tiles than CUs: 64 x 64 tiles (N = K
-    // = 32, 4000 rows 17 -> 4.9 us; 970 x 970, K = 64 29 -> 10.5; with more
-    // tiles the larger ones win, 2500 x 2500, K = 256 at 32 against 23
-    // TFLOP/s)
-    if (N <= 128 || tiles_m * tiles_n < 256)
+    // 64 x 64 tiles for fewer columns than a tile (N = K = 32, 4000 rows 17 -> 4.9
+    // us), and where the large ones leave CUs idle: a round of 256 large tiles
+    // takes as long as 3.7 of 256 small ones, so up to three of those (K = 512,
+    // us, large / small: 1408 x 1408 89 / 54, 1664 x 1664 90 / 75, 1790 x 1790
+    // 92 / 98, 256 x 14000 92 / 99; K = 64: 18.1 / 12.9, 18.4 / 17.3, 19.9 /
+    // 23.2).
+    const int64_t small = ((M + 63) / 64) * ((N + 63) / 64);
+    if (N <= 128 || (tiles_m * tiles_n < 256 && small <= 768))
         return gemm_panel_sub<double>(M, N, K, A, lda, B, ldb, C, ldc, s);
     const dim3 grid((unsigned)(tiles_m * tiles_n));
     hipLaunchKernelGGL((gemm_f64_sub_kernel<false, false>), grid, dim3(256), 0, s, M, N, K, A, lda, B,

@@ -886,3 +886,19 @@ def test_panel_leaf_rows_in_lds_matches_oracle(api, m, nb):
     assert info == info_ref == 0
     assert np.array_equal(ipiv.cpu().numpy(), piv_ref)
     assert np.abs(dP.cpu().numpy() - Pref).max() <= 1e-12 * max(1.0, np.abs(Pref).max())
+
+
+@pytest.mark.parametrize("M,N,K", [(1664, 1660, 19), (1700, 1900, 36), (1793, 1793, 17), (250, 13000, 20)])
+def test_schur_update_tile_choice(api, M, N, K):
+    """Both sides of the choice between small and large tiles where the large
+    ones are fewer than the CUs: integer data, so that the result is exactly C -
+    A B whatever the order."""
+    note(f"schur tile choice M={M} N={N} K={K}")
+    rng = np.random.default_rng(M + N + K)
+    A = rng.integers(-8, 9, (M, K)).astype(np.float64)
+    B = rng.integers(-8, 9, (K, N)).astype(np.float64)
+    C = rng.integers(-8, 9, (M, N)).astype(np.float64)
+    dC = to_dev(C, ld=M + 1)
+    api.schur_update(dC, to_dev(A), to_dev(B))
+    torch.cuda.synchronize()
+    assert np.array_equal(dC.cpu().numpy(), C - A @ B)
