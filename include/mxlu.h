@@ -360,8 +360,8 @@ int mxlu_profile_read(double *ms, double *work, int64_t *count, int nphase);
 int64_t mxlu_profile_intervals(int phase, int64_t *step, double *ms, double *work, int64_t cap);
 
 /*
- * Planning helpers: host arithmetic only (no device access), the rules the
- * library applies with the current device's facts; exposed for tests.
+ * Planning helpers: host arithmetic only (no device access), the rules by
+ * which the library plans with the current device's facts; exposed for tests.
  *   mxlu_plan_panel_cus: CUs given to the look-ahead's panel stream on a
  *     device with `cus` CUs: cus / 4 when that is a multiple of 32 (an equal
  *     number in every shader engine of an 8-XCD, 4-engine-per-XCD part),
@@ -373,7 +373,10 @@ int64_t mxlu_profile_intervals(int phase, int64_t *step, double *ms, double *wor
  *     elem_bytes (4 or 8; the register forms are FP64 only).  Returns
  *     1 or 2 (register form, rows per thread), 3 (LDS form), 0 (no form
  *     fits: the call would fail with MXLU_E_NOMEM), -1 (bad argument);
- *     *rows_per_group and *groups receive the geometry.
+ *     *rows_per_group and *groups receive the geometry.  Look-ahead is planned
+ *     by these forms; leaves of up to 65536 rows and 1024 per usable CU are
+ *     launched in a form of their own (1024 rows per group and CU, one group up
+ *     to 2048 rows), taller ones in form 2 or 3.
  *   mxlu_plan_lookahead: CUs of the panel stream when lu_factor(n, nb) runs
  *     look-ahead depth 1 on such a device (given 16-byte aligned A and even
  *     lda), else 0.

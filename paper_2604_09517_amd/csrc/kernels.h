@@ -41,10 +41,6 @@ constexpr int kSpinLimit = 1 << 22;
 constexpr int kLeafW = 32;        // columns factored by one leaf kernel
 constexpr int kMaxGroups = 256;   // workgroups of one leaf kernel (<= CUs)
 
-// Workgroups the leaf kernel launches for an m-row leaf with group cap `cap`
-// (they must all be resident at once), or -1 when no geometry fits.
-template <typename T> int panel_leaf_groups(int64_t m, int cap);
-
 // Inputs of the leaf planner: the CUs the leaf may use (cap > 0: that many,
 // else all `cus`), workgroups of the register form per CU (0: form not
 // available), dynamic LDS per workgroup of the LDS form, element size.

@@ -19,11 +19,9 @@ namespace {
 //   1. local candidate: first row >= j of largest |a_ij| in the group;
 //   2. publish the candidate (|a|, row) and its whole leaf row and, by the
 //      owner, row j itself;
-//   3. gather (wave 0 of each group; fewer pollers on the same lines): with
-//      at most kOnePhaseGroups groups all candidates and candidate rows in
-//      one batch of loads, otherwise the candidates first and then only the
-//      winner's row.  Every wave reduces the G candidates to the same
-//      winner p;
+//   3. gather (wave 0 of each group; fewer pollers on the same lines): the
+//      candidates first, then only the winner's row.  Every wave reduces the G
+//      candidates to the same winner p;
 //   4. the owner threads of rows j and p swap those rows (whole leaf rows);
 //   5. every thread divides column j of its rows > j by the pivot and
 //      applies the rank-1 update to their columns > j.
@@ -33,7 +31,7 @@ namespace {
 // it carries the current sequence number.  A word is atomic, so its payload
 // is the one written with that number: no fences and no separate flag are
 // needed.  Every load of a phase is issued before the first wait, so a
-// column costs one round trip (two for many groups).  Buffers are
+// column costs two round trips.  Buffers are
 // double-buffered by the parity of j: a group overwrites its words of column
 // j only after it has gathered every candidate of column j-1, which every
 // group publishes only after it has finished reading column j-2.  Sequence
@@ -46,13 +44,9 @@ namespace {
 // high), the row index, one unused word and the candidate's leaf row (two
 // words per value); `rowj` is [2][kRowWords].
 // ---------------------------------------------------------------------------
-constexpr int kOnePhaseGroups = 8;               // one-batch gather up to this many groups
 // the gathers are done by wave 0 alone: fewer pollers on the same lines
-constexpr int kOneBatch = (kOnePhaseGroups * kSlotWords + 63) / 64;
 constexpr int kCandPerLane = (mxlu::kMaxGroups * 3 + 63) / 64;
-constexpr int kWordsLds = (kOnePhaseGroups * kSlotWords > mxlu::kMaxGroups * 3)
-                              ? kOnePhaseGroups * kSlotWords
-                              : mxlu::kMaxGroups * 3;
+constexpr int kWordsLds = mxlu::kMaxGroups * 3;
 
 template <typename T>
 __global__ __launch_bounds__(256) void panel_leaf_kernel(
@@ -60,10 +54,8 @@ __global__ __launch_bounds__(256) void panel_leaf_kernel(
     int32_t *__restrict__ ipiv, uint64_t *slots, uint64_t *rowj, int *flags, int limit) {
     extern __shared__ __attribute__((aligned(16))) unsigned char lds_raw[];
     T *sp = reinterpret_cast<T *>(lds_raw);     // [w][R]
-    // one-batch form: slot words of every group (slot layout); two-phase
-    // form: the 3 candidate words of every group, then the winner's row
-    __shared__ uint32_t s_words[kWordsLds];
-    __shared__ uint32_t s_prow[kRowWords];
+    __shared__ uint32_t s_words[kWordsLds];   // the 3 candidate words of every group
+    __shared__ uint32_t s_prow[kRowWords];    // the winner's row
     __shared__ uint32_t s_rowj[kRowWords];
     __shared__ double s_wv[4];
     __shared__ int s_wi[4];
@@ -72,7 +64,6 @@ __global__ __launch_bounds__(256) void panel_leaf_kernel(
     const int lane = tid & 63, wave = tid >> 6;
     const int rb = g * R;
     const int rows = min(R, m - rb);
-    const bool one_phase = G <= kOnePhaseGroups;
     auto word_double = [](const uint32_t *q) {
         return __longlong_as_double((long long)(((uint64_t)q[1] << 32) | q[0]));
     };
@@ -135,78 +126,40 @@ __global__ __launch_bounds__(256) void panel_leaf_kernel(
         // 3. gather
         double gv = -1.0;
         int gi = INT_MAX;
-        const uint32_t *prow;
-        bool swap;
-        if (one_phase) {
-            // every slot word in use, and row j, in one batch
-            const int nw = G * kSlotWords;
-            if (wave == 0) {
-                // word k < kOneBatch: slot word lane + 64 k; word kOneBatch: row j
-                uint64_t x[kOneBatch + 1];
-                uint32_t valid = 0;
-                auto addr = [&](int k) -> const uint64_t * {
-                    return k < kOneBatch ? &gs[lane + 64 * k] : &grj[lane];
-                };
+        // the candidates first, then the winner's row (and row j when it moves)
+        const int nc = G * 3;
+        if (wave == 0) {
+            uint64_t x[kCandPerLane];
+            uint32_t valid = 0;
+            auto addr = [&](int k) -> const uint64_t * {
+                const int t = lane + 64 * k;
+                return &gs[(t / 3) * kSlotWords + t % 3];
+            };
 #pragma unroll
-                for (int k = 0; k < kOneBatch; ++k) {
-                    const int t = lane + 64 * k, u = t % kSlotWords;
-                    const bool use = t < nw && u != 3 && u < 4 + 2 * w;
-                    valid |= (uint32_t)use << k;
-                    x[k] = use ? ll_load(addr(k)) : 0ull;
-                }
-                valid |= (uint32_t)(lane < 2 * w) << kOneBatch;
-                x[kOneBatch] = (lane < 2 * w) ? ll_load(addr(kOneBatch)) : 0ull;
-                ll_gather(x, valid, addr, seq, limit, flags);
-#pragma unroll
-                for (int k = 0; k < kOneBatch; ++k)
-                    if ((valid >> k) & 1u) s_words[lane + 64 * k] = (uint32_t)x[k];
-                if (lane < 2 * w) s_rowj[lane] = (uint32_t)x[kOneBatch];
+            for (int k = 0; k < kCandPerLane; ++k) {
+                const bool use = lane + 64 * k < nc;
+                valid |= (uint32_t)use << k;
+                x[k] = use ? ll_load(addr(k)) : 0ull;
             }
-            __syncthreads();
-            for (int t = lane; t < G; t += 64)
-                argmax_merge(gv, gi, word_double(&s_words[t * kSlotWords]),
-                             (int)s_words[t * kSlotWords + 2]);
-            wave_argmax(gv, gi);
-            if (gi < j || gi >= m) gi = j;   // expired wait only (see below)
-            prow = &s_words[(gi / R) * kSlotWords + 4];
-            swap = (gv != 0.0) && gi != j;
-        } else {
-            // the candidates first, then the winner's row (and row j when it moves)
-            const int nc = G * 3;
-            if (wave == 0) {
-                uint64_t x[kCandPerLane];
-                uint32_t valid = 0;
-                auto addr = [&](int k) -> const uint64_t * {
-                    const int t = lane + 64 * k;
-                    return &gs[(t / 3) * kSlotWords + t % 3];
-                };
+            ll_gather(x, valid, addr, seq, limit, flags);
 #pragma unroll
-                for (int k = 0; k < kCandPerLane; ++k) {
-                    const bool use = lane + 64 * k < nc;
-                    valid |= (uint32_t)use << k;
-                    x[k] = use ? ll_load(addr(k)) : 0ull;
-                }
-                ll_gather(x, valid, addr, seq, limit, flags);
-#pragma unroll
-                for (int k = 0; k < kCandPerLane; ++k)
-                    if ((valid >> k) & 1u) s_words[lane + 64 * k] = (uint32_t)x[k];
-            }
-            __syncthreads();
-            for (int t = lane; t < G; t += 64)
-                argmax_merge(gv, gi, word_double(&s_words[3 * t]), (int)s_words[3 * t + 2]);
-            wave_argmax(gv, gi);
-            if (gi < j || gi >= m) gi = j;   // expired wait only (see below)
-            swap = (gv != 0.0) && gi != j;
-            if (tid < 2 * w) {
-                const uint64_t *src = gs + (size_t)(gi / R) * kSlotWords + 4 + tid;
-                s_prow[tid] = ll_wait(src, ll_load(src), seq, limit, flags);
-            } else if (swap && tid >= 64 && tid < 64 + 2 * w) {
-                const uint64_t *src = &grj[tid - 64];
-                s_rowj[tid - 64] = ll_wait(src, ll_load(src), seq, limit, flags);
-            }
-            __syncthreads();
-            prow = s_prow;
+            for (int k = 0; k < kCandPerLane; ++k)
+                if ((valid >> k) & 1u) s_words[lane + 64 * k] = (uint32_t)x[k];
         }
+        __syncthreads();
+        for (int t = lane; t < G; t += 64)
+            argmax_merge(gv, gi, word_double(&s_words[3 * t]), (int)s_words[3 * t + 2]);
+        wave_argmax(gv, gi);
+        if (gi < j || gi >= m) gi = j;   // expired wait only (see below)
+        const bool swap = (gv != 0.0) && gi != j;
+        if (tid < 2 * w) {
+            const uint64_t *src = gs + (size_t)(gi / R) * kSlotWords + 4 + tid;
+            s_prow[tid] = ll_wait(src, ll_load(src), seq, limit, flags);
+        } else if (swap && tid >= 64 && tid < 64 + 2 * w) {
+            const uint64_t *src = &grj[tid - 64];
+            s_rowj[tid - 64] = ll_wait(src, ll_load(src), seq, limit, flags);
+        }
+        __syncthreads();
         // gi is a valid row >= j (the group holding row j has a candidate);
         // only after an expired wait (stale words) could it have left [j, m),
         // and it was then replaced by j above, so no index leaves the panel
@@ -220,12 +173,12 @@ __global__ __launch_bounds__(256) void panel_leaf_kernel(
         // 4. swap (owner threads of rows j and p, whole leaf rows)
         if (swap) {
             if (j >= rb && j < rb + rows && ((j - rb) & 255) == tid)
-                for (int c = 0; c < w; ++c) sp[c * R + (j - rb)] = (T)word_double(&prow[2 * c]);
+                for (int c = 0; c < w; ++c) sp[c * R + (j - rb)] = (T)word_double(&s_prow[2 * c]);
             if (p >= rb && p < rb + rows && ((p - rb) & 255) == tid)
                 for (int c = 0; c < w; ++c) sp[c * R + (p - rb)] = (T)word_double(&s_rowj[2 * c]);
         }
         // 5. scale and rank-1 update of the own rows below the pivot
-        const T piv = (T)word_double(&prow[2 * j]);
+        const T piv = (T)word_double(&s_prow[2 * j]);
         for (int i = tid; i < rows; i += 256) {
             if (rb + i > j) {
                 T l = sp[j * R + i];
@@ -234,7 +187,7 @@ __global__ __launch_bounds__(256) void panel_leaf_kernel(
                     sp[j * R + i] = l;
                 }
                 for (int c = j + 1; c < w; ++c)
-                    sp[c * R + i] = fma(-l, (T)word_double(&prow[2 * c]), sp[c * R + i]);
+                    sp[c * R + i] = fma(-l, (T)word_double(&s_prow[2 * c]), sp[c * R + i]);
             }
         }
         // the next column's step 1 reads s_wv/s_wi only after its own barrier,
@@ -405,78 +358,42 @@ __device__ __forceinline__ const uint32_t *reg_leaf_column(RegLeafState<RPT> &st
     uint64_t *grj = a.rowj + (J & 1) * kRowWords;
     double gv = -1.0;
     int gi = INT_MAX;
-    const uint32_t *prow;
-    bool swap;
-    if (G <= kOnePhaseGroups) {
-        // every slot word in use in one batch
-        const int nw = G * kSlotWords;
-        if (wave == 0) {
-            uint64_t x[kOneBatch];
-            uint32_t valid = 0;
-            auto addr = [&](int k) -> const uint64_t * { return &gs[lane + 64 * k]; };
+    // the candidates first, then the winner's row (and row J when it
+    // moves into this group)
+    const int nc = G * 3;
+    if (wave == 0) {
+        uint64_t x[kCandPerLane];
+        uint32_t valid = 0;
+        auto addr = [&](int k) -> const uint64_t * {
+            const int t = lane + 64 * k;
+            return &gs[(t / 3) * kSlotWords + t % 3];
+        };
 #pragma unroll
-            for (int k = 0; k < kOneBatch; ++k) {
-                const int t = lane + 64 * k, u = t % kSlotWords;
-                const bool use = t < nw && u != 3 && u < 4 + 2 * w;
-                valid |= (uint32_t)use << k;
-                x[k] = use ? ll_load(addr(k)) : 0ull;
-            }
-            ll_gather(x, valid, addr, seq, a.limit, a.flags);
+        for (int k = 0; k < kCandPerLane; ++k) {
+            const bool use = lane + 64 * k < nc;
+            valid |= (uint32_t)use << k;
+            x[k] = use ? ll_load(addr(k)) : 0ull;
+        }
+        ll_gather(x, valid, addr, seq, a.limit, a.flags);
 #pragma unroll
-            for (int k = 0; k < kOneBatch; ++k)
-                if ((valid >> k) & 1u) sh.words[lane + 64 * k] = (uint32_t)x[k];
-        }
-        __syncthreads();
-        for (int t = lane; t < G; t += 64)
-            argmax_merge(gv, gi, words_double(&sh.words[t * kSlotWords]),
-                         (int)sh.words[t * kSlotWords + 2]);
-        wave_argmax_dpp(gv, gi);
-        if (gi < J || gi >= a.m) gi = J;   // expired wait only (see below)
-        prow = &sh.words[(gi / R) * kSlotWords + 4];
-        swap = (gv != 0.0) && gi != J;
-        if (swap && gi >= a.rb && gi < a.rb + a.rows && tid >= 64 && tid < 64 + 2 * w) {
-            const uint64_t *src = &grj[tid - 64];
-            sh.rowj[tid - 64] = ll_wait(src, ll_load(src), seq, a.limit, a.flags);
-        }
-        __syncthreads();
-    } else {
-        // the candidates first, then the winner's row (and row J when it
-        // moves into this group)
-        const int nc = G * 3;
-        if (wave == 0) {
-            uint64_t x[kCandPerLane];
-            uint32_t valid = 0;
-            auto addr = [&](int k) -> const uint64_t * {
-                const int t = lane + 64 * k;
-                return &gs[(t / 3) * kSlotWords + t % 3];
-            };
-#pragma unroll
-            for (int k = 0; k < kCandPerLane; ++k) {
-                const bool use = lane + 64 * k < nc;
-                valid |= (uint32_t)use << k;
-                x[k] = use ? ll_load(addr(k)) : 0ull;
-            }
-            ll_gather(x, valid, addr, seq, a.limit, a.flags);
-#pragma unroll
-            for (int k = 0; k < kCandPerLane; ++k)
-                if ((valid >> k) & 1u) sh.words[lane + 64 * k] = (uint32_t)x[k];
-        }
-        __syncthreads();
-        for (int t = lane; t < G; t += 64)
-            argmax_merge(gv, gi, words_double(&sh.words[3 * t]), (int)sh.words[3 * t + 2]);
-        wave_argmax_dpp(gv, gi);
-        if (gi < J || gi >= a.m) gi = J;   // expired wait only (see below)
-        swap = (gv != 0.0) && gi != J;
-        if (tid < 2 * w) {
-            const uint64_t *src = gs + (size_t)(gi / R) * kSlotWords + 4 + tid;
-            sh.prow[tid] = ll_wait(src, ll_load(src), seq, a.limit, a.flags);
-        } else if (swap && gi >= a.rb && gi < a.rb + a.rows && tid >= 64 && tid < 64 + 2 * w) {
-            const uint64_t *src = &grj[tid - 64];
-            sh.rowj[tid - 64] = ll_wait(src, ll_load(src), seq, a.limit, a.flags);
-        }
-        __syncthreads();
-        prow = sh.prow;
+        for (int k = 0; k < kCandPerLane; ++k)
+            if ((valid >> k) & 1u) sh.words[lane + 64 * k] = (uint32_t)x[k];
     }
+    __syncthreads();
+    for (int t = lane; t < G; t += 64)
+        argmax_merge(gv, gi, words_double(&sh.words[3 * t]), (int)sh.words[3 * t + 2]);
+    wave_argmax_dpp(gv, gi);
+    if (gi < J || gi >= a.m) gi = J;   // expired wait only (see below)
+    const bool swap = (gv != 0.0) && gi != J;
+    if (tid < 2 * w) {
+        const uint64_t *src = gs + (size_t)(gi / R) * kSlotWords + 4 + tid;
+        sh.prow[tid] = ll_wait(src, ll_load(src), seq, a.limit, a.flags);
+    } else if (swap && gi >= a.rb && gi < a.rb + a.rows && tid >= 64 && tid < 64 + 2 * w) {
+        const uint64_t *src = &grj[tid - 64];
+        sh.rowj[tid - 64] = ll_wait(src, ll_load(src), seq, a.limit, a.flags);
+    }
+    __syncthreads();
+    const uint32_t *prow = sh.prow;
     // gi is a valid row >= J (the group holding row J has a candidate); only
     // after an expired wait (stale words) could it have left [J, m), and it
     // was then replaced by J above, so no index leaves the panel
@@ -698,17 +615,6 @@ int leaf_plan(int64_t m, const LeafDevice &d, int64_t *R_out, int64_t *G_out) {
 }
 
 int leaf_device_f64(int cap, LeafDevice *d) { return leaf_device<double>(cap, d); }
-
-template <typename T>
-int panel_leaf_groups(int64_t m, int cap) {
-    if (m <= 0) return 0;
-    LeafDevice d;
-    if (leaf_device<T>(cap, &d)) return -1;
-    int64_t R = 0, G = 0;
-    return leaf_plan(m, d, &R, &G) == kLeafNone ? -1 : (int)G;
-}
-template int panel_leaf_groups<double>(int64_t, int);
-template int panel_leaf_groups<float>(int64_t, int);
 
 template <typename T>
 int panel_leaf(int64_t m, int w, T *P, int64_t ldp, int64_t r0, int32_t *ipiv,
