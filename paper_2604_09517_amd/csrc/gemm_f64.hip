@@ -36,13 +36,6 @@ constexpr int BM = 128, BN = 128, BK = 16;
 constexpr int BST = BN + 4;   // LDS row of a k (padded: 16 k's of a column spread over the banks)
 constexpr int GROUP_M = 8;
 
-// Barrier that orders LDS only, so that global loads stay in flight.
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 __device__ inline void tile_of(int g, int tiles_m, int tiles_n, int &tm, int &tn) {
     const int G = tiles_m * tiles_n;
     // XCD-contiguous remap: id g runs on XCD g % 8.

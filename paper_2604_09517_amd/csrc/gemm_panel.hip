@@ -4,6 +4,7 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "matrix16.h"
 
 namespace {
 
@@ -27,29 +28,6 @@ namespace {
 // rows, N = K = 64 / 128: 22 / 25 -> 7 / 8; 50000 rows, N = K = 256: 200 -> 165.
 constexpr int kTile = 64, kChunk = 32;   // rows of a workgroup, k of a chunk
 constexpr int kBst = 81;   // LDS row of a k: odd, and 4 rows apart in the banks
-
-template <typename T> struct Mat;
-template <> struct Mat<double> {
-    typedef double V4 __attribute__((ext_vector_type(4)));
-    __device__ static V4 mul(double a, double b, V4 c) {
-        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-    }
-    __device__ static int row(int lq, int r) { return lq + 4 * r; }   // of accumulator r
-};
-template <> struct Mat<float> {
-    typedef float V4 __attribute__((ext_vector_type(4)));
-    __device__ static V4 mul(float a, float b, V4 c) {
-        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-    }
-    __device__ static int row(int lq, int r) { return 4 * lq + r; }
-};
-
-// Barrier that orders LDS only, so that global loads stay in flight.
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
 
 // NF: tiles of 16 columns per workgroup.
 template <typename T, int NF>

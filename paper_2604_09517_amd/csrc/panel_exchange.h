@@ -7,17 +7,10 @@
 #include <climits>
 #include <cstdint>
 
+#include "common.h"
 #include "kernels.h"
 
 namespace {
-
-// Barrier that orders LDS only, so that global loads issued before it stay in
-// flight across it.
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
 
 // (value, index) argmax: larger value wins, equal values go to the smaller
 // index (the first maximum, as in BLAS idamax).  NaN never wins.

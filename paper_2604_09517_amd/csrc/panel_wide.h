@@ -82,13 +82,6 @@ __device__ __forceinline__ int first_of(double v, int idx) {
     return __builtin_ctzll(__builtin_amdgcn_ballot_w64(v0 == v && i0 == idx));
 }
 
-// LDS written by some lanes of the wave is read by others after this
-__device__ __forceinline__ void wave_sync_lds() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 struct __attribute__((aligned(16))) WideKey {
     double v;   // the candidate's value
     int idx;    // its position (INT_MAX: no candidate)

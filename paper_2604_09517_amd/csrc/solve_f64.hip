@@ -14,21 +14,6 @@ namespace {
 
 typedef double v4d __attribute__((ext_vector_type(4)));
 
-// Barrier that orders LDS only, so that global loads issued before it stay in
-// flight across it.
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
-// LDS written by some lanes of a wave is read by others after this
-__device__ __forceinline__ void wave_sync_lds() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
 // ---------------------------------------------------------------------------
 // T X = B for up to 16 right-hand sides in one launch, T one of
 //   KIND 0: L (unit lower), forward      KIND 1: U (upper), backward

@@ -7,6 +7,7 @@
 
 #include "common.h"
 #include "kernels.h"
+#include "matrix16.h"
 #include "quarter.h"
 
 namespace {
@@ -35,36 +36,11 @@ namespace {
 // (FP64, n = 5001, all four; now 6.3) and 32 (FP32, n = 3001; now 8).
 constexpr int kStripRows = 16, kWaves = 8;
 
-template <typename T> struct Mat;
-template <> struct Mat<double> {
-    typedef double V4 __attribute__((ext_vector_type(4)));
-    __device__ static V4 mul(double a, double b, V4 c) {
-        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-    }
-    // strip row of row i of the instruction: its accumulators hold rows
-    // lq + 4 r, which are to be strip rows 4 lq + r
-    __device__ static int row(int i) { return 4 * (i & 3) + (i >> 2); }
-};
-template <> struct Mat<float> {
-    typedef float V4 __attribute__((ext_vector_type(4)));
-    __device__ static V4 mul(float a, float b, V4 c) {
-        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-    }
-    __device__ static int row(int i) { return i; }
-};
-
-// Barrier that orders LDS only, so that global loads stay in flight.
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
-// LDS written by some lanes of the wave, read by others.
-__device__ __forceinline__ void wave_sync_lds() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+// Strip row that row i of the instruction stands for, so that lane (li, lq)
+// accumulates strip rows 4 lq + r (FP64 accumulates rows lq + 4 r).
+template <typename T>
+__device__ __forceinline__ int strip_row(int i) {
+    return sizeof(T) == 8 ? 4 * (i & 3) + (i >> 2) : i;
 }
 
 // NQ strips per wave: kb <= 128 NQ; min(8, strips) waves.  NT tiles of 16 columns.
@@ -96,7 +72,7 @@ __global__ __launch_bounds__(64 * kWaves) void trsm_llnu_kernel(int kb, int64_t 
         }
     // tile of strip t's rows and strip s's columns as a matrix operand
     auto tile = [&](int t, int s, T(&a)[4]) {
-        const int row = min(kStripRows * t + Mat<T>::row(li), kb - 1);
+        const int row = min(kStripRows * t + strip_row<T>(li), kb - 1);
         const T *src = L + (size_t)row + (size_t)(kStripRows * s + lq) * ldl;
 #pragma unroll
         for (int kk = 0; kk < 4; ++kk) a[kk] = src[(size_t)(4 * kk) * ldl];
@@ -119,7 +95,7 @@ __global__ __launch_bounds__(64 * kWaves) void trsm_llnu_kernel(int kb, int64_t 
             for (int i = 1, e = 0; i < 4; ++i)
 #pragma unroll
                 for (int k = 0; k < i; ++k, ++e) tri[b][e] = D[t][4 * b + k][4 * b + i];
-            const int i = Mat<T>::row(li);
+            const int i = strip_row<T>(li);
             below[b] = i >= 4 * b + 4 ? D[t][4 * b + lq][i] : (T)0;
         }
 #pragma unroll

@@ -73,20 +73,6 @@ __device__ __forceinline__ uint64_t ll_load(const uint64_t *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// LDS written by some lanes of the wave, read by others.
-__device__ __forceinline__ void wave_sync_lds() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
-
-// Barrier that orders LDS only, so that global accesses stay in flight.
-__device__ __forceinline__ void lds_barrier() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 __device__ __forceinline__ float lane_f32(float v, int l) {
     return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
 }
@@ -349,7 +335,6 @@ __global__ __launch_bounds__(256) void trsv_chain_kernel(
             // strip s's solution, 16 rows behind its solver
             if (active) get(own[wave * (wave + 1) / 2 + s], rr);
             auto group = [&](auto gq) {
-                constexpr int g = decltype(gq)::value;
                 lds_barrier();
                 const float x = xl[s][lane];
                 if (active) terms(rr, x, gq);
