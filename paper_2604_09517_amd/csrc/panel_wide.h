@@ -555,6 +555,11 @@ __global__ __launch_bounds__(NT) void panel_leaf_wide_kernel(int m, int w, T *P,
     for (int J0 = 0; J0 < w; J0 += CW) {   // the halves (or the whole leaf)
         load(J0);
         if (CW < mxlu::kLeafW && J0 > 0) s.second_half(sh, P, lda);
+        // With loads still on their way every masked region waits for some, and
+        // a region with a wait gets a branch round it: with one row per thread
+        // that costs more than the wait for all of them here (the leaves of n =
+        // 1024, NB = 64: 1.31 -> 1.28 ms; of more rows 1 to 2 % the other way).
+        if (RPT == 1) retire_vector_loads();
         for (int jb = 0; jb < Leaf::NB; ++jb) {
             s.template block<0>(sh, J0, jb);
             s.rotate();   // NB rotations bring the columns back to their registers
