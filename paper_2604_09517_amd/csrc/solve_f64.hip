@@ -31,9 +31,9 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 // rows than smaller ones and still leave n / 128 compute units streaming the
 // factor.  Before, every 256 rows took two launches (a diagonal block on one
 // workgroup with a barrier per row, and a row-per-thread update):
-// n = 8192, 16 right-hand sides: 18.0 -> 1.12 ms; n = 32768, one: 12.4 -> 4.4
+// n = 8192, 16 right-hand sides: 18.0 -> 1.14 ms; n = 32768, one: 12.4 -> 4.4
 // (measured with the factors of a matrix of the benchmark recipe).
-// A block takes 7.6 us (L) and 8.2 us (U): eight strips of about 0.7 us and 2
+// A block takes 7.5 us (L) and 8.6 us (U): eight strips of about 0.7 us and 2
 // us for the way to the next workgroup.  With the accumulators' rows spread over
 // the quarter waves the other way, each step exchanged its four rows among all
 // quarters first, and a block took 8.6 and 9.3 us; a substitution with a lane
@@ -298,7 +298,7 @@ __global__ __launch_bounds__(512) void tri_chain_f64_kernel(
     // range (Markstein's theorem); DIV divides.  Returned: whether it did, for d
     // within [2^-500, 2^500]: quotients up to 2^900, and numerators of 2^-390 at
     // least or zero (whose exponent reads as 0; looking at the numerators takes U's
-    // chain of n = 8192, 16 right-hand sides from 527 to 552 us).
+    // chain of n = 8192, 16 right-hand sides from 526 to 548 us).
     auto substitute = [&](auto div, double (&x)[4]) -> bool {
         constexpr bool DIV = decltype(div)::value;
         v4d c = acc;
