@@ -612,12 +612,13 @@ extern "C" int lu_solve(int64_t n, int64_t nrhs, const double *LU, int64_t lda,
     clear_error();
     hipStream_t s = (hipStream_t)stream;
     Scratch scratch(s);
-    static_assert(sizeof(TriSync) == sizeof(double), "one allocation with Y");
+    static_assert(sizeof(TriSync) == sizeof(double), "one allocation, behind Y");
+    const size_t ny = (size_t)n * (size_t)std::min<int64_t>(16, nrhs);
     int32_t *perm = scratch.alloc_n<int32_t>((size_t)n);
-    double *Y = scratch.alloc_n<double>((size_t)n * (size_t)std::min<int64_t>(16, nrhs) + 1);
+    double *Y = scratch.alloc_n<double>(ny + 1);
     if (!perm || !Y) return MXLU_E_NOMEM;
-    return solve_impl(n, nrhs, LU, lda, ipiv, B, ldb, trans, s, perm, Y + 1,
-                      reinterpret_cast<TriSync *>(Y));
+    return solve_impl(n, nrhs, LU, lda, ipiv, B, ldb, trans, s, perm, Y,
+                      reinterpret_cast<TriSync *>(Y + ny));
 }
 
 extern "C" int lu_solve_noalloc(int64_t n, int64_t nrhs, const double *LU, int64_t lda,
