@@ -113,21 +113,25 @@ __global__ __launch_bounds__(512) void tri_chain_f64_kernel(
 
     // -F of the wave's 16 rows, columns p0 .. p0 + BS: lane (li, lq), entry kk
     // is -F[row][p0 + 4 kk + lq] (F: the effective lower or upper factor);
-    // rows and columns past n are zero
+    // rows and columns past n are zero.  L and L^T: F itself, the earlier blocks'
+    // solutions are negated instead, so that nothing waits for the loads before
+    // their block's turn (L, n = 2047 / 12001: 165 / 980 -> 139 / 855 us; U^T
+    // takes 172 for 151 that way, U the same).
+    constexpr bool NEGX = UNIT;
     auto load_f = [&](int64_t p0, double (&a)[BS / 4]) {
         if (p0 + BS <= n && r0 + 16 * v + 16 <= n) {   // uniform
             const double *src = TR ? T + (size_t)(p0 + lq) + (size_t)row * (size_t)ldt
                                    : T + (size_t)row + (size_t)(p0 + lq) * (size_t)ldt;
             const size_t st = TR ? 4 : 4 * (size_t)ldt;
 #pragma unroll
-            for (int kk = 0; kk < BS / 4; ++kk) a[kk] = -src[kk * st];
+            for (int kk = 0; kk < BS / 4; ++kk) a[kk] = NEGX ? src[kk * st] : -src[kk * st];
         } else {
 #pragma unroll
             for (int kk = 0; kk < BS / 4; ++kk) {
                 const int64_t k = p0 + 4 * kk + lq, kc = k < n ? k : n - 1;
                 const double f = TR ? T[(size_t)kc + (size_t)rowc * (size_t)ldt]
                                     : T[(size_t)rowc + (size_t)kc * (size_t)ldt];
-                a[kk] = row < n && k < n ? -f : 0.0;
+                a[kk] = row < n && k < n ? (NEGX ? f : -f) : 0.0;
             }
         }
     };
@@ -137,6 +141,10 @@ __global__ __launch_bounds__(512) void tri_chain_f64_kernel(
     // solution words of the block at p0: thread (row tid % BS, right-hand
     // sides tid / BS + 4 e); rows and columns that do not exist are zero
     const int xr = tid & (BS - 1), xc = tid / BS;
+    auto operand = [](uint64_t x) {   // of the products with F as loaded
+        const double d = __longlong_as_double((long long)x);
+        return NEGX ? -d : d;
+    };
     uint64_t xw[4];
     auto load_x = [&](int64_t p0) {
 #pragma unroll
@@ -186,7 +194,7 @@ __global__ __launch_bounds__(512) void tri_chain_f64_kernel(
     for (int s = 0; s < NS; ++s)
         if (FWD ? s < v : s > v) {
 #pragma unroll
-            for (int kk = 0; kk < 4; ++kk) Ot[tile(v, s)][kk][lane] = a[4 * s + kk];
+            for (int kk = 0; kk < 4; ++kk) Ot[tile(v, s)][kk][lane] = NEGX ? -a[4 * s + kk] : a[4 * s + kk];
         }
 #pragma unroll
     for (int kk = 0; kk < 4; ++kk) {
@@ -216,7 +224,7 @@ __global__ __launch_bounds__(512) void tri_chain_f64_kernel(
         double(*X)[kTriLd] = Xs[t & 1];
 #pragma unroll
         for (int e = 0; e < 4; ++e)
-            X[xr][xc + 4 * e] = __longlong_as_double((long long)xw[e]);
+            X[xr][xc + 4 * e] = operand(xw[e]);
         lds_barrier();
         load_f(block_row(t + 1), an);
         // a block's products are summed by themselves: n / 128 partial sums
@@ -274,7 +282,7 @@ __global__ __launch_bounds__(512) void tri_chain_f64_kernel(
                         x = give_up(spins) ? kTriNaN : tri_load(p);
                     }
                 }
-                X[16 * s + sr][sc] = __longlong_as_double((long long)x);
+                X[16 * s + sr][sc] = operand(x);
             }
             lds_barrier();
 #pragma unroll
