@@ -302,7 +302,7 @@ bool lookahead_fits(int64_t n, int64_t nb, const double *A, int64_t lda,
 
 // Columns of the remaining update given to the update stream while the next
 // panel is factored: about 1.5x what its CUs finish in the panel's expected
-// time (the leaves take 3.2 us per column at 4096 rows and 4.7 at 32768, the
+// time (the leaves take 2.8 us per column at 4096 rows and 4.5 at 32768, the
 // update kernel ~0.24 TFLOP/s per CU).  The rest runs on all CUs once the
 // panel is done, alongside the tail of this part: erring high puts work on the
 // update's CUs that all could share, erring low leaves them idle until the
