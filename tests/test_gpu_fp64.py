@@ -902,3 +902,30 @@ def test_schur_update_tile_choice(api, M, N, K):
     api.schur_update(dC, to_dev(A), to_dev(B))
     torch.cuda.synchronize()
     assert np.array_equal(dC.cpu().numpy(), C - A @ B)
+
+
+@pytest.mark.parametrize("n,nrhs,trans", [(700, 1, False), (2500, 18, True)])
+def test_captured_solve_replays(api, n, nrhs, trans):
+    """lu_solve_noalloc recorded into a graph and replayed on other right-hand
+    sides, with eager solves in between: every replay equals the eager solve bit
+    for bit (the chain's state is cleared by each launch itself)."""
+    note(f"captured solve n={n} nrhs={nrhs} trans={trans}")
+    LU = api.fortran_empty(n, n)
+    api.fill_uniform(LU, 13, inputs.STREAM_A)
+    LU.mul_(1.0 / n)
+    LU.diagonal().add_(1.0)
+    ipiv = torch.arange(n, dtype=torch.int32, device="cuda")
+    B = api.fortran_empty(n, nrhs)
+    api.fill_uniform(B, 1, inputs.STREAM_B)
+    api.lu_solve_noalloc(LU, ipiv, B, trans=trans)   # looks its scratch up
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        api.lu_solve_noalloc(LU, ipiv, B, trans=trans)
+    for k in range(4):
+        api.fill_uniform(B, 20 + k, inputs.STREAM_B)
+        ref = api.lu_solve(LU, ipiv, B.clone(), trans=trans)
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(B, ref)
