@@ -31,7 +31,7 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 // rows than smaller ones and still leave n / 128 compute units streaming the
 // factor.  Before, every 256 rows took two launches (a diagonal block on one
 // workgroup with a barrier per row, and a row-per-thread update):
-// n = 8192, 16 right-hand sides: 18.0 -> 1.14 ms; n = 32768, one: 12.4 -> 4.4
+// n = 8192, 16 right-hand sides: 18.0 -> 1.13 ms; n = 32768, one: 12.4 -> 4.4
 // (measured with the factors of a matrix of the benchmark recipe).
 // A block takes 7.5 us (L) and 8.6 us (U): eight strips of about 0.7 us and 2
 // us for the way to the next workgroup.  With the accumulators' rows spread over
